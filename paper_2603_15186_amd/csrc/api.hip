@@ -68,7 +68,7 @@ struct hgs_ctx {
     DevMem mlp_w, mlp_w32, mlp_dev;
     LodMlpDev mlp_host{};
     double s_hi = 64.0;               // candidate band of the learned cut (pixels)
-    DevMem train_scratch, region_dev, surf;
+    DevMem train_scratch, region_dev, region_part, surf;
     int32_t n_surf = 0;
     // options
     bool sync_check = true, auto_regrow = true, use_graph = false;
@@ -800,7 +800,7 @@ void hgs_destroy(hgs_ctx* c) {
     (void)hipSetDevice(c->device);
     (void)hipDeviceSynchronize();
     DevMem* all[] = {&c->geo, &c->sh, &c->bound, &c->child, &c->leaf_ids, &c->parent, &c->nodefeat, &c->lvl,
-                     &c->train_scratch, &c->region_dev, &c->surf, &c->views,
+                     &c->train_scratch, &c->region_dev, &c->region_part, &c->surf, &c->views,
                      &c->tile_view, &c->mlp_w, &c->mlp_w32, &c->mlp_dev, &c->ranges,
                      &c->counters, &c->sort_k, &c->sort_v, &c->sort_n, &c->sort_hist, &c->px_state, &c->nav_goals, &c->nav_flags,
                      &c->nav_active, &c->nav_steps, &c->egrad, &c->dimg, &c->brec};
@@ -1801,21 +1801,24 @@ hgs_status hgs_downsample2x(hgs_ctx* c, void* stream, const float* src, int32_t 
 
 namespace {
 
-// Check n region descriptors and copy them to the context's device buffer
-// (after the stream's previous work, which may still read it).
-hgs_status upload_regions(hgs_ctx* c, hipStream_t s, int64_t n, const hgs_region* regions) {
+// Check n region descriptors, cut them into chunks and copy them to the
+// context's device buffer (after the stream's previous work, which may still
+// read it and the chunks' sums).
+hgs_status upload_regions(hgs_ctx* c, hipStream_t s, int64_t n, const hgs_region* regions, uint32_t* chunks) {
     std::vector<RegionDev> r((size_t)n);
     for (int64_t i = 0; i < n; ++i) {
         const hgs_region& q = regions[i];
         if (!q.img || !q.ref || q.w < 1 || q.h < 1 || q.x0 < 0 || q.y0 < 0 || q.x0 + q.w > q.ref_w ||
             q.y0 + q.h > q.ref_h)
             return fail(c, HGS_E_INVALID, "region %lld is outside its reference", (long long)i);
-        r[i] = RegionDev{q.img, q.ref, q.w, q.h, q.ref_w, q.ref_h, q.x0, q.y0};
+        r[i] = RegionDev{q.img, q.ref, q.w, q.h, q.ref_w, q.ref_h, q.x0, q.y0, 0, 0, 0};
     }
+    *chunks = plan_regions(r.data(), n);
     HIP_TRY(c, hipSetDevice(c->device));
     hgs_status st;
     HIP_TRY(c, hipStreamSynchronize(s));   // the descriptor buffer is reused
     if ((st = ensure(c, c->region_dev, sizeof(RegionDev) * (size_t)n))) return st;
+    if (*chunks != (uint32_t)n && (st = ensure(c, c->region_part, sizeof(double) * (size_t)*chunks))) return st;
     HIP_TRY(c, hipMemcpy(c->region_dev.p, r.data(), sizeof(RegionDev) * (size_t)n, hipMemcpyHostToDevice));
     return HGS_OK;
 }
@@ -1826,9 +1829,10 @@ hgs_status hgs_region_mse(hgs_ctx* c, void* stream, int32_t n, const hgs_region*
     if (!c || n < 0 || (n > 0 && (!regions || !out))) return HGS_E_INVALID;
     if (n == 0) return HGS_OK;
     hipStream_t s = (hipStream_t)stream;
-    hgs_status st = upload_regions(c, s, n, regions);
+    uint32_t chunks = 0;
+    hgs_status st = upload_regions(c, s, n, regions, &chunks);
     if (st) return st;
-    launch_region_mse(P<RegionDev>(c->region_dev), n, out, s);
+    launch_region_mse(P<RegionDev>(c->region_dev), n, chunks, P<double>(c->region_part), out, s);
     HIP_TRY(c, hipGetLastError());
     return HGS_OK;
 }
@@ -1840,9 +1844,11 @@ hgs_status hgs_lod_labels(hgs_ctx* c, void* stream, int32_t n, const hgs_region*
     if (n > 0x3fffffff) return fail(c, HGS_E_INVALID, "too many candidates");
     if (n == 0) return HGS_OK;
     hipStream_t s = (hipStream_t)stream;
-    hgs_status st = upload_regions(c, s, 2 * (int64_t)n, regions);
+    uint32_t chunks = 0;
+    hgs_status st = upload_regions(c, s, 2 * (int64_t)n, regions, &chunks);
     if (st) return st;
-    launch_lod_labels(P<RegionDev>(c->region_dev), n, (double)label_db, labels, drop_db, s);
+    launch_lod_labels(P<RegionDev>(c->region_dev), n, chunks, P<double>(c->region_part), (double)label_db, labels,
+                      drop_db, s);
     HIP_TRY(c, hipGetLastError());
     return HGS_OK;
 }

@@ -430,7 +430,12 @@ struct RegionDev {
     const float* img;                // planar [3][h][w]
     const float* ref;                // planar [3][ref_h][ref_w]
     int32_t w, h, ref_w, ref_h, x0, y0;
+    int64_t rows;                    // channel rows per chunk (plan_regions)
+    uint32_t blk0;                   // first chunk
+    uint32_t vec;                    // rows of both images can be read 16 bytes at a time
 };
+// Cut n regions into chunks (rows, blk0, vec); returns the number of chunks.
+uint32_t plan_regions(RegionDev* reg, int64_t n);
 void launch_downsample2x(const float* src, int W, int H, float* dst, hipStream_t s);
 // dst = src, `bytes` (a multiple of 16) of 16-byte aligned device memory
 void launch_stream_copy(const void* src, void* dst, size_t bytes, hipStream_t s);
@@ -445,8 +450,11 @@ struct SurfaceDev {
     float r, h;
 };
 void launch_surfaces(const SurfaceDev* surf, int ns, const ViewDev& V, int ss, float* out, hipStream_t s);
-void launch_region_mse(const RegionDev* reg, int n, float* out, hipStream_t s);
+// chunks: plan_regions' count; part: that many doubles (unused when every
+// region is one chunk)
+void launch_region_mse(const RegionDev* reg, int n, uint32_t chunks, double* part, float* out, hipStream_t s);
 // labels[i], drop_db[i] (may be null) from regions 2i (refined) and 2i + 1 (kept)
-void launch_lod_labels(const RegionDev* reg, int n, double label_db, float* labels, float* drop_db, hipStream_t s);
+void launch_lod_labels(const RegionDev* reg, int n, uint32_t chunks, double* part, double label_db, float* labels,
+                       float* drop_db, hipStream_t s);
 
 }  // namespace hgs
