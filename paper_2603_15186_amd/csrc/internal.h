@@ -156,8 +156,8 @@ constexpr int kScanBlocks = 1024;
 constexpr int kCutBlocks = 4096;     // workgroups of a cut level's count and emit passes
 constexpr int kSortBlocks = 1024;
 constexpr int kSortBins = 2048;          // widest radix digit: 11 bits
-constexpr int kSortGroup = 8192;         // histogram groups of the radix sort: multiples of this size,
-constexpr int kSortMaxGroups = 8192;     // at most this many groups per sort
+constexpr int kSortGroup = 8192;         // histogram groups of a large radix sort: multiples of this size,
+constexpr int kSortMaxGroups = 8192;     // at most this many groups per sort (small sorts: smaller groups, at most 512)
 // histogram buffer: per-group counts of every digit, then the digit totals
 constexpr size_t kSortHistBytes = (size_t)kSortBins * (kSortMaxGroups + 1) * 4;
 

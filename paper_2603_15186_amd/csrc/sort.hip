@@ -3,9 +3,7 @@
 // A sort over `bits` key bits runs ceil(bits / D) passes with digits of
 // ceil(bits / passes) bits, D the widest digit allowed (6..11: up to 2048
 // buckets), so a 17-bit tile key takes two or three passes and a 32-bit depth
-// key three to six.  The input is cut into at most kSortMaxGroups groups, each
-// the smallest multiple of kSortGroup elements that keeps their number in that
-// bound; a workgroup takes groups b, b + G, b + 2G, ... so that the groups in flight
+// key three to six.  The input is cut into groups (group_size); a workgroup takes groups b, b + G, b + 2G, ... so that the groups in flight
 // at any moment form one contiguous window of the input and each digit's
 // output advances as one front (writes of neighbouring groups land next to
 // each other and fill whole cache lines).  Each pass is three launches with
@@ -35,12 +33,24 @@ __device__ __forceinline__ uint32_t n_of(const uint32_t* count, uint32_t cap) {
     return n < cap ? n : cap;
 }
 
-// Elements per histogram group of an n-element sort (a multiple of
-// kSortGroup; at most kSortMaxGroups groups).
+// Elements per histogram group of an n-element sort.  A pass over few
+// elements is one sub-tile's latency (load, rank, place, store) per sub-tile
+// that a workgroup takes, so sorts below 512 groups of kSortGroup get smaller
+// groups of one sub-tile each, the smallest that keep their number at 512,
+// two workgroups per compute unit; larger sorts take the smallest multiple of
+// kSortGroup with at most kSortMaxGroups groups.  (A 20,000-element pass in
+// three groups of 8,192: 17.4 us of downsweep; a blocking 256 x 256 render of
+// a 20,000-Gaussian box 236 -> 165 us with groups of 1,024, a 700,000-entry
+// backward step 1.49 -> 1.40 ms.)
+constexpr uint32_t kSmallGroups = 512;
 __device__ __forceinline__ uint32_t group_size(uint32_t n) {
+    if (n <= kSmallGroups * 1024u) return 1024u;
+    if (n <= kSmallGroups * 2048u) return 2048u;
+    if (n <= kSmallGroups * 4096u) return 4096u;
     const uint32_t per = ceil_div(n, (uint32_t)kSortGroup * (uint32_t)kSortMaxGroups);
     return (per > 1u ? per : 1u) * (uint32_t)kSortGroup;
 }
+static_assert(kSortMaxGroups >= (int)kSmallGroups && kSortGroup >= 4096, "small sorts have at most kSmallGroups groups");
 
 // Lanes of the wave (among `active`) whose DB-bit digit equals this lane's.
 template <int DB>
@@ -57,8 +67,7 @@ __device__ __forceinline__ uint64_t match_digit(uint32_t d, uint64_t active) {
 
 // Digit histogram of every group the block owns: per-wave LDS histograms
 // take one atomic add per key (counts do not depend on order), four keys per
-// thread and step with 16-byte loads (groups start at multiples of
-// kSortGroup).
+// thread and step with 16-byte loads (groups start at multiples of 1,024).
 template <int DB>
 __global__ __launch_bounds__(kNT) void k_upsweep(const uint32_t* __restrict__ keys, const uint32_t* count,
                                                  uint32_t cap, int shift, uint32_t MASK, uint32_t* __restrict__ hist,
@@ -123,54 +132,38 @@ __global__ __launch_bounds__(1024) void k_rowscan(uint32_t* __restrict__ hist, c
 // written out in that order so that consecutive lanes store consecutive
 // addresses of one digit's run.
 template <int DB, int ITEMS>
-__global__ __launch_bounds__(kNT) void k_downsweep(const uint32_t* __restrict__ kin, const uint32_t* __restrict__ vin,
-                                                   uint32_t* __restrict__ kout, uint32_t* __restrict__ vout,
-                                                   const uint32_t* count, uint32_t cap, int shift, uint32_t MASK,
-                                                   const uint32_t* __restrict__ hist, uint32_t stride,
-                                                   const uint32_t* __restrict__ totals) {
+struct DownShared {
+    static constexpr int NB = 1 << DB;
+    uint32_t start[NB];                     // first output position of digit d
+    uint32_t off[NB];                       // global position of the next element of digit d
+    uint32_t loc[NB];                       // start of digit d inside the staged sub-tile
+    uint32_t cnt[kNW][NB];
+    uint32_t scan[kNW + 1];
+    uint32_t key[kNT * ITEMS];
+    uint32_t val[kNT * ITEMS];
+};
+
+// The groups of this workgroup in sub-tiles of ITEMS elements per thread.
+template <int DB, int ITEMS, class SH>
+__device__ __forceinline__ void downsweep_groups(SH& S, const uint32_t* __restrict__ kin,
+                                                 const uint32_t* __restrict__ vin, uint32_t* __restrict__ kout,
+                                                 uint32_t* __restrict__ vout, uint32_t n, uint32_t gs, uint32_t ng,
+                                                 int shift, uint32_t MASK, const uint32_t* __restrict__ hist,
+                                                 uint32_t stride) {
     constexpr int NB = 1 << DB;
     constexpr int PER = NB / kNT > 0 ? NB / kNT : 1;      // digits per thread
-    constexpr int SUB = kNT * ITEMS;
-    static_assert(kSortGroup % SUB == 0, "whole sub-tiles per group");
-    __shared__ uint32_t s_start[NB];                     // first output position of digit d
-    __shared__ uint32_t s_off[NB];                       // global position of the next element of digit d
-    __shared__ uint32_t s_loc[NB];                       // start of digit d inside the staged sub-tile
-    __shared__ uint32_t s_cnt[kNW][NB];
-    __shared__ uint32_t s_scan[kNW + 1];
-    __shared__ uint32_t s_key[SUB];
-    __shared__ uint32_t s_val[SUB];
+    constexpr uint32_t SUB = kNT * ITEMS;
     const int t = threadIdx.x;
     const int w = t / kWave, l = lane_id();
-    const uint32_t n = n_of(count, cap);
-    const uint32_t gs = group_size(n), ng = ceil_div(n, gs);
-    if (blockIdx.x >= ng) return;
-    {
-        uint32_t mine[PER];
-        uint32_t sum = 0;
-#pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            const int d = t * PER + k;
-            mine[k] = d < NB ? totals[d] : 0u;
-            sum += mine[k];
-        }
-        uint32_t tot;
-        uint32_t ex = block_excl_scan<kNT>(sum, s_scan, &tot);
-#pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            const int d = t * PER + k;
-            if (d < NB) s_start[d] = ex;
-            ex += mine[k];
-        }
-    }
     for (uint32_t g = blockIdx.x; g < ng; g += gridDim.x) {
         __syncthreads();
-        for (int d = t; d < NB; d += kNT) s_off[d] = s_start[d] + hist[(size_t)d * stride + g];
+        for (int d = t; d < NB; d += kNT) S.off[d] = S.start[d] + hist[(size_t)d * stride + g];
         const uint32_t lo = g * gs;
         const uint32_t hi = min(lo + gs, n);
         for (uint32_t base = lo; base < hi; base += SUB) {
             for (int i = t; i < NB; i += kNT) {
 #pragma unroll
-                for (int k = 0; k < kNW; ++k) s_cnt[k][i] = 0;
+                for (int k = 0; k < kNW; ++k) S.cnt[k][i] = 0;
             }
             __syncthreads();
             uint32_t key[ITEMS], val[ITEMS], rank[ITEMS];
@@ -191,9 +184,9 @@ __global__ __launch_bounds__(kNT) void k_downsweep(const uint32_t* __restrict__ 
                 const uint64_t peers = match_digit<DB>(d, act);
                 const uint64_t below = peers & lanemask_lt();
                 uint32_t before = 0;
-                if (valid) before = s_cnt[w][d];
+                if (valid) before = S.cnt[w][d];
                 rank[r] = before + (uint32_t)__popcll(below);
-                if (valid && below == 0) s_cnt[w][d] = before + (uint32_t)__popcll(peers);
+                if (valid && below == 0) S.cnt[w][d] = before + (uint32_t)__popcll(peers);
             }
             __syncthreads();
             // per digit: local start of each wave's run inside the sub-tile
@@ -206,23 +199,23 @@ __global__ __launch_bounds__(kNT) void k_downsweep(const uint32_t* __restrict__ 
                     uint32_t c = 0;
                     if (d < NB) {
 #pragma unroll
-                        for (int q = 0; q < kNW; ++q) c += s_cnt[q][d];
+                        for (int q = 0; q < kNW; ++q) c += S.cnt[q][d];
                     }
                     mine[k] = c;
                     sum += c;
                 }
                 uint32_t tot;
-                uint32_t ex = block_excl_scan<kNT>(sum, s_scan, &tot);
+                uint32_t ex = block_excl_scan<kNT>(sum, S.scan, &tot);
 #pragma unroll
                 for (int k = 0; k < PER; ++k) {
                     const int d = t * PER + k;
                     if (d < NB) {
-                        s_loc[d] = ex;
+                        S.loc[d] = ex;
                         uint32_t run = ex;
 #pragma unroll
                         for (int q = 0; q < kNW; ++q) {
-                            const uint32_t c = s_cnt[q][d];
-                            s_cnt[q][d] = run;
+                            const uint32_t c = S.cnt[q][d];
+                            S.cnt[q][d] = run;
                             run += c;
                         }
                     }
@@ -235,29 +228,71 @@ __global__ __launch_bounds__(kNT) void k_downsweep(const uint32_t* __restrict__ 
                 const uint32_t i = seg + r * kWave + l;
                 if (i < hi) {
                     const uint32_t d = (key[r] >> shift) & MASK;
-                    const uint32_t p = s_cnt[w][d] + rank[r];
-                    s_key[p] = key[r];
-                    s_val[p] = val[r];
+                    const uint32_t p = S.cnt[w][d] + rank[r];
+                    S.key[p] = key[r];
+                    S.val[p] = val[r];
                 }
             }
             __syncthreads();
-            const uint32_t n_sub = (hi - base) < (uint32_t)SUB ? (hi - base) : (uint32_t)SUB;
+            const uint32_t n_sub = (hi - base) < SUB ? (hi - base) : SUB;
             for (uint32_t p = t; p < n_sub; p += kNT) {
-                const uint32_t k = s_key[p];
+                const uint32_t k = S.key[p];
                 const uint32_t d = (k >> shift) & MASK;
-                const uint32_t pos = s_off[d] + (p - s_loc[d]);
+                const uint32_t pos = S.off[d] + (p - S.loc[d]);
                 kout[pos] = k;
-                vout[pos] = s_val[p];
+                vout[pos] = S.val[p];
             }
+            if (base + SUB >= hi) break;
             __syncthreads();
             // advance each digit's global position by its count in this sub-tile
             for (int d = t; d < NB; d += kNT) {
-                const uint32_t next = (d + 1 < NB) ? s_loc[d + 1] : n_sub;
-                s_off[d] += next - s_loc[d];
+                const uint32_t next = (d + 1 < NB) ? S.loc[d + 1] : n_sub;
+                S.off[d] += next - S.loc[d];
             }
             __syncthreads();
         }
     }
+}
+
+template <int DB, int ITEMS>
+__global__ __launch_bounds__(kNT) void k_downsweep(const uint32_t* __restrict__ kin, const uint32_t* __restrict__ vin,
+                                                   uint32_t* __restrict__ kout, uint32_t* __restrict__ vout,
+                                                   const uint32_t* count, uint32_t cap, int shift, uint32_t MASK,
+                                                   const uint32_t* __restrict__ hist, uint32_t stride,
+                                                   const uint32_t* __restrict__ totals) {
+    constexpr int NB = 1 << DB;
+    constexpr int PER = NB / kNT > 0 ? NB / kNT : 1;      // digits per thread
+    static_assert(kSortGroup % (kNT * ITEMS) == 0, "whole sub-tiles per group");
+    __shared__ DownShared<DB, ITEMS> S;
+    const int t = threadIdx.x;
+    const uint32_t n = n_of(count, cap);
+    const uint32_t gs = group_size(n), ng = ceil_div(n, gs);
+    if (blockIdx.x >= ng) return;
+    {
+        uint32_t mine[PER];
+        uint32_t sum = 0;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const int d = t * PER + k;
+            mine[k] = d < NB ? totals[d] : 0u;
+            sum += mine[k];
+        }
+        uint32_t tot;
+        uint32_t ex = block_excl_scan<kNT>(sum, S.scan, &tot);
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const int d = t * PER + k;
+            if (d < NB) S.start[d] = ex;
+            ex += mine[k];
+        }
+    }
+    // small groups in one sub-tile of fewer elements per thread
+    if (gs == 1024u)
+        downsweep_groups<DB, 4>(S, kin, vin, kout, vout, n, gs, ng, shift, MASK, hist, stride);
+    else if (ITEMS > 8 && gs == 2048u)
+        downsweep_groups<DB, 8>(S, kin, vin, kout, vout, n, gs, ng, shift, MASK, hist, stride);
+    else
+        downsweep_groups<DB, ITEMS>(S, kin, vin, kout, vout, n, gs, ng, shift, MASK, hist, stride);
 }
 
 // One pass over digit bits [shift, shift + nbits) (nbits <= DB).
