@@ -4,9 +4,9 @@
 // Network 8 -> 32 -> 32 -> 1 (ReLU, logit of P(refine)), BF16 weights used
 // in every forward pass, FP32 master weights updated by Adam, FP32
 // accumulation throughout.  Loss: mean binary cross-entropy with logits.
-// Gradient sums run in a fixed order (per-sample terms, then per-chunk
-// partial sums, then the chunks in index order), so a training run is
-// bitwise reproducible.
+// Gradient sums run in a fixed order (within a wave's samples, then the
+// waves of a workgroup, then the workgroups), so a training run is bitwise
+// reproducible.
 #include "device_util.h"
 #include "internal.h"
 #include "lod_mlp.h"
@@ -16,10 +16,6 @@ namespace hgs {
 namespace {
 
 constexpr int kNT = 256;
-// per-sample record of the training pass, stored feature-major [k][n]:
-// x[8], h1[32], h2[32], d1[32] (dL/da1), d2[32] (dL/da2), dz
-constexpr int kOffX = 0, kOffH1 = 8, kOffH2 = 40, kOffD1 = 72, kOffD2 = 104, kOffDz = 136, kActRows = 137;
-
 __device__ __forceinline__ uint16_t f32_to_bf16(float x) {
     uint32_t b = __float_as_uint(x);
     b += 0x7fffu + ((b >> 16) & 1u);   // round to nearest, ties to even
@@ -41,96 +37,235 @@ __global__ __launch_bounds__(kNT) void k_mlp_forward(const float* __restrict__ f
     }
 }
 
-// Forward and backward of one sample per thread; loss partial per block.
-__global__ __launch_bounds__(kNT) void k_mlp_fwd_bwd(const float* __restrict__ feats, const float* __restrict__ labels,
-                                                     uint32_t n, MlpNorm nm, const uint16_t* __restrict__ w,
-                                                     float* __restrict__ act, float* __restrict__ loss_part) {
-    __shared__ float s_w[kMlpParams];
-    __shared__ float s_red[kNT];
-    for (int i = threadIdx.x; i < kMlpParams; i += kNT) s_w[i] = bf16_to_f32(w[i]);
-    __syncthreads();
-    const uint32_t s = blockIdx.x * kNT + threadIdx.x;
-    float lossv = 0.f;
-    if (s < n) {
-        float x[kMlpIn], a1[kMlpH], h1[kMlpH], a2[kMlpH], h2[kMlpH];
+// Sum over the 16 lanes that hold one lane group's samples (lanes 16 g ..
+// 16 g + 15), in every lane.
+__device__ __forceinline__ float sum16(float x) {
 #pragma unroll
-        for (int i = 0; i < kMlpIn; ++i) x[i] = (feats[(size_t)s * kMlpIn + i] - nm.mean[i]) * nm.inv_std[i];
-#pragma unroll
-        for (int j = 0; j < kMlpH; ++j) {
-            float acc = s_w[kOffB1 + j];
-#pragma unroll
-            for (int i = 0; i < kMlpIn; ++i) acc = fmaf(s_w[kOffW1 + j * kMlpIn + i], x[i], acc);
-            a1[j] = acc;
-            h1[j] = acc > 0.f ? acc : 0.f;
-        }
-        float z = s_w[kOffB3];
-#pragma unroll
-        for (int j = 0; j < kMlpH; ++j) {
-            float acc = s_w[kOffB2 + j];
-#pragma unroll
-            for (int i = 0; i < kMlpH; ++i) acc = fmaf(s_w[kOffW2 + j * kMlpH + i], h1[i], acc);
-            a2[j] = acc;
-            h2[j] = acc > 0.f ? acc : 0.f;
-            z = fmaf(s_w[kOffW3 + j], h2[j], z);
-        }
-        const float y = labels[s];
-        lossv = fmaxf(z, 0.f) + log1pf(expf(-fabsf(z))) - y * z;
-        const float p = 1.f / (1.f + expf(-z));
-        const float dz = (p - y) / (float)n;
-        float d2[kMlpH];
-#pragma unroll
-        for (int j = 0; j < kMlpH; ++j) d2[j] = a2[j] > 0.f ? dz * s_w[kOffW3 + j] : 0.f;
-        float d1[kMlpH];
-#pragma unroll
-        for (int i = 0; i < kMlpH; ++i) {
-            float acc = 0.f;
-#pragma unroll
-            for (int j = 0; j < kMlpH; ++j) acc = fmaf(s_w[kOffW2 + j * kMlpH + i], d2[j], acc);
-            d1[i] = a1[i] > 0.f ? acc : 0.f;
-        }
-#pragma unroll
-        for (int i = 0; i < kMlpIn; ++i) act[(size_t)(kOffX + i) * n + s] = x[i];
-#pragma unroll
-        for (int j = 0; j < kMlpH; ++j) {
-            act[(size_t)(kOffH1 + j) * n + s] = h1[j];
-            act[(size_t)(kOffH2 + j) * n + s] = h2[j];
-            act[(size_t)(kOffD1 + j) * n + s] = d1[j];
-            act[(size_t)(kOffD2 + j) * n + s] = d2[j];
-        }
-        act[(size_t)kOffDz * n + s] = dz;
-    }
-    // fixed-order tree reduction of the block's losses
-    s_red[threadIdx.x] = lossv;
-    __syncthreads();
-    for (int o = kNT / 2; o > 0; o >>= 1) {
-        if (threadIdx.x < o) s_red[threadIdx.x] += s_red[threadIdx.x + o];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) loss_part[blockIdx.x] = s_red[0];
+    for (int d = 1; d < 16; d <<= 1) x += __shfl_xor(x, d, kWave);
+    return x;
 }
 
-// Partial gradient of parameter p over the samples of chunk blockIdx.y.
-__global__ __launch_bounds__(kNT) void k_mlp_grad_partial(const float* __restrict__ act, uint32_t n, uint32_t chunk,
-                                                          float* __restrict__ partial) {
-    const int p = blockIdx.x * kNT + threadIdx.x;
-    if (p >= kMlpParams) return;
-    const uint32_t lo = blockIdx.y * chunk, hi = min(n, lo + chunk);
-    int ra, rb = -1;   // act rows: gradient = sum_s act[ra][s] * act[rb][s] (rb < 0: just act[ra])
-    if (p < kOffB1) { ra = kOffD1 + (p - kOffW1) / kMlpIn; rb = kOffX + (p - kOffW1) % kMlpIn; }
-    else if (p < kOffW2) { ra = kOffD1 + (p - kOffB1); }
-    else if (p < kOffB2) { ra = kOffD2 + (p - kOffW2) / kMlpH; rb = kOffH1 + (p - kOffW2) % kMlpH; }
-    else if (p < kOffW3) { ra = kOffD2 + (p - kOffB2); }
-    else if (p < kOffB3) { ra = kOffDz; rb = kOffH2 + (p - kOffW3); }
-    else { ra = kOffDz; }
-    const float* A = act + (size_t)ra * n;
-    float acc = 0.f;
-    if (rb >= 0) {
-        const float* B = act + (size_t)rb * n;
-        for (uint32_t s = lo; s < hi; ++s) acc = fmaf(A[s], B[s], acc);
-    } else {
-        for (uint32_t s = lo; s < hi; ++s) acc += A[s];
+// Forward, loss, backward and the workgroup's share of every parameter's
+// gradient, on the FP32 matrix cores (16x16x4, FP32 products and sums).
+//
+// A wave takes 16 samples at a time.  Layers run with the samples as the N
+// dimension (lane l, register r of an accumulator: unit 4 (l / 16) + r of a
+// 16-unit tile, sample l % 16), where a layer's accumulators are the next
+// product's B operand as they stand: a1 = W1 x, a2 = W2 h1, and back through
+// W2^T for d1 = dL/da1.  The weight gradients contract over the samples
+// (dW2 = d2 h1^T, dW1 = d1 x^T): h1, d1 and d2 go through LDS once to put
+// the samples on the K dimension, and the 32 x 32 and 32 x 8 sums stay in
+// accumulators over all of the wave's samples.  Bias and output gradients
+// are per-lane sums, added over the 16 samples at the end.
+//
+// What bounds it: latency.  4,096 samples are 60 matrix instructions for
+// each of 256 waves; one thread per sample with its record written to memory
+// and a thread per parameter walking the records took 47 + 96 us, this
+// kernel 9.9 (and the whole step 147 -> 13.6 us).
+constexpr int kTrainWaves = kNT / kWave;
+constexpr int kTStride = kMlpH + 4;        // LDS row of 32 units, 16-byte aligned
+
+__global__ __launch_bounds__(kNT) void k_mlp_train(const float* __restrict__ feats, const float* __restrict__ labels,
+                                                   uint32_t n, MlpNorm nm, const uint16_t* __restrict__ w,
+                                                   uint32_t tiles_per_wave, float* __restrict__ partial,
+                                                   float* __restrict__ loss_part) {
+    __shared__ float s_w[kMlpParams];
+    __shared__ float s_norm[2 * kMlpIn];
+    __shared__ __align__(16) float s_t[kTrainWaves][3][16 * kTStride];    // h1, d1, d2
+    __shared__ float s_x[kTrainWaves][16 * kMlpXStride];
+    __shared__ float s_loss[kTrainWaves];
+    float (*s_g)[kMlpParams] = reinterpret_cast<float (*)[kMlpParams]>(&s_t[0][0][0]);   // at the end
+    static_assert(sizeof(s_t) >= sizeof(float) * kTrainWaves * kMlpParams, "gradients overlay the staging rows");
+    for (int i = threadIdx.x; i < kMlpParams; i += kNT) s_w[i] = bf16_to_f32(w[i]);
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int i = 0; i < kMlpIn; ++i) {
+            s_norm[i] = nm.mean[i];
+            s_norm[kMlpIn + i] = nm.inv_std[i];
+        }
     }
-    partial[(size_t)blockIdx.y * kMlpParams + p] = acc;
+    __syncthreads();
+    const int wv = threadIdx.x / kWave, l = lane_id(), lr = l & 15, lg = l >> 4;
+    // operands of this lane: W1 and W2 rows (A of the forward), W2 columns
+    // (A of the way back), biases and output weights of its units
+    float a1[2][2], a2[2][2][4], ab[2][2][4], b1[2][4], b2[2][4], w3[2][4];
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) a1[m][q] = s_w[kOffW1 + (16 * m + lr) * kMlpIn + 4 * q + lg];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int u = 16 * m + 4 * lg + r;
+            b1[m][r] = s_w[kOffB1 + u];
+            b2[m][r] = s_w[kOffB2 + u];
+            w3[m][r] = s_w[kOffW3 + u];
+#pragma unroll
+            for (int mp = 0; mp < 2; ++mp) {
+                const int k = 16 * mp + 4 * lg + r;
+                a2[m][mp][r] = s_w[kOffW2 + (16 * m + lr) * kMlpH + k];
+                ab[m][mp][r] = s_w[kOffW2 + k * kMlpH + 16 * m + lr];
+            }
+        }
+    }
+    const float b3 = s_w[kOffB3];
+    mlp_f4 gw2[2][2], gw1[2];
+    float gb1[2][4], gb2[2][4], gw3[2][4], gb3 = 0.f, loss = 0.f;
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+        gw1[m] = mlp_f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int q = 0; q < 2; ++q) gw2[m][q] = mlp_f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int r = 0; r < 4; ++r) gb1[m][r] = gb2[m][r] = gw3[m][r] = 0.f;
+    }
+    float* th1 = s_t[wv][0];
+    float* td1 = s_t[wv][1];
+    float* td2 = s_t[wv][2];
+    float* tx = s_x[wv];
+    const uint32_t tile0 = (blockIdx.x * kTrainWaves + wv) * tiles_per_wave;
+    // every wave of the workgroup runs the same number of tiles (the
+    // barriers below); tiles past the end hold no samples and add nothing
+    for (uint32_t tl = 0; tl < tiles_per_wave; ++tl) {
+        const uint64_t s0 = (uint64_t)(tile0 + tl) * 16;
+        // standardised features of 16 samples, two per lane
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int k = 2 * l + q, sm = k / kMlpIn, f = k % kMlpIn;
+            const bool in = s0 + sm < n;
+            const float v = in ? feats[s0 * kMlpIn + k] : 0.f;
+            tx[sm * kMlpXStride + f] = in ? (v - s_norm[f]) * s_norm[kMlpIn + f] : 0.f;
+        }
+        const bool valid = s0 + lr < n;
+        const float y = valid ? labels[s0 + lr] : 0.f;
+        __syncthreads();
+        mlp_f4 h1[2], h2[2];
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            h1[m] = mlp_f4{b1[m][0], b1[m][1], b1[m][2], b1[m][3]};
+            h2[m] = mlp_f4{b2[m][0], b2[m][1], b2[m][2], b2[m][3]};
+        }
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const float x = tx[lr * kMlpXStride + 4 * q + lg];
+#pragma unroll
+            for (int m = 0; m < 2; ++m) h1[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1[m][q], x, h1[m], 0, 0, 0);
+        }
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) h1[m][r] = h1[m][r] > 0.f ? h1[m][r] : 0.f;
+#pragma unroll
+        for (int mp = 0; mp < 2; ++mp)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int m = 0; m < 2; ++m)
+                    h2[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(a2[m][mp][r], h1[mp][r], h2[m], 0, 0, 0);
+        float z = 0.f;
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                h2[m][r] = h2[m][r] > 0.f ? h2[m][r] : 0.f;
+                z = fmaf(w3[m][r], h2[m][r], z);
+            }
+        z += __shfl_xor(z, 16, kWave);
+        z += __shfl_xor(z, 32, kWave);
+        z += b3;                                   // in every lane group: the logit of sample lr
+        const float p = 1.f / (1.f + expf(-z));
+        const float dz = valid ? (p - y) / (float)n : 0.f;
+        if (valid && lg == 0) {
+            loss += fmaxf(z, 0.f) + log1pf(expf(-fabsf(z))) - y * z;
+            gb3 += dz;
+        }
+        mlp_f4 d1[2], d2[2];
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            d1[m] = mlp_f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                d2[m][r] = h2[m][r] > 0.f ? dz * w3[m][r] : 0.f;
+                gw3[m][r] = fmaf(dz, h2[m][r], gw3[m][r]);
+                gb2[m][r] += d2[m][r];
+            }
+        }
+#pragma unroll
+        for (int mp = 0; mp < 2; ++mp)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int m = 0; m < 2; ++m)
+                    d1[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(ab[m][mp][r], d2[mp][r], d1[m], 0, 0, 0);
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                d1[m][r] = h1[m][r] > 0.f ? d1[m][r] : 0.f;
+                gb1[m][r] += d1[m][r];
+            }
+            const int at = lr * kTStride + 16 * m + 4 * lg;
+            *reinterpret_cast<mlp_f4*>(th1 + at) = h1[m];
+            *reinterpret_cast<mlp_f4*>(td1 + at) = d1[m];
+            *reinterpret_cast<mlp_f4*>(td2 + at) = d2[m];
+        }
+        __syncthreads();
+        // samples on K: step r takes samples 4 lg + r
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int row = 4 * lg + r;
+            const float x = lr < kMlpIn ? tx[row * kMlpXStride + lr] : 0.f;
+            float hb[2], da[2], db[2];
+#pragma unroll
+            for (int m = 0; m < 2; ++m) {
+                hb[m] = th1[row * kTStride + 16 * m + lr];
+                da[m] = td1[row * kTStride + 16 * m + lr];
+                db[m] = td2[row * kTStride + 16 * m + lr];
+            }
+#pragma unroll
+            for (int m = 0; m < 2; ++m) {
+                gw1[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(da[m], x, gw1[m], 0, 0, 0);
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+                    gw2[m][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(db[m], hb[q], gw2[m][q], 0, 0, 0);
+            }
+        }
+        __syncthreads();
+    }
+    float* g = s_g[wv];
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int u = 16 * m + 4 * lg + r;
+            if (lr < kMlpIn) g[kOffW1 + u * kMlpIn + lr] = gw1[m][r];
+#pragma unroll
+            for (int q = 0; q < 2; ++q) g[kOffW2 + u * kMlpH + 16 * q + lr] = gw2[m][q][r];
+            const float sb1 = sum16(gb1[m][r]), sb2 = sum16(gb2[m][r]), s3 = sum16(gw3[m][r]);
+            if (lr == 0) {
+                g[kOffB1 + u] = sb1;
+                g[kOffB2 + u] = sb2;
+                g[kOffW3 + u] = s3;
+            }
+        }
+    gb3 = sum16(gb3);                              // lanes 0-15 hold the samples' terms
+    loss = sum16(loss);
+    if (l == 0) {
+        g[kOffB3] = gb3;
+        s_loss[wv] = loss;
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < kMlpParams; i += kNT) {
+        float t = 0.f;
+#pragma unroll
+        for (int q = 0; q < kTrainWaves; ++q) t += s_g[q][i];
+        partial[(size_t)blockIdx.x * kMlpParams + i] = t;
+    }
+    if (threadIdx.x == 0) {
+        float t = 0.f;
+#pragma unroll
+        for (int q = 0; q < kTrainWaves; ++q) t += s_loss[q];
+        loss_part[blockIdx.x] = t;
+    }
 }
 
 struct AdamArgs {
@@ -147,16 +282,33 @@ struct AdamArgs {
     uint32_t n;
 };
 
+// Sum of every parameter's partial gradients and the Adam step: 32
+// parameters per workgroup, the chunks dealt to eight slices of 32 threads
+// whose loads are in flight together, the slices added in order.
+constexpr int kAdamPer = 32, kAdamSlices = kNT / kAdamPer;
+
 __global__ __launch_bounds__(kNT) void k_mlp_reduce_adam(const float* __restrict__ partial, uint32_t chunks, AdamArgs a) {
-    const int p = blockIdx.x * kNT + threadIdx.x;
-    if (p == 0 && a.loss_out) {
+    __shared__ float sh[kAdamSlices][kAdamPer];
+    const int k = threadIdx.x % kAdamPer, sl = threadIdx.x / kAdamPer;
+    const int p = blockIdx.x * kAdamPer + k;
+    if (blockIdx.x == 0 && threadIdx.x < kWave && a.loss_out) {
         float t = 0.f;
-        for (uint32_t i = 0; i < a.n_loss_part; ++i) t += a.loss_part[i];
-        *a.loss_out = t / (float)a.n;
+        for (uint32_t i = threadIdx.x; i < a.n_loss_part; i += kWave) t += a.loss_part[i];
+#pragma unroll
+        for (int d = kWave / 2; d >= 1; d >>= 1) t += __shfl_xor(t, d, kWave);
+        if (threadIdx.x == 0) *a.loss_out = t / (float)a.n;
     }
-    if (p >= kMlpParams) return;
+    float part = 0.f;
+    if (p < kMlpParams) {
+#pragma unroll 8
+        for (uint32_t c = sl; c < chunks; c += kAdamSlices) part += partial[(size_t)c * kMlpParams + p];
+    }
+    sh[sl][k] = part;
+    __syncthreads();
+    if (sl != 0 || p >= kMlpParams) return;
     float g = 0.f;
-    for (uint32_t c = 0; c < chunks; ++c) g += partial[(size_t)c * kMlpParams + p];
+#pragma unroll
+    for (int q = 0; q < kAdamSlices; ++q) g += sh[q][k];
     if (a.grad_out) a.grad_out[p] = g;
     if (a.lr > 0.f) {
         const float m = a.beta1 * a.m[p] + (1.f - a.beta1) * g;
@@ -220,10 +372,11 @@ void launch_mlp_forward(const float* feats, uint32_t n, const float* mean, const
     k_mlp_forward<<<grid, kNT, 0, s>>>(feats, n, nm, w, logits);
 }
 
-size_t mlp_train_scratch_floats(uint32_t n) {
-    const uint32_t chunks = min(64u, max(1u, ceil_div(n, 512u)));
-    return (size_t)kActRows * n + (size_t)chunks * kMlpParams + ceil_div(n, (uint32_t)kNT) + 16;
-}
+// Workgroups of a training pass: a tile of 16 samples for each wave, up to
+// one workgroup per compute unit; then more tiles per wave.
+static uint32_t train_blocks(uint32_t n) { return min(256u, max(1u, ceil_div(n, 16u * kTrainWaves))); }
+
+size_t mlp_train_scratch_floats(uint32_t n) { return (size_t)train_blocks(n) * (kMlpParams + 1); }
 
 void launch_mlp_train_step(const float* feats, const float* labels, uint32_t n, const float* mean, const float* stdv,
                            float* master, uint16_t* w, float* m, float* v, int step, float lr, float* grad_out,
@@ -233,15 +386,11 @@ void launch_mlp_train_step(const float* feats, const float* labels, uint32_t n, 
         nm.mean[i] = mean[i];
         nm.inv_std[i] = 1.f / stdv[i];
     }
-    const uint32_t chunks = min(64u, max(1u, ceil_div(n, 512u)));
-    const uint32_t chunk = ceil_div(n, chunks);
-    const uint32_t nblk = ceil_div(n, (uint32_t)kNT);
-    float* act = scratch;
-    float* partial = act + (size_t)kActRows * n;
-    float* loss_part = partial + (size_t)chunks * kMlpParams;
-    k_mlp_fwd_bwd<<<nblk, kNT, 0, s>>>(feats, labels, n, nm, w, act, loss_part);
-    dim3 g((kMlpParams + kNT - 1) / kNT, chunks);
-    k_mlp_grad_partial<<<g, kNT, 0, s>>>(act, n, chunk, partial);
+    const uint32_t nblk = train_blocks(n);
+    const uint32_t tiles_per_wave = ceil_div(ceil_div(n, 16u), nblk * kTrainWaves);
+    float* partial = scratch;
+    float* loss_part = partial + (size_t)nblk * kMlpParams;
+    k_mlp_train<<<nblk, kNT, 0, s>>>(feats, labels, n, nm, w, tiles_per_wave, partial, loss_part);
     AdamArgs a;
     a.master = master;
     a.w = w;
@@ -257,7 +406,7 @@ void launch_mlp_train_step(const float* feats, const float* labels, uint32_t n, 
     a.loss_part = loss_part;
     a.n_loss_part = nblk;
     a.n = n;
-    k_mlp_reduce_adam<<<(kMlpParams + kNT - 1) / kNT, kNT, 0, s>>>(partial, chunks, a);
+    k_mlp_reduce_adam<<<(kMlpParams + kAdamPer - 1) / kAdamPer, kNT, 0, s>>>(partial, nblk, a);
 }
 
 void launch_mlp_adam(const float* grad, float* master, uint16_t* w, float* m, float* v, int step, float lr,
@@ -278,7 +427,7 @@ void launch_mlp_adam(const float* grad, float* master, uint16_t* w, float* m, fl
     a.n_loss_part = 0;
     a.n = 1;
     // one "chunk": the gradient itself, summed as g = 0 + grad, exactly grad
-    k_mlp_reduce_adam<<<(kMlpParams + kNT - 1) / kNT, kNT, 0, s>>>(grad, 1, a);
+    k_mlp_reduce_adam<<<(kMlpParams + kAdamPer - 1) / kAdamPer, kNT, 0, s>>>(grad, 1, a);
 }
 
 void launch_bf16_from_master(const float* master, uint16_t* w, hipStream_t s) {
