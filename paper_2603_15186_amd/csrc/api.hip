@@ -194,13 +194,6 @@ bool pair_keys_fit(int n_views, uint64_t max_view_tiles) {
     return max_view_tiles < (1ull << 31) && bits_for((uint32_t)n_views) + bits_for((uint32_t)max_view_tiles) <= 31;
 }
 
-__global__ void k_reset(Counters* c) {
-    if (threadIdx.x == 0) {
-        Counters z = {};
-        *c = z;
-    }
-}
-
 hgs_status alloc_work(hgs_ctx* c) {
     hgs_status s;
     const size_t F = c->frontier_cap, M = c->cut_cap, Pc = c->pair_cap;
@@ -220,7 +213,7 @@ hgs_status alloc_work(hgs_ctx* c) {
         if ((s = ensure(c, w.ntiles, M * 4))) return s;
         if ((s = ensure(c, w.bins, M * sizeof(BinRec)))) return s;
         if ((s = ensure(c, w.offsets, M * 4))) return s;
-        if ((s = ensure(c, w.scan_tmp, (std::max(kScanBlocks, kCutBlocks) + 1) * sizeof(uint4)))) return s;
+        if ((s = ensure(c, w.scan_tmp, kScanTmp * sizeof(uint4)))) return s;
         if ((s = ensure(c, w.hist, kSortHistBytes))) return s;
     }
     return HGS_OK;
@@ -387,7 +380,6 @@ void enqueue_pass(hgs_ctx* c, hipStream_t s, int g) {
     const uint32_t t0 = pass_tile0(c, g), t1 = pass_tile0(c, g + 1);
     if (c->stage_timing && c->ev_used >= 6 * 512) (void)harvest_events(c);
     mark(c, 0, s);
-    k_reset<<<1, 64, 0, s>>>(ctr);
     CutArgs ca{};
     ca.bound = P<float4>(c->bound);
     ca.child = P<int2>(c->child);
@@ -1625,7 +1617,6 @@ hgs_status hgs_lod_candidates(hgs_ctx* c, void* stream, float s_hi, uint32_t* en
     if ((st = upload_views(c, s, none.data()))) return st;
     for (int attempt = 0; attempt < 8; ++attempt) {
         Counters* ctr = P<Counters>(c->counters);
-        k_reset<<<1, 64, 0, s>>>(ctr);
         CutArgs ca{};
         ca.bound = P<float4>(c->bound);
         ca.child = P<int2>(c->child);

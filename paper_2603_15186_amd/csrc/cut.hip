@@ -6,13 +6,17 @@
 // a node's views mostly next to each other (see k_level_emit).  Per level:
 //   count : each block decides its contiguous chunk (in the learned cut the
 //           network settles the candidates right there), stores the
-//           decisions and reduces (emitted, children) counts;
-//   scan  : one block scans the per-block counts, advances the cut size and
-//           sets the next frontier size (capacity checks here);
-//   emit  : each block reads its chunk's decisions back, scans within the
-//           block and writes emitted ids and child ids in order.
+//           decisions and reduces (emitted, children) counts, which are also
+//           added to the bin of its 64 neighbours;
+//   emit  : each block adds the bins and blocks before it, reads its chunk's
+//           decisions back, scans within the block and writes emitted ids
+//           and child ids in order; block 0 advances the cut size and sets
+//           the next frontier size (capacity checks here).
 // A level's grid is sized to its frontier's bound (nodes of the level times
-// views), at most kCutBlocks workgroups.
+// views), at most kCutBlocks workgroups.  The leading levels of at most
+// kTopEntries entries run in one launch of one workgroup (k_cut_top).
+// A launch of a small level costs 3 to 6 us whatever it does: a level was
+// three launches with a one-block scan of the counts between the two.
 // Ids come out ascending per view because ids are level-major, children
 // of a node are contiguous and ordered like their parents, and each view's
 // entries keep their order through the emission.
@@ -30,6 +34,11 @@ namespace {
 
 constexpr int kNT = 256;
 constexpr int kNW = kNT / kWave;
+static_assert(kCutBins * kWave == kCutBlocks, "a bin per 64 blocks");
+
+// Leading levels of at most this many entries (nodes x views) run in the one
+// workgroup of k_cut_top, an entry per thread.
+constexpr int kTopEntries = 1024;
 
 enum : uint32_t { kDrop = 0, kEmit = 1, kExpand = 2, kCandidate = 4 };
 
@@ -68,12 +77,14 @@ struct LevelCtx {
     const ViewDev* views;
     int n_views;
     const uint2* in;
-    uint32_t* in_count;
     uint2* out;
+    uint32_t in_cap;
     uint32_t out_cap;
     uint2* cut;
     uint32_t cut_cap;
-    uint4* tmp;               // [G] block counts, then offsets; [G] = level bases
+    uint4* fine;              // [G] block counts
+    uint4* bins;              // [kCutBins] sums of 64 blocks' counts, zero before the level
+    uint4* lvl;               // per level: (frontier entries, cut entries and candidates before it)
     uint8_t* dec;             // per frontier entry: decision of the count pass
     bool defer;               // learned cut: the count pass lets the network settle candidates
     const float* w32;         // learned cut: FP32 weights (uniform: read through the scalar cache)
@@ -86,7 +97,6 @@ struct LevelCtx {
     int level;
     bool leaves;              // the last level: every node is a leaf (no child ranges to read)
     bool group;               // children laid out child-major per group of a node's views
-    int out_slot;             // index of the next frontier's counter
 };
 
 __device__ __forceinline__ void chunk_of(uint32_t n, int G, int b, uint32_t* lo, uint32_t* hi) {
@@ -122,78 +132,87 @@ constexpr int kLdsViews = 64;
 constexpr int kCutViewWords = (int)((offsetof(ViewDev, nb) + sizeof(double)) / 8);
 static_assert(offsetof(ViewDev, o) == 0 && offsetof(ViewDev, nb) % 8 == 0, "views start with their FP64 words");
 
-template <bool DEFER>
-__global__ __launch_bounds__(kNT) void k_level_count(LevelCtx c, uint32_t in_cap) {
-    __shared__ uint4 sh[kNT / kWave + 1];
-    __shared__ float s_x[DEFER ? kNT * kMlpXStride : 1];
-    __shared__ float s_w[DEFER ? kMlpParams : 1];  // the network's FP32 weights
-    __shared__ uint64_t s_view[kLdsViews * kCutViewWords];
-    __shared__ int32_t s_keep[kLdsViews];
-    uint32_t n = *c.in_count;
-    n = n < in_cap ? n : in_cap;
-    uint32_t lo, hi;
-    chunk_of(n, gridDim.x, blockIdx.x, &lo, &hi);
-    if (lo >= hi) {
-        if (threadIdx.x == 0) c.tmp[blockIdx.x] = make_uint4(0, 0, 0, 0);
-        return;
-    }
+template <bool DEFER, int NT>
+struct CountShared {
+    float x[DEFER ? NT * kMlpXStride : 1];
+    float w[DEFER ? kMlpParams : 1];               // the network's FP32 weights
+    uint64_t view[kLdsViews * kCutViewWords];
+    int32_t keep[kLdsViews];
+};
+
+// (view-major frontiers keep a wave on one view: scalar loads serve it)
+__device__ __forceinline__ bool use_lds_views(const LevelCtx& c) { return c.group && c.n_views <= kLdsViews; }
+
+template <bool DEFER, int NT>
+__device__ __forceinline__ void stage_count(const LevelCtx& c, CountShared<DEFER, NT>& S) {
     if (DEFER)
-        for (int k = threadIdx.x; k < kMlpParams; k += kNT) s_w[k] = c.w32[k];
-    // (view-major frontiers keep a wave on one view: scalar loads serve it)
-    const bool lds_views = c.group && c.n_views <= kLdsViews;
-    if (lds_views) {
+        for (int k = threadIdx.x; k < kMlpParams; k += NT) S.w[k] = c.w32[k];
+    if (use_lds_views(c)) {
         const uint64_t* src = reinterpret_cast<const uint64_t*>(c.views);
-        for (int k = threadIdx.x; k < c.n_views * kCutViewWords; k += kNT) {
+        for (int k = threadIdx.x; k < c.n_views * kCutViewWords; k += NT) {
             const int v = k / kCutViewWords, q = k - v * kCutViewWords;
-            s_view[k] = src[(size_t)v * (sizeof(ViewDev) / 8) + q];
+            S.view[k] = src[(size_t)v * (sizeof(ViewDev) / 8) + q];
         }
-        for (int v = threadIdx.x; v < c.n_views; v += kNT) s_keep[v] = c.views[v].keep_node;
-        __syncthreads();
+        for (int v = threadIdx.x; v < c.n_views; v += NT) S.keep[v] = c.views[v].keep_node;
     }
-    // f applied to view v (the staged words; the others, which neither the
-    // node test nor the features read, stay zero)
-    auto with_view = [&](uint32_t v, auto&& f) {
-        if (lds_views) {
-            uint64_t wd[sizeof(ViewDev) / 8];
+    __syncthreads();
+}
+
+// f applied to view v (the staged words; the others, which neither the node
+// test nor the features read, stay zero).
+template <bool DEFER, int NT, class F>
+__device__ __forceinline__ auto with_view(const LevelCtx& c, const CountShared<DEFER, NT>& S, uint32_t v, F&& f) {
+    if (use_lds_views(c)) {
+        uint64_t wd[sizeof(ViewDev) / 8];
 #pragma unroll
-            for (int q = 0; q < (int)(sizeof(ViewDev) / 8); ++q)
-                wd[q] = q < kCutViewWords ? s_view[v * kCutViewWords + q] : 0ull;
-            ViewDev V;
-            __builtin_memcpy(&V, wd, sizeof V);
-            V.keep_node = s_keep[v];
-            return f(V);
-        }
-        return on_view(c.views, v, f);
-    };
-    const int w = threadIdx.x / kWave;
+        for (int q = 0; q < (int)(sizeof(ViewDev) / 8); ++q)
+            wd[q] = q < kCutViewWords ? S.view[v * kCutViewWords + q] : 0ull;
+        ViewDev V;
+        __builtin_memcpy(&V, wd, sizeof V);
+        V.keep_node = S.keep[v];
+        return f(V);
+    }
+    return on_view(c.views, v, f);
+}
+
+template <bool DEFER, int NT>
+__device__ __forceinline__ uint32_t decide(const LevelCtx& c, const CountShared<DEFER, NT>& S, bool valid, uint2 e,
+                                           float4 b, int nchild) {
+    if (!valid) return kDrop;
+    return with_view(c, S, e.y, [&](const ViewDev& V) { return node_decision(V, (int)e.x, b, nchild, c.s_hi); });
+}
+
+// The network's say on the candidates among one entry per thread (every
+// thread of the workgroup takes part).
+template <int NT>
+__device__ __forceinline__ uint32_t settle(const LevelCtx& c, CountShared<true, NT>& S, uint32_t d, uint2 e, float4 b) {
+    const bool cand = (d & kCandidate) != 0;
+    if (!__syncthreads_or(cand)) return d;         // also orders S.x's reuse and publishes S.w
+    const LodMlpDev& m = *(const LodMlpDev*)c.mlp;
+    float f[kMlpIn];
+#pragma unroll
+    for (int k = 0; k < kMlpIn; ++k) f[k] = 0.f;
+    if (cand) {
+        with_view(c, S, e.y, [&](const ViewDev& V) {
+            NodeGeom g;
+            node_geometry(V, b, &g);
+            lod_features(m, V, (int)e.x, b, g, c.level, f);
+        });
+#pragma unroll
+        for (int k = 0; k < kMlpIn; ++k) f[k] = (f[k] - m.mean[k]) * m.inv_std[k];
+    }
+#pragma unroll
+    for (int k = 0; k < kMlpIn; ++k) S.x[threadIdx.x * kMlpXStride + k] = f[k];
+    __syncthreads();
+    const float z = lod_mlp_logit_mfma(S.w, S.x + threadIdx.x / kWave * kWave * kMlpXStride);
+    return (cand && !(1.f / (1.f + __expf(-z)) >= m.p_star)) ? (uint32_t)kEmit : d;
+}
+
+// Decide entries [lo, hi), the staged views and weights in S; returns this
+// thread's share of the counts.
+template <bool DEFER>
+__device__ __forceinline__ uint4 count_chunk(const LevelCtx& c, uint32_t lo, uint32_t hi, CountShared<DEFER, kNT>& S) {
     uint4 acc = make_uint4(0, 0, 0, 0);
-    auto decide = [&](bool valid, uint2 e, float4 b, int2 ch) -> uint32_t {
-        if (!valid) return kDrop;
-        return with_view(e.y, [&](const ViewDev& V) { return node_decision(V, (int)e.x, b, ch.y, c.s_hi); });
-    };
-    // the network's say on the group's candidates (every thread takes part)
-    auto settle = [&](uint32_t d, uint2 e, float4 b) -> uint32_t {
-        const bool cand = (d & kCandidate) != 0;
-        if (!__syncthreads_or(cand)) return d;     // also orders s_x's reuse and publishes s_w
-        const LodMlpDev& m = *(const LodMlpDev*)c.mlp;
-        float f[kMlpIn];
-#pragma unroll
-        for (int k = 0; k < kMlpIn; ++k) f[k] = 0.f;
-        if (cand) {
-            with_view(e.y, [&](const ViewDev& V) {
-                NodeGeom g;
-                node_geometry(V, b, &g);
-                lod_features(m, V, (int)e.x, b, g, c.level, f);
-            });
-#pragma unroll
-            for (int k = 0; k < kMlpIn; ++k) f[k] = (f[k] - m.mean[k]) * m.inv_std[k];
-        }
-#pragma unroll
-        for (int k = 0; k < kMlpIn; ++k) s_x[threadIdx.x * kMlpXStride + k] = f[k];
-        __syncthreads();
-        const float z = lod_mlp_logit_mfma(s_w, s_x + w * kWave * kMlpXStride);
-        return (cand && !(1.f / (1.f + __expf(-z)) >= m.p_star)) ? (uint32_t)kEmit : d;
-    };
     auto count = [&](uint32_t i, bool valid, uint32_t d, int2 ch) {
         if (!valid) return;
         c.dec[i] = (uint8_t)d;
@@ -211,72 +230,82 @@ __global__ __launch_bounds__(kNT) void k_level_count(LevelCtx c, uint32_t in_cap
         const float4 b0 = c.bound[e0.x], b1 = c.bound[e1.x];
         const int2 ch0 = c.leaves ? make_int2(0, 0) : c.child[e0.x];
         const int2 ch1 = c.leaves ? make_int2(0, 0) : c.child[e1.x];
-        uint32_t d0 = decide(v0, e0, b0, ch0);
-        uint32_t d1 = decide(v1, e1, b1, ch1);
-        if (DEFER) {
-            d0 = settle(d0, e0, b0);
-            d1 = settle(d1, e1, b1);
+        uint32_t d0 = decide(c, S, v0, e0, b0, ch0.y);
+        uint32_t d1 = decide(c, S, v1, e1, b1, ch1.y);
+        if constexpr (DEFER) {
+            d0 = settle(c, S, d0, e0, b0);
+            d1 = settle(c, S, d1, e1, b1);
         }
         count(i0, v0, d0, ch0);
         count(i1, v1, d1, ch1);
     }
-    uint4 tot;
-    block_excl_scan4<kNT>(acc, sh, &tot);
-    if (threadIdx.x == 0) c.tmp[blockIdx.x] = tot;
+    return acc;
 }
 
-// Exclusive scan of the G <= 4 * 1024 block counts (four consecutive ones
-// per thread).
-__global__ __launch_bounds__(1024) void k_level_scan(LevelCtx c, int G, uint32_t in_cap) {
-    __shared__ uint4 sh[1024 / kWave + 1];
-    const int t = threadIdx.x;
-    uint4 x[4];
-    uint4 sum = make_uint4(0, 0, 0, 0);
+// Sum of (x, y, z) over a wave, in every lane.
+__device__ __forceinline__ uint4 wave_sum3(uint4 v) {
+    return make_uint4(wave_sum(v.x), wave_sum(v.y), wave_sum(v.z), 0u);
+}
+
+template <bool DEFER>
+__global__ __launch_bounds__(kNT) void k_level_count(LevelCtx c) {
+    __shared__ CountShared<DEFER, kNT> S;
+    __shared__ uint4 s_tot[kNW];
+    const uint32_t n = c.lvl[c.level].x;
+    uint32_t lo, hi;
+    chunk_of(n, gridDim.x, blockIdx.x, &lo, &hi);
+    if (lo >= hi) return;                          // no block at or after this one is read
+    stage_count(c, S);
+    const uint4 acc = wave_sum3(count_chunk<DEFER>(c, lo, hi, S));
+    if (lane_id() == 0) s_tot[threadIdx.x / kWave] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint4 t = make_uint4(0, 0, 0, 0);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int b = 4 * t + j;
-        x[j] = b < G ? c.tmp[b] : make_uint4(0, 0, 0, 0);
-        sum.x += x[j].x;
-        sum.y += x[j].y;
-        sum.z += x[j].z;
-    }
-    uint4 tot;
-    uint4 ex = block_excl_scan4<1024>(sum, sh, &tot);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int b = 4 * t + j;
-        if (b < G) c.tmp[b] = ex;
-        ex.x += x[j].x;
-        ex.y += x[j].y;
-        ex.z += x[j].z;
-    }
-    if (t == 0) {
-        Counters* k = c.ctr;
-        const uint32_t n_in = *c.in_count;
-        k->visited += n_in < in_cap ? n_in : in_cap;
-        const uint32_t base = k->cut;
-        const uint32_t cbase = k->cand;
-        c.tmp[G] = make_uint4(base, 0, cbase, 0);
-        if (c.cand != nullptr) {
-            const uint64_t want = (uint64_t)cbase + tot.z;
-            if (want > c.cand_cap) {
-                k->overflow |= kOvCand;
-                if (want > k->need_cand) k->need_cand = (uint32_t)(want < 0xffffffffull ? want : 0xffffffffull);
-            }
-            k->cand = (uint32_t)(want < c.cand_cap ? want : c.cand_cap);
+        for (int w = 0; w < kNW; ++w) {
+            t.x += s_tot[w].x;
+            t.y += s_tot[w].y;
+            t.z += s_tot[w].z;
         }
-        const uint64_t want_cut = (uint64_t)base + tot.x;
-        if (want_cut > c.cut_cap) {
-            k->overflow |= kOvCut;
-            if (want_cut > k->need_cut) k->need_cut = (uint32_t)(want_cut < 0xffffffffull ? want_cut : 0xffffffffull);
-        }
-        k->cut = (uint32_t)(want_cut < c.cut_cap ? want_cut : c.cut_cap);
-        if (tot.y > c.out_cap) {
-            k->overflow |= kOvFrontier;
-            if (tot.y > k->need_frontier) k->need_frontier = tot.y;
-        }
-        k->frontier[c.out_slot] = tot.y < c.out_cap ? tot.y : c.out_cap;
+        c.fine[blockIdx.x] = t;
+        uint4* bin = c.bins + blockIdx.x / kWave;
+        if (t.x) atomicAdd(&bin->x, t.x);
+        if (t.y) atomicAdd(&bin->y, t.y);
+        if (t.z) atomicAdd(&bin->z, t.z);
     }
+}
+
+// End of a level of n_in entries with totals tot (one thread): capacity
+// checks, the cut size, and the next level's line of the table (returned).
+__device__ __forceinline__ uint4 finish_level(const LevelCtx& c, uint32_t n_in, uint4 at, uint4 tot) {
+    Counters* k = c.ctr;
+    k->visited += n_in;
+    uint4 next;
+    const uint64_t want_cand = (uint64_t)at.z + tot.z;
+    next.z = at.z;
+    if (c.cand != nullptr) {
+        if (want_cand > c.cand_cap) {
+            k->overflow |= kOvCand;
+            if (want_cand > k->need_cand) k->need_cand = (uint32_t)(want_cand < 0xffffffffull ? want_cand : 0xffffffffull);
+        }
+        next.z = (uint32_t)(want_cand < c.cand_cap ? want_cand : c.cand_cap);
+        k->cand = next.z;
+    }
+    const uint64_t want_cut = (uint64_t)at.y + tot.x;
+    if (want_cut > c.cut_cap) {
+        k->overflow |= kOvCut;
+        if (want_cut > k->need_cut) k->need_cut = (uint32_t)(want_cut < 0xffffffffull ? want_cut : 0xffffffffull);
+    }
+    next.y = (uint32_t)(want_cut < c.cut_cap ? want_cut : c.cut_cap);
+    k->cut = next.y;
+    if (tot.y > c.out_cap) {
+        k->overflow |= kOvFrontier;
+        if (tot.y > k->need_frontier) k->need_frontier = tot.y;
+    }
+    next.x = tot.y < c.out_cap ? tot.y : c.out_cap;
+    next.w = 0;
+    c.lvl[c.level + 1] = next;
+    return next;
 }
 
 // Each thread takes kEmitPer consecutive entries of the chunk, so that one
@@ -297,19 +326,36 @@ constexpr uint32_t kEmitStage = 4096;
 // wave (32 measured best on 50-view batches, between 16 and 64).
 constexpr uint32_t kCutViewGroup = 32;
 
-__global__ __launch_bounds__(kNT) void k_level_emit(LevelCtx c, uint32_t in_cap) {
+__global__ __launch_bounds__(kNT) void k_level_emit(LevelCtx c) {
     __shared__ uint4 sh[kNT / kWave + 1];
+    __shared__ uint4 s_off[2];
     __shared__ uint2 s_out[kEmitStage];
     __shared__ uint2 s_last[kNT];                       // (node, view group) of each thread's last entry
     __shared__ uint32_t s_gbase[kEmitPer * kNT + 1];    // children before each group, then the total
-    uint32_t n = *c.in_count;
-    n = n < in_cap ? n : in_cap;
+    const uint32_t blk = blockIdx.x, l = lane_id();
+    // what the blocks before this one emitted: whole bins (first wave), then
+    // the blocks before it in its bin (second wave)
+    static_assert(kCutBins == kWave, "one bin per lane");
+    const uint4 zero = make_uint4(0, 0, 0, 0);
+    uint4 cnt = zero;
+    if (threadIdx.x < kWave) cnt = c.bins[l];
+    else if (threadIdx.x < 2 * kWave) cnt = c.fine[blk - blk % kWave + l];
+    const uint4 at = c.lvl[c.level];
+    const uint32_t n = at.x;
     uint32_t lo, hi;
-    chunk_of(n, gridDim.x, blockIdx.x, &lo, &hi);
+    chunk_of(n, gridDim.x, blk, &lo, &hi);
+    if (threadIdx.x < kWave && blk == 0) {
+        const uint4 tot = wave_sum3(cnt);
+        if (l == 0) finish_level(c, n, at, tot);
+    }
     if (lo >= hi) return;
-    uint4 off = c.tmp[blockIdx.x];
-    const uint32_t base = c.tmp[gridDim.x].x;
-    const uint32_t cbase = c.tmp[gridDim.x].z;
+    if (threadIdx.x < 2 * kWave) {
+        const uint4 before = wave_sum3(l < (threadIdx.x < kWave ? blk / kWave : blk % kWave) ? cnt : zero);
+        if (l == 0) s_off[threadIdx.x / kWave] = before;
+    }
+    __syncthreads();
+    uint4 off = make_uint4(s_off[0].x + s_off[1].x, s_off[0].y + s_off[1].y, s_off[0].z + s_off[1].z, 0u);
+    const uint32_t base = at.y, cbase = at.z;
     for (uint32_t s = lo; s < hi; s += kEmitPer * kNT) {
         // chunks start at multiples of kNT, so i0 is a multiple of kEmitPer
         const uint32_t i0 = s + kEmitPer * threadIdx.x;
@@ -428,24 +474,109 @@ __global__ __launch_bounds__(kNT) void k_level_emit(LevelCtx c, uint32_t in_cap)
     }
 }
 
-// Frontier of every view's roots (nodes [0, n_roots)): grouped, view
-// groups in order and node-major within a group; otherwise view-major.
-__global__ void k_init_roots(uint2* out, uint32_t n_roots, uint32_t n_views, uint32_t cap, Counters* ctr, int slot,
-                             bool grouped) {
-    const uint32_t total = n_roots * n_views;
+// Entry i of the frontier of every view's roots (nodes [0, n_roots)):
+// grouped, view groups in order and node-major within a group; otherwise
+// view-major.
+__device__ __forceinline__ uint2 root_entry(uint32_t i, uint32_t n_roots, uint32_t n_views, bool grouped) {
+    if (!grouped) return make_uint2(i % n_roots, i / n_roots);
     const uint32_t per = n_roots * kCutViewGroup;          // entries of a full group
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < total; i += gridDim.x * blockDim.x) {
-        const uint32_t vb = i / per, loc = i - vb * per;
-        const uint32_t nb = min(kCutViewGroup, n_views - vb * kCutViewGroup);
-        const uint2 e = grouped ? make_uint2(loc / nb, vb * kCutViewGroup + loc % nb) : make_uint2(i % n_roots, i / n_roots);
-        if (i < cap) out[i] = e;
+    const uint32_t vb = i / per, loc = i - vb * per;
+    const uint32_t nb = min(kCutViewGroup, n_views - vb * kCutViewGroup);
+    return make_uint2(loc / nb, vb * kCutViewGroup + loc % nb);
+}
+
+// Counters of a new render, with the roots' frontier size checked.
+__device__ __forceinline__ void start_counters(Counters* ctr, uint64_t roots, uint32_t cap) {
+    Counters z = {};
+    if (roots > cap) {
+        z.overflow = kOvFrontier;
+        z.need_frontier = (uint32_t)(roots < 0xffffffffull ? roots : 0xffffffffull);
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        if (total > cap) {
-            ctr->overflow |= kOvFrontier;
-            if (total > ctr->need_frontier) ctr->need_frontier = total;
+    *ctr = z;
+}
+
+// Start of a cut: counters, the levels' bins, the roots' frontier.
+__global__ __launch_bounds__(kNT) void k_cut_init(LevelCtx c, uint2* out, uint32_t n_roots, uint4* bins, int n_bins) {
+    const uint32_t total = n_roots * (uint32_t)c.n_views;
+    const uint32_t i0 = blockIdx.x * kNT + threadIdx.x, step = gridDim.x * kNT;
+    for (uint32_t i = i0; i < total && i < c.in_cap; i += step) out[i] = root_entry(i, n_roots, c.n_views, c.group);
+    for (uint32_t i = i0; i < (uint32_t)n_bins; i += step) bins[i] = make_uint4(0, 0, 0, 0);
+    if (i0 == 0) {
+        start_counters(c.ctr, total, c.in_cap);
+        c.lvl[0] = make_uint4(total < c.in_cap ? total : c.in_cap, 0, 0, 0);
+    }
+}
+
+// The same start, then the first `levels` levels, by one workgroup with an
+// entry per thread (every one of these levels holds at most kTopEntries
+// entries): an entry is decided, counted, placed and its children written to
+// the next frontier, in LDS, without a trip through memory in between; the
+// children of the last of these levels go to out.  The same cut order as
+// k_level_emit's: children child-major within a node's views.  One view's
+// four leading levels of a 2M-leaf tree: 15.0 us here, 54 as a reset, a
+// roots' launch and three launches a level.
+template <bool DEFER>
+__global__ __launch_bounds__(kTopEntries) void k_cut_top(LevelCtx c, uint2* out, uint32_t n_roots, int levels,
+                                                         int n_levels, uint4* bins, int n_bins) {
+    constexpr int NT = kTopEntries;
+    __shared__ CountShared<DEFER, NT> S;
+    __shared__ uint2 s_f[2][NT];
+    __shared__ uint4 s_scan[NT / kWave + 1];
+    __shared__ uint32_t s_gbase[NT + 1];
+    __shared__ uint4 s_next;
+    const uint32_t t = threadIdx.x;
+    const uint32_t total = n_roots * (uint32_t)c.n_views;
+    uint4 at = make_uint4(total < c.in_cap ? total : c.in_cap, 0, 0, 0);
+    if (t < total) s_f[0][t] = root_entry(t, n_roots, c.n_views, c.group);
+    for (int i = t; i < n_bins; i += NT) bins[i] = make_uint4(0, 0, 0, 0);
+    if (t == 0) start_counters(c.ctr, total, c.in_cap);
+    stage_count(c, S);                             // (also orders the roots' entries)
+    for (int L = 0; L < levels; ++L) {
+        c.level = L;
+        const bool leaves = L == n_levels - 1, last = L == levels - 1;
+        const bool valid = t < at.x;
+        const uint2 e = valid ? s_f[L & 1][t] : make_uint2(0, 0);
+        const uint2 prev = valid && t > 0 ? s_f[L & 1][t - 1] : make_uint2(~0u, ~0u);
+        const float4 b = c.bound[e.x];
+        const int2 ch = leaves ? make_int2(0, 0) : c.child[e.x];
+        uint32_t d = decide(c, S, valid, e, b, ch.y);
+        if constexpr (DEFER) d = settle(c, S, d, e, b);
+        uint4 r = counts_of(c, d, ch.y);
+        // a group starts where the node or the view group changes; ungrouped,
+        // every entry is one
+        r.w = !c.group || e.x != prev.x || e.y / kCutViewGroup != prev.y / kCutViewGroup || t == 0 ? 1u : 0u;
+        uint4 tot;
+        const uint4 ex = block_excl_scan4<NT>(r, s_scan, &tot);
+        const uint32_t grp = ex.w + r.w - 1u;
+        if (r.w) s_gbase[grp] = ex.y;
+        if (t == 0) {
+            s_gbase[tot.w] = tot.y;
+            s_next = finish_level(c, at.x, at, tot);
         }
-        ctr->frontier[slot] = total < cap ? total : cap;
+        __syncthreads();
+        if (r.x) {
+            const uint64_t pos = (uint64_t)at.y + ex.x;
+            if (pos < c.cut_cap) c.cut[pos] = e;
+        }
+        if (r.z) {
+            const uint64_t pos = (uint64_t)at.z + ex.z;
+            if (pos < c.cand_cap) c.cand[pos] = e;
+        }
+        if (r.y) {
+            const uint32_t m = r.y, gb = s_gbase[grp];
+            const uint32_t n_exp = (s_gbase[grp + 1] - gb) / m, rank = (ex.y - gb) / m;
+            for (uint32_t q = 0; q < m; ++q) {
+                const uint32_t pos = gb + q * n_exp + rank;
+                const uint2 child = make_uint2((uint32_t)ch.x + q, e.y);
+                if (last) {
+                    if (pos < c.out_cap) out[pos] = child;
+                } else if (pos < (uint32_t)NT) {
+                    s_f[(L & 1) ^ 1][pos] = child;
+                }
+            }
+        }
+        __syncthreads();
+        at = s_next;
     }
 }
 
@@ -458,11 +589,13 @@ __global__ void k_emit_all(uint2* cut, const int32_t* ids, uint32_t n, uint32_t 
         cut[i] = make_uint2(ids ? (uint32_t)ids[k] : k, (uint32_t)(i / n));
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
+        Counters z = {};
         if (total > cap) {
-            ctr->overflow |= kOvCut;
-            ctr->need_cut = (uint32_t)(total < 0xffffffffull ? total : 0xffffffffull);
+            z.overflow = kOvCut;
+            z.need_cut = (uint32_t)(total < 0xffffffffull ? total : 0xffffffffull);
         }
-        ctr->cut = (uint32_t)(total < cap ? total : cap);
+        z.cut = (uint32_t)(total < cap ? total : cap);
+        *ctr = z;
     }
 }
 
@@ -506,8 +639,6 @@ void launch_lod_features(const uint2* cand, const uint32_t* count, const ViewDev
 }
 
 void launch_cut(const CutArgs& a, hipStream_t s) {
-    const int G = kCutBlocks;
-    static_assert(kCutBlocks <= 4 * 1024, "the level scan takes four counts per thread");
     if (a.flat || a.mode == HGS_LOD_ALL_LEAVES) {
         const uint32_t n = a.flat ? (uint32_t)a.n_nodes : (uint32_t)a.n_leaves;
         const int32_t* ids = a.flat ? nullptr : a.leaf_ids;
@@ -515,49 +646,62 @@ void launch_cut(const CutArgs& a, hipStream_t s) {
         return;
     }
     const uint32_t n_roots = (uint32_t)a.level_offset_host[1];
-    k_init_roots<<<64, 256, 0, s>>>(a.frontier[0], n_roots, (uint32_t)a.n_views, a.frontier_cap, a.ctr, 0,
-                                    a.group_children);
-    int cur = 0;
-    for (int L = 0; L < a.n_levels; ++L) {
-        LevelCtx c;
-        c.bound = a.bound;
-        c.child = a.child;
-        c.views = a.views;
-        c.n_views = a.n_views;
-        c.in = a.frontier[cur];
-        c.in_count = &a.ctr->frontier[cur];
-        c.out = a.frontier[cur ^ 1];
-        c.out_cap = a.frontier_cap;
-        c.cut = a.cut;
-        c.cut_cap = a.cut_cap;
-        c.tmp = a.scan_tmp;
-        c.dec = a.dec;
-        // p* = 0 refines every candidate: nothing for the network to decide
-        c.defer = a.mode == HGS_LOD_LEARNED && a.mlp != nullptr && a.p_star > 0.f;
-        c.w32 = a.mlp_w32;
-        c.ctr = a.ctr;
-        c.mode = a.mode;
-        c.mlp = a.mlp;
-        c.s_hi = a.s_hi;
-        c.cand = a.cand;
-        c.cand_cap = a.cand_cap;
+    // scratch: block counts, the level table, the bins of every level
+    uint4* lvl = a.scan_tmp + kCutBlocks;
+    uint4* bins = lvl + kCutLevels + 1;
+    const int n_bins = a.n_levels * kCutBins;
+    LevelCtx c;
+    c.bound = a.bound;
+    c.child = a.child;
+    c.views = a.views;
+    c.n_views = a.n_views;
+    c.in_cap = c.out_cap = a.frontier_cap;
+    c.cut = a.cut;
+    c.cut_cap = a.cut_cap;
+    c.fine = a.scan_tmp;
+    c.lvl = lvl;
+    c.dec = a.dec;
+    // p* = 0 refines every candidate: nothing for the network to decide
+    c.defer = a.mode == HGS_LOD_LEARNED && a.mlp != nullptr && a.p_star > 0.f;
+    c.w32 = a.mlp_w32;
+    c.ctr = a.ctr;
+    c.mode = a.mode;
+    c.mlp = a.mlp;
+    c.s_hi = a.s_hi;
+    c.cand = a.cand;
+    c.cand_cap = a.cand_cap;
+    c.group = a.group_children;
+    // a level's frontier holds at most (nodes of the level) x views entries
+    auto bound_of = [&](int L) {
+        return (uint64_t)(a.level_offset_host[L + 1] - a.level_offset_host[L]) * (uint64_t)a.n_views;
+    };
+    int top = 0;
+    while (top < a.n_levels && bound_of(top) <= (uint64_t)kTopEntries) ++top;
+    auto set_level = [&](int L) {
+        c.in = a.frontier[L & 1];
+        c.out = a.frontier[(L & 1) ^ 1];
+        c.bins = bins + (size_t)L * kCutBins;
         c.level = L;
         c.leaves = L == a.n_levels - 1;
-        c.group = a.group_children;
-        c.out_slot = cur ^ 1;
-        // the frontier holds at most (nodes of level L) x views entries;
-        // small levels get a grid of that size (the chunking keeps the
-        // entries' order, so the cut does not depend on the grid)
-        const uint64_t bound = (uint64_t)(a.level_offset_host[L + 1] - a.level_offset_host[L]) * (uint64_t)a.n_views;
-        const int GL = (int)std::min<uint64_t>((uint64_t)G, std::max<uint64_t>(1, (bound + kNT - 1) / kNT));
+    };
+    set_level(0);
+    if (top == 0)
+        k_cut_init<<<64, kNT, 0, s>>>(c, a.frontier[0], n_roots, bins, n_bins);
+    else if (c.defer)
+        k_cut_top<true><<<1, kTopEntries, 0, s>>>(c, a.frontier[top & 1], n_roots, top, a.n_levels, bins, n_bins);
+    else
+        k_cut_top<false><<<1, kTopEntries, 0, s>>>(c, a.frontier[top & 1], n_roots, top, a.n_levels, bins, n_bins);
+    for (int L = top; L < a.n_levels; ++L) {
+        set_level(L);
+        // small levels get a grid of their bound's size (the chunking keeps
+        // the entries' order, so the cut does not depend on the grid)
+        const int GL = (int)std::min<uint64_t>((uint64_t)kCutBlocks, std::max<uint64_t>(1, (bound_of(L) + kNT - 1) / kNT));
         // a leaf is never refined, so the last level has no candidates
         if (c.defer && !c.leaves)
-            k_level_count<true><<<GL, kNT, 0, s>>>(c, a.frontier_cap);
+            k_level_count<true><<<GL, kNT, 0, s>>>(c);
         else
-            k_level_count<false><<<GL, kNT, 0, s>>>(c, a.frontier_cap);
-        k_level_scan<<<1, 1024, 0, s>>>(c, GL, a.frontier_cap);
-        k_level_emit<<<GL, kNT, 0, s>>>(c, a.frontier_cap);
-        cur ^= 1;
+            k_level_count<false><<<GL, kNT, 0, s>>>(c);
+        k_level_emit<<<GL, kNT, 0, s>>>(c);
     }
 }
 

@@ -116,7 +116,6 @@ struct alignas(16) BinRec {
 constexpr int kCutLevels = 64;       // hierarchy levels at most (scene validation enforces it)
 
 struct Counters {
-    uint32_t frontier[2];            // frontier sizes (ping, pong)
     uint32_t cut;                    // cut entries written so far
     uint32_t pairs;                  // total (tile, Gaussian) pairs
     uint32_t overflow;               // kOv* bits
@@ -151,9 +150,11 @@ bool tile_shape_ok(int tile_w, int tile_h, int px);
 
 // ---------------------------------------------------------------- launchers
 
-// Scan scratch needs (uint2 / uint32 elements).
-constexpr int kScanBlocks = 1024;
+// Grids and scratch sizes.
 constexpr int kCutBlocks = 4096;     // workgroups of a cut level's count and emit passes
+constexpr int kCutBins = 64;         // sums of 64 blocks' counts each, per level
+// uint4 elements of the cut's scratch: block counts, the level table, bins
+constexpr int kScanTmp = kCutBlocks + (kCutLevels + 1) + kCutLevels * kCutBins;
 constexpr int kSortBlocks = 1024;
 constexpr int kSortBins = 2048;          // widest radix digit: 11 bits
 constexpr int kSortGroup = 8192;         // histogram groups of a large radix sort: multiples of this size,
@@ -162,7 +163,7 @@ constexpr int kSortMaxGroups = 8192;     // at most this many groups per sort (s
 constexpr size_t kSortHistBytes = (size_t)kSortBins * (kSortMaxGroups + 1) * 4;
 
 // Threshold / all-leaves / flat cut for all views.  Writes (node, view)
-// entries to `cut` and the count to ctr->cut.
+// entries to `cut` and the count to ctr->cut; starts the render's counters.
 struct CutArgs {
     const float4* bound;
     const int2* child;               // (first_child, child_count)
@@ -179,7 +180,7 @@ struct CutArgs {
     uint32_t frontier_cap;
     uint2* cut;
     uint32_t cut_cap;
-    uint4* scan_tmp;                 // kScanBlocks + 1 entries
+    uint4* scan_tmp;                 // kScanTmp entries
     uint8_t* dec;                    // frontier_cap bytes: per-entry decisions
     Counters* ctr;
     // learned refinement (nullptr = off); candidate band for it and for
@@ -297,8 +298,6 @@ struct CompositeArgs {
 };
 void launch_ranges(const CompositeArgs& a, hipStream_t s);
 void launch_composite(const CompositeArgs& a, hipStream_t s);
-
-void launch_reset_counters(Counters* c, hipStream_t s);
 
 // GS-slice occupancy (slice.hip): occ[k][j][i] and map[j][i] bytes (either
 // may be null), cell (i, j) = [x0 + i cell, x0 + (i+1) cell] x [y0 + j cell,
