@@ -28,7 +28,7 @@ struct DevMem {
 // alternate between two sets on two streams, so one pass's compositing
 // overlaps the next pass's cut, projection and binning.
 struct Work {
-    DevMem frontier[2], cut, proj, dkey[2], dval[2], ntiles, bins, offsets, dec;
+    DevMem frontier[2], cut, proj, dkey[2], dval[2], ntiles, bins, sums, dec;
     DevMem pkey[2], pval[2], scan_tmp, hist;
 };
 
@@ -76,13 +76,16 @@ struct hgs_ctx {
     // work buffers
     uint32_t frontier_cap = 0, cut_cap = 0, pair_cap = 0;
     Work w[2];                        // per lane
-    DevMem ranges, counters;          // shared: indexed by absolute tile / by pass
+    DevMem ranges, tile_cnt, counters;   // shared: indexed by absolute tile / by pass
     int lanes = 1;                    // HGS_OPT_LANES
     hipStream_t lane_stream = nullptr;
     hipEvent_t fork_ev = nullptr, join_ev = nullptr;
     Counters* ctr_host = nullptr;     // pinned
     bool last_valid = false;
     int64_t regrows = 0;
+    int64_t seen_pairs = -1;          // pairs of the last render whose counters were read (-1: none since the
+                                      // scene, LOD or tile layout changed)
+    bool tile_lists = false;          // passes of the last render (and of the captured graph) used per-tile lists
     uint32_t forced_cap = 0;          // test hook: start from this capacity
     int sort_digit_bits = 8;          // widest radix digit
     double mean_lo[3] = {0, 0, 0}, mean_hi[3] = {0, 0, 0};   // bounding box of every node's mean
@@ -212,7 +215,7 @@ hgs_status alloc_work(hgs_ctx* c) {
         }
         if ((s = ensure(c, w.ntiles, M * 4))) return s;
         if ((s = ensure(c, w.bins, M * sizeof(BinRec)))) return s;
-        if ((s = ensure(c, w.offsets, M * 4))) return s;
+        if ((s = ensure(c, w.sums, tile_sum_words(M) * 4))) return s;
         if ((s = ensure(c, w.scan_tmp, kScanTmp * sizeof(uint4)))) return s;
         if ((s = ensure(c, w.hist, kSortHistBytes))) return s;
     }
@@ -224,7 +227,7 @@ int lane_of(const hgs_ctx* c, int g) { return c->lanes > 1 ? g % c->lanes : 0; }
 
 void release_work(Work& w) {
     DevMem* all[] = {&w.frontier[0], &w.frontier[1], &w.cut, &w.proj, &w.dkey[0], &w.dkey[1], &w.dval[0],
-                     &w.dval[1], &w.ntiles, &w.bins, &w.offsets, &w.dec, &w.pkey[0], &w.pkey[1], &w.pval[0],
+                     &w.dval[1], &w.ntiles, &w.bins, &w.sums, &w.dec, &w.pkey[0], &w.pkey[1], &w.pval[0],
                      &w.pval[1], &w.scan_tmp, &w.hist};
     for (DevMem* m : all) release(*m);
 }
@@ -372,6 +375,64 @@ hgs_status plan_passes(hgs_ctx* c, int want, bool upload_table) {
     return HGS_OK;
 }
 
+// Binning by sorts: the entries by (view, depth), their pairs in that order,
+// the pairs by tile, the tiles' ranges.  Returns the pair buffer that holds
+// the grouped pairs.
+int bin_sorted(hgs_ctx* c, Work& W, const ProjectArgs& pa, EmitArgs ea, CompositeArgs xa, Counters* ctr,
+               const SortArgs& sa, bool view_pass, hipStream_t s) {
+    int dr = launch_sort(sa, s);
+    if (view_pass) {
+        // stable pass on the entries' views: depth order within each view
+        SortArgs sv = sa;
+        sv.keys[0] = sa.keys[dr];
+        sv.keys[1] = sa.keys[dr ^ 1];
+        sv.vals[0] = sa.vals[dr];
+        sv.vals[1] = sa.vals[dr ^ 1];
+        sv.key_bits = bits_for((uint32_t)pa.n_views);
+        launch_view_keys(sa.vals[dr], pa.cut, &ctr->cut, c->cut_cap, sa.keys[dr], sort_bins(sv), s);
+        dr ^= launch_sort(sv, s);
+    }
+    SortArgs pb{};
+    pb.keys[0] = P<uint32_t>(W.pkey[0]);
+    pb.keys[1] = P<uint32_t>(W.pkey[1]);
+    pb.vals[0] = P<uint32_t>(W.pval[0]);
+    pb.vals[1] = P<uint32_t>(W.pval[1]);
+    pb.count = &ctr->pairs;
+    pb.cap = c->pair_cap;
+    pb.key_bits = pa.key_shift;
+    pb.max_digit_bits = c->sort_digit_bits;
+    pb.hist = sa.hist;
+    ea.order = sa.vals[dr];
+    ea.clear = sort_bins(pb);
+    launch_emit(ea, s);
+    const int pr = launch_sort(pb, s);
+    xa.keys = pb.keys[pr];
+    launch_ranges(xa, s);
+    return pr;
+}
+
+// Whether the passes bin through per-tile lists (launch_emit_tiles) or
+// through the depth and pair sorts.  Both give the same lists; the choice
+// follows the pairs the last counted render had (a flat scene's entries when
+// none was counted yet), since the host does not know a render's own.
+// Blocking renders of one view, by the sorts and by the lists: 120,000 pairs
+// in 1,200 tiles 224 and 169 us, 203,000 in 3,600 tiles 255 and 192, 472,000
+// in 1,200 273 and 272, 761,000 in 1,200 337 and 411, 921,000 of large
+// splats in 5,700 453 and 891.  A render that changes its mind needs half or
+// twice the pairs, so that views near the line do not keep re-recording a
+// graph.
+constexpr int64_t kTileListPairs = 1 << 18;
+bool per_tile_lists(const hgs_ctx* c) {
+    uint32_t tiles = 0;
+    for (int g = 0; g + 1 < (int)c->pass_v0.size(); ++g) tiles = std::max(tiles, pass_tile0(c, g + 1) - pass_tile0(c, g));
+    if (tiles == 0 || tiles > kTileListMax) return false;
+    const int64_t slack = c->tile_lists ? 2 : 1;
+    if (c->seen_pairs >= 0)
+        return c->seen_pairs <= slack * kTileListPairs && c->seen_pairs <= slack * 256 * (int64_t)c->total_tiles;
+    const int64_t n = c->n * (int64_t)c->cams.size();
+    return !c->hier && n <= 65536 && n <= 128 * (int64_t)c->total_tiles;
+}
+
 // One pipeline pass over the views of pass g (counters slot g).
 void enqueue_pass(hgs_ctx* c, hipStream_t s, int g) {
     Work& W = c->w[lane_of(c, g)];
@@ -412,6 +473,9 @@ void enqueue_pass(hgs_ctx* c, hipStream_t s, int g) {
     // gathers each tile's entry records: 8.74 ms with the plain order,
     // 8.99 ms node-grouped)
     ca.group_children = !c->ropts.lod_blend && !c->ropts.keep_state;
+    const bool lists = c->tile_lists;
+    ca.zero = P<uint32_t>(c->tile_cnt) + t0;
+    ca.n_zero = lists ? t1 - t0 : 0u;
     launch_cut(ca, s);
     mark(c, 1, s);
 
@@ -482,10 +546,10 @@ void enqueue_pass(hgs_ctx* c, hipStream_t s, int g) {
     const int view_bits = ca.n_views > 1 ? bits_for((uint32_t)ca.n_views) : 0;
     const bool view_in_key = ca.n_views > 1 && depth_bits + view_bits <= 32;
     pa.view_shift = view_in_key ? depth_bits : 0;
-    launch_project(pa, s);
-    mark(c, 2, s);
-
-    SortArgs sa{};
+    pa.tile_count = lists ? ca.zero : nullptr;
+    pa.total_tiles = t1 - t0;
+    pa.scan_tmp = ca.scan_tmp;
+    SortArgs sa{};                    // the depth sort
     sa.keys[0] = P<uint32_t>(W.dkey[0]);
     sa.keys[1] = P<uint32_t>(W.dkey[1]);
     sa.vals[0] = P<uint32_t>(W.dval[0]);
@@ -495,26 +559,16 @@ void enqueue_pass(hgs_ctx* c, hipStream_t s, int g) {
     sa.key_bits = view_in_key ? depth_bits + view_bits : depth_bits;
     sa.max_digit_bits = c->sort_digit_bits;
     sa.hist = P<uint32_t>(W.hist);
-    int dr = launch_sort(sa, s);
-    if (ca.n_views > 1 && !view_in_key) {
-        // stable pass on the entries' views: depth order within each view
-        launch_view_keys(sa.vals[dr], ca.cut, &ctr->cut, c->cut_cap, sa.keys[dr], s);
-        SortArgs sv = sa;
-        sv.keys[0] = sa.keys[dr];
-        sv.keys[1] = sa.keys[dr ^ 1];
-        sv.vals[0] = sa.vals[dr];
-        sv.vals[1] = sa.vals[dr ^ 1];
-        sv.key_bits = bits_for((uint32_t)ca.n_views);
-        dr ^= launch_sort(sv, s);
-    }
+    if (!lists) pa.clear = sort_bins(sa);
+    launch_project(pa, s);
+    mark(c, 2, s);
 
     EmitArgs ea{};
-    ea.order = sa.vals[dr];
     ea.ntiles = pa.ntiles;
     ea.bins = pa.bins;
     ea.proj = pa.proj;
     ea.cut_cap = c->cut_cap;
-    ea.offsets = P<uint32_t>(W.offsets);
+    ea.sums = P<uint32_t>(W.sums);
     ea.keys = P<uint32_t>(W.pkey[0]);
     ea.vals = P<uint32_t>(W.pval[0]);
     ea.pair_cap = c->pair_cap;
@@ -523,28 +577,8 @@ void enqueue_pass(hgs_ctx* c, hipStream_t s, int g) {
     ea.ctr = ctr;
     ea.tile_w = c->ropts.tile_w;
     ea.tile_h = c->ropts.tile_h;
-    launch_emit(ea, s);
-
-    SortArgs pb{};
-    pb.keys[0] = P<uint32_t>(W.pkey[0]);
-    pb.keys[1] = P<uint32_t>(W.pkey[1]);
-    pb.vals[0] = P<uint32_t>(W.pval[0]);
-    pb.vals[1] = P<uint32_t>(W.pval[1]);
-    pb.count = &ctr->pairs;
-    pb.cap = c->pair_cap;
-    pb.key_bits = key_shift;
-    pb.max_digit_bits = c->sort_digit_bits;
-    pb.hist = sa.hist;
-    const int pr = launch_sort(pb, s);
-    c->last_pair_buf = pr;
-    c->last_lane = lane_of(c, g);
-    c->last_blend = pa.blend;
-    c->last_keep = c->ropts.keep_state;
-    c->last_default_tiles = c->ropts.tile_w == kTile && c->ropts.tile_h == kTile;
 
     CompositeArgs xa{};
-    xa.keys = pb.keys[pr];
-    xa.vals = pb.vals[pr];
     xa.pair_cap = c->pair_cap;
     xa.cut_cap = c->cut_cap;
     xa.ranges = P<uint2>(c->ranges) + t0;
@@ -557,7 +591,30 @@ void enqueue_pass(hgs_ctx* c, hipStream_t s, int g) {
     xa.opts = c->ropts;
     xa.ctr = ctr;
     xa.state = c->ropts.keep_state ? P<uint2>(c->px_state) + (size_t)t0 * kTilePx : nullptr;
-    launch_ranges(xa, s);
+
+    int pr = 1;
+    if (lists) {
+        TileListArgs ta{};
+        ta.tile_count = pa.tile_count;
+        ta.total_tiles = t1 - t0;
+        ta.depth = pa.depth_key;
+        for (int i = 0; i < 2; ++i) {
+            ta.keys[i] = P<uint32_t>(W.pkey[i]);
+            ta.vals[i] = P<uint32_t>(W.pval[i]);
+        }
+        ta.pair_cap = c->pair_cap;
+        ta.ranges = xa.ranges;
+        ta.ctr = ctr;
+        launch_emit_tiles(ea, ta, s);
+    } else {
+        pr = bin_sorted(c, W, pa, ea, xa, ctr, sa, ca.n_views > 1 && !view_in_key, s);
+    }
+    xa.vals = P<uint32_t>(W.pval[pr]);
+    c->last_pair_buf = pr;
+    c->last_lane = lane_of(c, g);
+    c->last_blend = pa.blend;
+    c->last_keep = c->ropts.keep_state;
+    c->last_default_tiles = c->ropts.tile_w == kTile && c->ropts.tile_h == kTile;
     mark(c, 4, s);
     launch_composite(xa, s);
     mark(c, 5, s);
@@ -599,9 +656,17 @@ Counters merge_passes(const hgs_ctx* c, uint64_t* need_cut_sum) {
     return m;
 }
 
+// The counters of a render have arrived: remember its pairs (per_tile_lists).
+void note_pairs(hgs_ctx* c) {
+    int64_t pairs = 0;
+    for (int g = 0; g < n_passes(c); ++g) pairs += std::max(c->ctr_host[g].pairs, c->ctr_host[g].need_pairs);
+    c->seen_pairs = pairs;
+}
+
 hgs_status read_counters(hgs_ctx* c, hipStream_t s) {
     HIP_TRY(c, hipMemcpyAsync(c->ctr_host, c->counters.p, sizeof(Counters) * n_passes(c), hipMemcpyDeviceToHost, s));
     HIP_TRY(c, hipStreamSynchronize(s));
+    note_pairs(c);
     return HGS_OK;
 }
 
@@ -713,7 +778,7 @@ constexpr uint32_t kStaticSortGroups = kStaticSortMax / kSortGroup;
 static_assert(kStaticSortMax % kSortGroup == 0, "whole histogram groups");
 constexpr size_t kScratchPing = (size_t)kStaticSortMax * 4;
 constexpr size_t kScratchHistOff = 2 * kScratchPing + 256;
-constexpr size_t kScratchBytes = kScratchHistOff + (size_t)kSortBins * (kStaticSortGroups + 1) * 4;
+constexpr size_t kScratchBytes = kScratchHistOff + sort_hist_bytes(kStaticSortGroups);
 constexpr int kMaxDevices = 64;
 
 }  // namespace
@@ -741,8 +806,11 @@ hipError_t scratch_address(int device, void** out) {
     return hipSuccess;
 }
 
-__global__ void k_set_count(uint32_t* count, uint32_t n) {
-    if (threadIdx.x == 0) *count = n;
+// Start of a sort of n pairs: the element count and the first pass's bins.
+__global__ void k_start_sort(uint32_t* count, uint32_t n, SortBins clear) {
+    const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t == 0) *count = n;
+    for (uint32_t i = t; i < clear.n; i += gridDim.x * blockDim.x) clear.words[i] = 0;
 }
 
 __global__ void k_copy_pairs(const uint32_t* __restrict__ ks, const uint32_t* __restrict__ vs, uint32_t* kd,
@@ -793,7 +861,7 @@ void hgs_destroy(hgs_ctx* c) {
     (void)hipDeviceSynchronize();
     DevMem* all[] = {&c->geo, &c->sh, &c->bound, &c->child, &c->leaf_ids, &c->parent, &c->nodefeat, &c->lvl,
                      &c->train_scratch, &c->region_dev, &c->region_part, &c->surf, &c->views,
-                     &c->tile_view, &c->mlp_w, &c->mlp_w32, &c->mlp_dev, &c->ranges,
+                     &c->tile_view, &c->mlp_w, &c->mlp_w32, &c->mlp_dev, &c->ranges, &c->tile_cnt,
                      &c->counters, &c->sort_k, &c->sort_v, &c->sort_n, &c->sort_hist, &c->px_state, &c->nav_goals, &c->nav_flags,
                      &c->nav_active, &c->nav_steps, &c->egrad, &c->dimg, &c->brec};
     for (DevMem* m : all) release(*m);
@@ -935,6 +1003,7 @@ hgs_status hgs_load_scene(hgs_ctx* c, const hgs_gaussians* g, const hgs_hierarch
         c->mean_hi[k] = mhi[k];
     }
     c->depth_full = false;
+    c->seen_pairs = -1;
     c->loaded = true;
     c->mlp_loaded = false;
     c->last_valid = false;
@@ -979,7 +1048,7 @@ hgs_status hgs_set_cameras(hgs_ctx* c, int32_t n, const hgs_camera* cams) {
         same_layout = c->cams[v].width == cams[v].width && c->cams[v].height == cams[v].height;
     hgs_status s;
     if ((s = ensure(c, c->views, sizeof(ViewDev) * n)) || (s = ensure(c, c->tile_view, tiles * 4)) ||
-        (s = ensure(c, c->ranges, tiles * sizeof(uint2))))
+        (s = ensure(c, c->ranges, tiles * sizeof(uint2))) || (s = ensure(c, c->tile_cnt, tiles * 4)))
         return s;
     if ((int)c->cams.size() < n || !c->views_host) {
         if (c->views_host) {
@@ -1031,6 +1100,7 @@ hgs_status hgs_set_cameras(hgs_ctx* c, int32_t n, const hgs_camera* cams) {
     c->cams.assign(cams, cams + n);
     c->total_tiles = (uint32_t)tiles;
     c->tile_abs = tile_base;
+    if (!same_layout) c->seen_pairs = -1;
     if ((s = plan_passes(c, same_layout ? c->want_passes : 1, !same_layout))) return s;
     c->views_dirty = true;
     c->last_valid = false;
@@ -1047,6 +1117,7 @@ hgs_status hgs_set_lod(hgs_ctx* c, int32_t mode, float tau) {
     if (!(tau > 0.f) || !finite(tau)) return fail(c, HGS_E_INVALID, "tau must be a positive number");
     if (mode == HGS_LOD_LEARNED && !c->mlp_loaded) return fail(c, HGS_E_STATE, "learned LOD needs hgs_load_lod_mlp first");
     invalidate_graph(c);
+    if (mode != c->lod_mode || tau != c->tau) c->seen_pairs = -1;
     c->lod_mode = mode;
     c->tau = tau;
     if (c->views_host) HIP_TRY(c, hipEventSynchronize(c->views_copied));
@@ -1077,7 +1148,9 @@ hgs_status relayout_tiles(hgs_ctx* c) {
     }
     if (tiles >= (1ull << 31) || !pair_keys_fit(V, max_tiles)) return fail(c, HGS_E_UNSUPPORTED, "too many tiles");
     hgs_status s;
-    if ((s = ensure(c, c->tile_view, tiles * 4)) || (s = ensure(c, c->ranges, tiles * sizeof(uint2)))) return s;
+    if ((s = ensure(c, c->tile_view, tiles * 4)) || (s = ensure(c, c->ranges, tiles * sizeof(uint2))) ||
+        (s = ensure(c, c->tile_cnt, tiles * 4)))
+        return s;
     HIP_TRY(c, hipEventSynchronize(c->views_copied));
     for (int v = 0; v < V; ++v) {
         c->views_host[v].tiles_x = (c->cams[v].width + tw - 1) / tw;
@@ -1085,6 +1158,7 @@ hgs_status relayout_tiles(hgs_ctx* c) {
     }
     c->total_tiles = (uint32_t)tiles;
     c->tile_abs = base;
+    c->seen_pairs = -1;
     c->last_valid = false;
     return plan_passes(c, c->want_passes, true);
 }
@@ -1208,6 +1282,10 @@ hgs_status hgs_render(hgs_ctx* c, void* stream, const hgs_output* outs) {
     }
     c->regrows = 0;
     for (int attempt = 0; attempt < 16; ++attempt) {
+        if (const bool lists = per_tile_lists(c); lists != c->tile_lists) {
+            invalidate_graph(c);
+            c->tile_lists = lists;
+        }
         if (c->use_graph && !c->stage_timing) {
             if (!c->graph_valid) {
                 invalidate_graph(c);
@@ -1261,6 +1339,7 @@ hgs_status hgs_check(hgs_ctx* c) {
     if (!c) return HGS_E_INVALID;
     HIP_TRY(c, hipSetDevice(c->device));
     HIP_TRY(c, hipMemcpy(c->ctr_host, c->counters.p, sizeof(Counters) * n_passes(c), hipMemcpyDeviceToHost));
+    note_pairs(c);
     const Counters k = merge_passes(c, nullptr);
     if (k.overflow) {
         c->last_valid = false;
@@ -1529,7 +1608,6 @@ hgs_status hgs_sort_pairs(hgs_ctx* c, void* stream, uint32_t* keys, uint32_t* va
         (st = ensure(c, c->sort_n, 4)) || (st = ensure(c, c->sort_hist, kSortHistBytes)))
         return st;
     const uint32_t nn = (uint32_t)n;
-    HIP_TRY(c, hipMemcpyAsync(c->sort_n.p, &nn, 4, hipMemcpyHostToDevice, s));
     SortArgs a{};
     a.keys[0] = keys;
     a.keys[1] = P<uint32_t>(c->sort_k);
@@ -1540,6 +1618,7 @@ hgs_status hgs_sort_pairs(hgs_ctx* c, void* stream, uint32_t* keys, uint32_t* va
     a.key_bits = key_bits;
     a.max_digit_bits = c->sort_digit_bits;
     a.hist = P<uint32_t>(c->sort_hist);
+    k_start_sort<<<64, 256, 0, s>>>(P<uint32_t>(c->sort_n), nn, sort_bins(a));
     const int r = launch_sort(a, s);
     if (r == 1) {
         HIP_TRY(c, hipMemcpyAsync(keys, a.keys[1], (size_t)n * 4, hipMemcpyDeviceToDevice, s));
@@ -1575,7 +1654,7 @@ hgs_status hgs_sort_pairs_noalloc(hgs_ctx* c, void* stream, uint32_t* keys, uint
     a.hist = reinterpret_cast<uint32_t*>(base + kScratchHistOff);
     a.hist_stride = kStaticSortGroups;
     // the count of the previous call is still there: every call writes its own
-    k_set_count<<<1, 64, 0, s>>>(count, (uint32_t)n);
+    k_start_sort<<<64, 256, 0, s>>>(count, (uint32_t)n, sort_bins(a));
     if (launch_sort(a, s) == 1) {
         const uint32_t grid = std::min<uint32_t>((uint32_t)((n + 255) / 256), 2048u);
         k_copy_pairs<<<grid, 256, 0, s>>>(a.keys[1], a.vals[1], keys, vals, (uint32_t)n);

@@ -551,8 +551,10 @@ __global__ __launch_bounds__(256) void k_gather_bwd(GatherArgs a) {
     }
 }
 
-__global__ void k_entry_keys(const uint2* cut, const Counters* ctr, uint32_t cap, uint32_t* keys, uint32_t* vals) {
+__global__ void k_entry_keys(const uint2* cut, const Counters* ctr, uint32_t cap, uint32_t* keys, uint32_t* vals,
+                             SortBins clear) {
     const uint32_t m = min(ctr->cut, cap);
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < clear.n; i += gridDim.x * blockDim.x) clear.words[i] = 0;
     for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < m; i += gridDim.x * blockDim.x) {
         keys[i] = cut[i].x;
         vals[i] = i;
@@ -570,7 +572,7 @@ void launch_backward_params(ProjBwdArgs p, SortArgs sa, GatherArgs ga, hipStream
     // the entries in Gaussian order: the chain rule reads each Gaussian's
     // parameters for its views in a row and writes the records in that
     // order, which the sum then reads sequentially
-    k_entry_keys<<<2048, 256, 0, s>>>(p.cut, p.ctr, p.cut_cap, sa.keys[0], sa.vals[0]);
+    k_entry_keys<<<2048, 256, 0, s>>>(p.cut, p.ctr, p.cut_cap, sa.keys[0], sa.vals[0], sort_bins(sa));
     const int r = launch_sort(sa, s);
     p.order = sa.vals[r];
     ga.keys = sa.keys[r];

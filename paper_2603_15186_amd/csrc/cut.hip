@@ -97,6 +97,8 @@ struct LevelCtx {
     int level;
     bool leaves;              // the last level: every node is a leaf (no child ranges to read)
     bool group;               // children laid out child-major per group of a node's views
+    uint32_t* zero;           // words to clear at the start
+    uint32_t n_zero;
 };
 
 __device__ __forceinline__ void chunk_of(uint32_t n, int G, int b, uint32_t* lo, uint32_t* hi) {
@@ -495,12 +497,14 @@ __device__ __forceinline__ void start_counters(Counters* ctr, uint64_t roots, ui
     *ctr = z;
 }
 
-// Start of a cut: counters, the levels' bins, the roots' frontier.
-__global__ __launch_bounds__(kNT) void k_cut_init(LevelCtx c, uint2* out, uint32_t n_roots, uint4* bins, int n_bins) {
+// Start of a cut: counters, the counts of binned entries and the levels' bins,
+// the roots' frontier.
+__global__ __launch_bounds__(kNT) void k_cut_init(LevelCtx c, uint2* out, uint32_t n_roots, uint4* clear, int n_clear) {
     const uint32_t total = n_roots * (uint32_t)c.n_views;
     const uint32_t i0 = blockIdx.x * kNT + threadIdx.x, step = gridDim.x * kNT;
     for (uint32_t i = i0; i < total && i < c.in_cap; i += step) out[i] = root_entry(i, n_roots, c.n_views, c.group);
-    for (uint32_t i = i0; i < (uint32_t)n_bins; i += step) bins[i] = make_uint4(0, 0, 0, 0);
+    for (uint32_t i = i0; i < (uint32_t)n_clear; i += step) clear[i] = make_uint4(0, 0, 0, 0);
+    for (uint32_t i = i0; i < c.n_zero; i += step) c.zero[i] = 0;
     if (i0 == 0) {
         start_counters(c.ctr, total, c.in_cap);
         c.lvl[0] = make_uint4(total < c.in_cap ? total : c.in_cap, 0, 0, 0);
@@ -517,7 +521,7 @@ __global__ __launch_bounds__(kNT) void k_cut_init(LevelCtx c, uint2* out, uint32
 // roots' launch and three launches a level.
 template <bool DEFER>
 __global__ __launch_bounds__(kTopEntries) void k_cut_top(LevelCtx c, uint2* out, uint32_t n_roots, int levels,
-                                                         int n_levels, uint4* bins, int n_bins) {
+                                                         int n_levels, uint4* clear, int n_clear) {
     constexpr int NT = kTopEntries;
     __shared__ CountShared<DEFER, NT> S;
     __shared__ uint2 s_f[2][NT];
@@ -528,7 +532,8 @@ __global__ __launch_bounds__(kTopEntries) void k_cut_top(LevelCtx c, uint2* out,
     const uint32_t total = n_roots * (uint32_t)c.n_views;
     uint4 at = make_uint4(total < c.in_cap ? total : c.in_cap, 0, 0, 0);
     if (t < total) s_f[0][t] = root_entry(t, n_roots, c.n_views, c.group);
-    for (int i = t; i < n_bins; i += NT) bins[i] = make_uint4(0, 0, 0, 0);
+    for (int i = t; i < n_clear; i += NT) clear[i] = make_uint4(0, 0, 0, 0);
+    for (uint32_t i = t; i < c.n_zero; i += NT) c.zero[i] = 0;
     if (t == 0) start_counters(c.ctr, total, c.in_cap);
     stage_count(c, S);                             // (also orders the roots' entries)
     for (int L = 0; L < levels; ++L) {
@@ -581,13 +586,15 @@ __global__ __launch_bounds__(kTopEntries) void k_cut_top(LevelCtx c, uint2* out,
 }
 
 // Every listed id (or 0..n-1 when ids is null) for every view, view-major.
-__global__ void k_emit_all(uint2* cut, const int32_t* ids, uint32_t n, uint32_t n_views, uint32_t cap, Counters* ctr) {
+__global__ void k_emit_all(uint2* cut, const int32_t* ids, uint32_t n, uint32_t n_views, uint32_t cap, Counters* ctr,
+                           uint32_t* zero, uint32_t n_zero, uint4* seen) {
     const uint64_t total = (uint64_t)n * n_views;
     for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < total && i < cap;
          i += (uint64_t)gridDim.x * blockDim.x) {
         const uint32_t k = (uint32_t)(i % n);
         cut[i] = make_uint2(ids ? (uint32_t)ids[k] : k, (uint32_t)(i / n));
     }
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n_zero; i += gridDim.x * blockDim.x) zero[i] = 0;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         Counters z = {};
         if (total > cap) {
@@ -597,6 +604,7 @@ __global__ void k_emit_all(uint2* cut, const int32_t* ids, uint32_t n, uint32_t 
         z.cut = (uint32_t)(total < cap ? total : cap);
         *ctr = z;
     }
+    if (blockIdx.x == 0 && threadIdx.x < kSeenSlots / 4) seen[threadIdx.x] = make_uint4(0, 0, 0, 0);
 }
 
 // Features and screen footprint of each collected candidate.  The level of
@@ -642,14 +650,16 @@ void launch_cut(const CutArgs& a, hipStream_t s) {
     if (a.flat || a.mode == HGS_LOD_ALL_LEAVES) {
         const uint32_t n = a.flat ? (uint32_t)a.n_nodes : (uint32_t)a.n_leaves;
         const int32_t* ids = a.flat ? nullptr : a.leaf_ids;
-        k_emit_all<<<2048, 256, 0, s>>>(a.cut, ids, n, (uint32_t)a.n_views, a.cut_cap, a.ctr);
+        k_emit_all<<<2048, 256, 0, s>>>(a.cut, ids, n, (uint32_t)a.n_views, a.cut_cap, a.ctr, a.zero, a.n_zero,
+                                      a.scan_tmp + kSeenAt);
         return;
     }
     const uint32_t n_roots = (uint32_t)a.level_offset_host[1];
     // scratch: block counts, the level table, the bins of every level
     uint4* lvl = a.scan_tmp + kCutBlocks;
-    uint4* bins = lvl + kCutLevels + 1;
-    const int n_bins = a.n_levels * kCutBins;
+    uint4* seen = a.scan_tmp + kSeenAt;             // (cleared with the bins behind them)
+    uint4* bins = seen + kSeenSlots / 4;
+    const int n_clear = kSeenSlots / 4 + a.n_levels * kCutBins;
     LevelCtx c;
     c.bound = a.bound;
     c.child = a.child;
@@ -671,6 +681,8 @@ void launch_cut(const CutArgs& a, hipStream_t s) {
     c.cand = a.cand;
     c.cand_cap = a.cand_cap;
     c.group = a.group_children;
+    c.zero = a.zero;
+    c.n_zero = a.n_zero;
     // a level's frontier holds at most (nodes of the level) x views entries
     auto bound_of = [&](int L) {
         return (uint64_t)(a.level_offset_host[L + 1] - a.level_offset_host[L]) * (uint64_t)a.n_views;
@@ -686,11 +698,11 @@ void launch_cut(const CutArgs& a, hipStream_t s) {
     };
     set_level(0);
     if (top == 0)
-        k_cut_init<<<64, kNT, 0, s>>>(c, a.frontier[0], n_roots, bins, n_bins);
+        k_cut_init<<<64, kNT, 0, s>>>(c, a.frontier[0], n_roots, seen, n_clear);
     else if (c.defer)
-        k_cut_top<true><<<1, kTopEntries, 0, s>>>(c, a.frontier[top & 1], n_roots, top, a.n_levels, bins, n_bins);
+        k_cut_top<true><<<1, kTopEntries, 0, s>>>(c, a.frontier[top & 1], n_roots, top, a.n_levels, seen, n_clear);
     else
-        k_cut_top<false><<<1, kTopEntries, 0, s>>>(c, a.frontier[top & 1], n_roots, top, a.n_levels, bins, n_bins);
+        k_cut_top<false><<<1, kTopEntries, 0, s>>>(c, a.frontier[top & 1], n_roots, top, a.n_levels, seen, n_clear);
     for (int L = top; L < a.n_levels; ++L) {
         set_level(L);
         // small levels get a grid of their bound's size (the chunking keeps

@@ -1,5 +1,5 @@
 // Wave64 and workgroup primitives for gfx950: prefix sums over wavefronts
-// and blocks, digit matching by ballots.
+// and blocks.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -17,31 +17,29 @@ __device__ __forceinline__ uint64_t lanemask_lt() {
     return l == 0 ? 0ull : (~0ull >> (64 - l));
 }
 
+// x of the lane CTRL names, 0 where it names none or the row is masked out.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_or_zero(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xf, false);
+}
+
+// Prefix sums in the vector pipeline: shifts by 1, 2, 4 and 8 within the rows
+// of 16 lanes, then lane 15 of a row onto the next row (rows 1 and 3) and
+// lane 31 onto rows 2 and 3.  (Lane shifts through LDS cost some 60 cycles
+// each of the six steps.)  Every lane of the wave takes part.
 __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x) {
-    const int l = lane_id();
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        uint32_t y = __shfl_up(x, d, kWave);
-        if (l >= d) x += y;
-    }
+    x += dpp_or_zero<0x111, 0xf>(x);       // row_shr:1
+    x += dpp_or_zero<0x112, 0xf>(x);       // row_shr:2
+    x += dpp_or_zero<0x114, 0xf>(x);       // row_shr:4
+    x += dpp_or_zero<0x118, 0xf>(x);       // row_shr:8
+    x += dpp_or_zero<0x142, 0xa>(x);       // row_bcast:15
+    x += dpp_or_zero<0x143, 0xc>(x);       // row_bcast:31
     return x;
 }
 
-__device__ __forceinline__ uint2 wave_incl_scan2(uint2 x) {
-    const int l = lane_id();
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        uint32_t a = __shfl_up(x.x, d, kWave);
-        uint32_t b = __shfl_up(x.y, d, kWave);
-        if (l >= d) { x.x += a; x.y += b; }
-    }
-    return x;
-}
-
+// Sum over the wave, in every lane.
 __device__ __forceinline__ uint32_t wave_sum(uint32_t x) {
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) x += __shfl_xor(x, d, kWave);
-    return x;
+    return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(x), kWave - 1);
 }
 
 // Exclusive scan over a block of NT threads; returns the thread's exclusive
@@ -66,39 +64,10 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t x, uint32_t* sh, ui
 }
 
 template <int NT>
-__device__ __forceinline__ uint2 block_excl_scan2(uint2 x, uint2* sh, uint2* total) {
-    constexpr int NW = NT / kWave;
-    const int w = threadIdx.x / kWave, l = lane_id();
-    uint2 inc = wave_incl_scan2(x);
-    if (l == kWave - 1) sh[w] = inc;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint2 run = make_uint2(0, 0);
-        for (int i = 0; i < NW; ++i) {
-            uint2 t = sh[i];
-            sh[i] = run;
-            run.x += t.x; run.y += t.y;
-        }
-        sh[NW] = run;
-    }
-    __syncthreads();
-    uint2 r = make_uint2(sh[w].x + inc.x - x.x, sh[w].y + inc.y - x.y);
-    *total = sh[NW];
-    __syncthreads();
-    return r;
-}
-
-template <int NT>
 __device__ __forceinline__ uint4 block_excl_scan4(uint4 x, uint4* sh, uint4* total) {
     constexpr int NW = NT / kWave;
     const int w = threadIdx.x / kWave, l = lane_id();
-    uint4 inc = x;
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        const uint32_t a = __shfl_up(inc.x, d, kWave), b = __shfl_up(inc.y, d, kWave);
-        const uint32_t c = __shfl_up(inc.z, d, kWave), e = __shfl_up(inc.w, d, kWave);
-        if (l >= d) { inc.x += a; inc.y += b; inc.z += c; inc.w += e; }
-    }
+    const uint4 inc = make_uint4(wave_incl_scan(x.x), wave_incl_scan(x.y), wave_incl_scan(x.z), wave_incl_scan(x.w));
     if (l == kWave - 1) sh[w] = inc;
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -116,18 +85,6 @@ __device__ __forceinline__ uint4 block_excl_scan4(uint4 x, uint4* sh, uint4* tot
     *total = sh[NW];
     __syncthreads();
     return r;
-}
-
-// Lanes of the wave (among `active`) whose 8-bit digit equals this lane's.
-__device__ __forceinline__ uint64_t match_digit8(uint32_t d, uint64_t active) {
-    uint64_t m = active;
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-        const bool bit = (d >> b) & 1u;
-        const uint64_t bal = __ballot(bit);
-        m &= bit ? bal : ~bal;
-    }
-    return m;
 }
 
 __host__ __device__ __forceinline__ uint32_t ceil_div(uint32_t a, uint32_t b) { return (a + b - 1) / b; }

@@ -153,14 +153,22 @@ bool tile_shape_ok(int tile_w, int tile_h, int px);
 // Grids and scratch sizes.
 constexpr int kCutBlocks = 4096;     // workgroups of a cut level's count and emit passes
 constexpr int kCutBins = 64;         // sums of 64 blocks' counts each, per level
-// uint4 elements of the cut's scratch: block counts, the level table, bins
-constexpr int kScanTmp = kCutBlocks + (kCutLevels + 1) + kCutLevels * kCutBins;
+// uint4 elements of the cut's scratch: block counts (then, once the cut is
+// done, the emission's sums of 2^20 entries), the level table, 64 counts of
+// binned entries, bins
+constexpr int kSeenAt = kCutBlocks + kCutLevels + 1, kSeenSlots = 64;
+constexpr int kScanTmp = kSeenAt + kSeenSlots / 4 + kCutLevels * kCutBins;
 constexpr int kSortBlocks = 1024;
 constexpr int kSortBins = 2048;          // widest radix digit: 11 bits
 constexpr int kSortGroup = 8192;         // histogram groups of a large radix sort: multiples of this size,
 constexpr int kSortMaxGroups = 8192;     // at most this many groups per sort (small sorts: smaller groups, at most 512)
-// histogram buffer: per-group counts of every digit, then the digit totals
-constexpr size_t kSortHistBytes = (size_t)kSortBins * (kSortMaxGroups + 1) * 4;
+// histogram buffer of up to `groups` groups: per-group counts of every
+// digit, then two sets of bins (rows of 16 and of 256 groups)
+constexpr size_t sort_bin_words(uint32_t groups) {
+    return 2 * (size_t)kSortBins * ((groups + 15) / 16 + (groups + 255) / 256);
+}
+constexpr size_t sort_hist_bytes(uint32_t groups) { return 4 * ((size_t)kSortBins * groups + sort_bin_words(groups)); }
+constexpr size_t kSortHistBytes = sort_hist_bytes(kSortMaxGroups);
 
 // Threshold / all-leaves / flat cut for all views.  Writes (node, view)
 // entries to `cut` and the count to ctr->cut; starts the render's counters.
@@ -194,6 +202,8 @@ struct CutArgs {
     // children of a node's views laid out child-major in the frontier
     // (node-grouped), else in plain parent order with view-major roots
     bool group_children;
+    uint32_t* zero;                  // words cleared at the start (n_zero may be 0)
+    uint32_t n_zero;
 };
 void launch_cut(const CutArgs& a, hipStream_t s);
 
@@ -202,6 +212,28 @@ void launch_cut(const CutArgs& a, hipStream_t s);
 // candidate (node, view) entries.
 void launch_lod_features(const uint2* cand, const uint32_t* count, const ViewDev* views, const void* mlp_geom,
                          float* feats, int4* rects, hipStream_t s);
+
+// Stable LSD radix sort of (key, value) pairs by the low key_bits bits.
+// count: device pointer to n (clamped to cap).  Ping-pong buffers; returns
+// the index (0 or 1) of the buffer pair that holds the result.
+struct SortArgs {
+    uint32_t* keys[2];
+    uint32_t* vals[2];
+    const uint32_t* count;
+    uint32_t cap;
+    int key_bits;
+    int max_digit_bits = 11;         // 6..11
+    uint32_t* hist;                  // sort_hist_bytes(hist_stride) bytes
+    uint32_t hist_stride = kSortMaxGroups;   // at least the sort's group count
+};
+// The bins of a sort's first pass: words that a kernel before launch_sort
+// (the one that writes the keys, say) has to clear.
+struct SortBins {
+    uint32_t* words;
+    uint32_t n;
+};
+SortBins sort_bins(const SortArgs& a);
+int launch_sort(const SortArgs& a, hipStream_t s);
 
 struct ProjectArgs {
     const uint2* cut;
@@ -234,25 +266,30 @@ struct ProjectArgs {
     // node-grouped cuts, whose waves span several views)
     bool lds_views;
     int n_views;
+    // per-tile lists: entries of every tile of the pass, zero before (null: off)
+    uint32_t* tile_count;
+    uint32_t total_tiles;            // of the pass, at most kTileListMax with per-tile lists
+    uint4* scan_tmp;                 // the cut's scratch: counts of binned entries
+    SortBins clear;                  // bins of the depth sort
 };
 constexpr int kProjectLdsViews = 64;
+constexpr uint32_t kTileListMax = 8192;   // tiles of a pass that per-tile lists serve (their counts fit in LDS)
 void launch_project(const ProjectArgs& a, hipStream_t s);
 
 // keys[i] = view of the depth-sorted entry order[i] (order: index | tiles
 // << 28), read from the cut, so that a stable pass on them groups the
 // entries by view.
 void launch_view_keys(const uint32_t* order, const uint2* cut, const uint32_t* count, uint32_t cap, uint32_t* keys,
-                      hipStream_t s);
+                      SortBins clear, hipStream_t s);
 
-// Pair emission in depth order: offsets = exclusive scan of ntiles over the
-// depth-sorted entries.
+// Pair emission in depth order.
 struct EmitArgs {
     const uint32_t* order;           // depth-sorted entries (index | min(tiles, 15) << 28)
     const uint32_t* ntiles;
     const BinRec* bins;
     const Proj* proj;
     uint32_t cut_cap;
-    uint32_t* offsets;               // scratch [cut_cap]
+    uint32_t* sums;                  // scratch: pairs of every 256 entries (tile_sum_words(cut_cap) words)
     uint32_t* keys;
     uint32_t* vals;
     uint32_t pair_cap;
@@ -260,23 +297,29 @@ struct EmitArgs {
     uint4* scan_tmp;
     Counters* ctr;
     int tile_w, tile_h;              // tile shape in pixels
+    SortBins clear;                  // bins of the pair sort
 };
+// u32 pairs of every 256 entries, then u64 pairs of every 16,384
+constexpr size_t tile_sum_words(size_t cap) {
+    return ((cap + 255) / 256 + 1) / 2 * 2 + 2 * ((cap + 16383) / 16384);
+}
 void launch_emit(const EmitArgs& a, hipStream_t s);
 
-// Stable LSD radix sort of (key, value) pairs by the low key_bits bits.
-// count: device pointer to n (clamped to cap).  Ping-pong buffers; returns
-// the index (0 or 1) of the buffer pair that holds the result.
-struct SortArgs {
+// Per-tile lists instead of emission in depth order and the pair sort: the
+// sorted entries of every tile go to vals[1], the tiles' ranges to ranges.
+// Of EmitArgs: ntiles, bins, proj, cut_cap, exact_tiles, ctr and the tile
+// shape.
+struct TileListArgs {
+    uint32_t* tile_count;            // the projection's counts; then the tiles' cursors
+    uint32_t total_tiles;
+    const uint32_t* depth;           // depth bits of the entries
     uint32_t* keys[2];
     uint32_t* vals[2];
-    const uint32_t* count;
-    uint32_t cap;
-    int key_bits;
-    int max_digit_bits = 11;         // 6..11
-    uint32_t* hist;                  // kSortBins * (hist_stride + 1) counts
-    uint32_t hist_stride = kSortMaxGroups;   // per-digit row of hist: at least the sort's group count
+    uint32_t pair_cap;
+    uint2* ranges;
+    Counters* ctr;
 };
-int launch_sort(const SortArgs& a, hipStream_t s);
+void launch_emit_tiles(const EmitArgs& e, const TileListArgs& a, hipStream_t s);
 
 struct CompositeArgs {
     const uint32_t* keys;            // pair sort keys (view << key_shift | tile within the view), grouped

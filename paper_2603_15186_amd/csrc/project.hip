@@ -25,6 +25,38 @@ constexpr int kNT = 256;
 // compositor can take, whatever the rounding of its single-precision q.
 constexpr double kBinSlack = 1e-3;
 
+// Entries of more tile rows than kTallRows (pairs than kBigPairs) may be
+// counted (emitted) by their whole wave.
+constexpr int kTallRows = 8;
+constexpr uint32_t kBigPairs = 64;
+
+// Entries per workgroup of a pass over m cut entries: 256, fewer when there
+// are few, so that they spread over `blocks` workgroups.  A small view's pass
+// lasts as long as its slowest workgroup, and a Gaussian close to the camera
+// covers hundreds of tiles (a 1600 x 900 view of 80 of them, 89,000 pairs,
+// rendered by one workgroup: 693 us; spread, and the large ones by whole
+// waves: 194).  1,024 workgroups where each starts at once, 256 where each
+// first clears the tiles' counts in LDS.  Wave w of a workgroup takes entries
+// [w per / 4, (w + 1) per / 4), a lane each.
+__device__ __forceinline__ uint32_t entries_per_block(uint32_t m, uint32_t blocks) {
+    const uint32_t per = (ceil_div(m, blocks) + 3u) & ~3u;
+    return per < (uint32_t)kNT ? (per > 4u ? per : 4u) : (uint32_t)kNT;
+}
+
+// Sums of 2^20 entries' pairs, enough for every entry index.
+constexpr int kTopSums = 1 << (kNtShift - 20);
+static_assert(kTopSums <= kNT && kTopSums / 2 <= kCutBlocks, "a thread per sum; they fit the cut's block counts");
+
+__device__ __forceinline__ void clear_bins(const SortBins& b) {
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < b.n; i += gridDim.x * blockDim.x) b.words[i] = 0;
+}
+
+// This thread's entry among the block's `per` (per or more: none).
+__device__ __forceinline__ uint32_t entry_slot(uint32_t per) {
+    const uint32_t l = lane_id(), q = per / (kNT / kWave);
+    return l < q ? threadIdx.x / kWave * q + l : per;
+}
+
 // Real spherical-harmonic basis (Condon-Shortley phase) up to degree 3 as
 // Cartesian polynomials of the unit direction; index l*l + l + m.
 // Constants: sqrt((2l+1)/(4 pi) (l-m)!/(l+m)!) times the polynomial's
@@ -172,19 +204,81 @@ __device__ __forceinline__ void row_tiles(const RowSpan& r, double u, double v, 
     *hi = b < tx_hi ? b : tx_hi;
 }
 
-// Number of tiles of rect `rc` that the ellipse reaches (all of them when
-// exact is false).
-__device__ __forceinline__ uint32_t count_tiles(const Proj& p, ushort4 rc, int tw, int th, int H, bool exact) {
-    const uint32_t all = (uint32_t)(rc.z - rc.x + 1) * (uint32_t)(rc.w - rc.y + 1);
-    if (!exact || all <= 1) return all;
+// Tiles [lo, hi] of every tile row of rect `rc` that the ellipse reaches (all
+// of the rect's when exact is false), handed to row(ty, lo, hi).
+template <class F>
+__device__ __forceinline__ void rect_rows(const Proj& p, ushort4 rc, int tw, int th, int H, bool exact, F row) {
+    if (!exact || (rc.x == rc.z && rc.y == rc.w)) {
+        for (int ty = rc.y; ty <= rc.w; ++ty) row(ty, (int)rc.x, (int)rc.z);
+        return;
+    }
     const RowSpan r = row_span_init(p);
-    uint32_t n = 0;
     for (int ty = rc.y; ty <= rc.w; ++ty) {
         int lo, hi;
         row_tiles(r, p.u, p.v, ty, tw, th, H, rc.x, rc.z, &lo, &hi);
-        n += hi >= lo ? (uint32_t)(hi - lo + 1) : 0u;
+        row(ty, lo, hi);
     }
-    return n;
+}
+
+__device__ __forceinline__ float lane_f(float x, int l) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l));
+}
+__device__ __forceinline__ double lane_d(double x, int l) {
+    const uint64_t b = (uint64_t)__double_as_longlong(x);
+    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)b, l), hi = __builtin_amdgcn_readlane((uint32_t)(b >> 32), l);
+    return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
+}
+
+// Whether the wave's large entries are better taken by the whole wave, one
+// after the other (about 200 instructions each and 18 per tile row), than by
+// their own lanes side by side, where the longest sets the time (about 150
+// per exact row, 8 per pair).  Uniform over the wave.
+__device__ __forceinline__ bool wave_is_better(bool large, uint32_t rows, uint32_t pairs, bool exact) {
+    if (__ballot(large) == 0) return false;
+    const uint32_t together = wave_sum(large ? 200u + 18u * rows : 0u);
+    uint32_t alone = large ? 8u * pairs + (exact ? 150u : 8u) * rows : 0u;
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) alone = max(alone, (uint32_t)__shfl_xor(alone, d, kWave));
+    return together < alone;
+}
+
+// The same rows by a whole wave, for the lanes with `big` set one after the
+// other, a lane per row: rows(src, ty0, n, lo, hi) for up to 64 tile rows
+// ty0 .. ty0 + n - 1 of lane src's entry, lane l holding the interval of row
+// ty0 + l (empty: lo > hi; also the lanes past the n rows).  Every lane of
+// the wave takes part.
+template <class F>
+__device__ __forceinline__ void wave_rect_rows(bool big, const Proj& p, ushort4 rc, int tw, int th, int H, bool exact,
+                                               F rows) {
+    uint64_t todo = __ballot(big);
+    while (todo) {
+        const int src = __builtin_ctzll(todo);
+        todo &= todo - 1;
+        Proj q = {};
+        q.u = lane_d(p.u, src);
+        q.v = lane_d(p.v, src);
+        q.p = lane_f(p.p, src);
+        q.r = lane_f(p.r, src);
+        q.s = lane_f(p.s, src);
+        const uint32_t xy0 = __builtin_amdgcn_readlane((uint32_t)rc.x | (uint32_t)rc.y << 16, src);
+        const uint32_t xy1 = __builtin_amdgcn_readlane((uint32_t)rc.z | (uint32_t)rc.w << 16, src);
+        const int x0 = (int)(xy0 & 0xffffu), y0 = (int)(xy0 >> 16), x1 = (int)(xy1 & 0xffffu), y1 = (int)(xy1 >> 16);
+        const int h = __builtin_amdgcn_readlane(H, src);
+        const RowSpan r = row_span_init(q);
+        for (int ty0 = y0; ty0 <= y1; ty0 += kWave) {
+            const int ty = ty0 + lane_id();
+            int lo = 1, hi = 0;
+            if (ty <= y1) {
+                if (exact) {
+                    row_tiles(r, q.u, q.v, ty, tw, th, h, x0, x1, &lo, &hi);
+                } else {
+                    lo = x0;
+                    hi = x1;
+                }
+            }
+            rows(src, ty0, min(kWave, y1 - ty0 + 1), lo, hi);
+        }
+    }
 }
 
 // Rows of T = M R diag(s) for the Gaussian with quaternion (w, x, y, z) =
@@ -233,18 +327,36 @@ __device__ __forceinline__ double sphere_size(const ViewDev& V, float4 b) {
 // level pass, in frontier order), so g is that first child unless the entry
 // before it is a sibling of the same view.  The blended mean and depth key
 // follow the same FP64 steps as the unblended ones.
-template <bool Blend, int DEG>
+//
+// PerTile: the entries go into per-tile lists (launch_emit_tiles): every
+// tile's entries are counted here -- per 256 entries in LDS, then one atomic
+// for each tile they reach -- and the depth key holds no view.
+template <bool Blend, int DEG, bool PerTile>
 __global__ __launch_bounds__(kNT) void k_project(ProjectArgs a) {
     constexpr int kWords = (int)(sizeof(ViewDev) / 8);
     __shared__ uint64_t s_view[kProjectLdsViews * kWords];
+    __shared__ uint32_t s_count[PerTile ? kTileListMax : 1];
     const uint32_t m = min(a.ctr->cut, a.cut_cap);
+    const uint32_t per = entries_per_block(m, PerTile ? 256u : 1024u);
+    clear_bins(a.clear);
+    // the emission's sums of 2^20 entries (u64), in the cut's block counts
+    if (blockIdx.x == 0 && threadIdx.x < kTopSums / 2) a.scan_tmp[threadIdx.x] = make_uint4(0, 0, 0, 0);
+    if (blockIdx.x * per >= m) return;
+    if (PerTile) {
+        for (uint32_t t = threadIdx.x; t < a.total_tiles; t += kNT) s_count[t] = 0;
+        __syncthreads();
+    }
     if (a.lds_views) {
         const uint64_t* src = reinterpret_cast<const uint64_t*>(a.views);
         for (int k = threadIdx.x; k < a.n_views * kWords; k += kNT) s_view[k] = src[k];
         __syncthreads();
     }
     uint32_t vis = 0;
-    for (uint32_t i = blockIdx.x * kNT + threadIdx.x; i < m; i += gridDim.x * kNT) {
+    const uint32_t slot = entry_slot(per);
+    for (uint32_t i0 = blockIdx.x * per; i0 < m; i0 += gridDim.x * per) {
+        // (lanes without an entry repeat the last one and write nothing)
+        const bool valid = slot < per && i0 + slot < m;
+        const uint32_t i = valid ? i0 + slot : m - 1;
         const uint2 e = a.cut[i];
         ViewDev V;
         if (a.lds_views) {
@@ -300,6 +412,7 @@ __global__ __launch_bounds__(kNT) void k_project(ProjectArgs a) {
         }
         Proj p = {};
         uint32_t ntiles = 0;
+        bool seen = false;                             // its pixel box meets the image
         ushort4 rc = make_ushort4(1, 1, 0, 0);
         const float zf = (float)tz;
         if (tz > V.znear) {
@@ -351,162 +464,209 @@ __global__ __launch_bounds__(kNT) void k_project(ProjectArgs a) {
                 if (cx0 <= cx1 && cy0 <= cy1) {
                     rc = make_ushort4((unsigned short)((int)cx0 / a.tile_w), (unsigned short)((int)cy0 / a.tile_h),
                                       (unsigned short)((int)cx1 / a.tile_w), (unsigned short)((int)cy1 / a.tile_h));
-                    ntiles = count_tiles(p, rc, a.tile_w, a.tile_h, V.height, a.exact_tiles);
-                }
-                if (ntiles > 0) {
-                    const double id = 1.0 / sqrt(dx * dx + dy * dy + dz * dz);
-                    float rgb[3];
-                    sh_colour<Blend, DEG>(a.sh, g, pg, (float)t, (float)(dx * id), (float)(dy * id),
-                                          (float)(dz * id), rgb);
-                    p.c0 = rgb[0];
-                    p.c1 = rgb[1];
-                    p.c2 = rgb[2];
+                    seen = valid;
                 }
             }
         }
-        a.proj[i] = p;
-        BinRec br;
-        br.rc = rc;
-        br.tile_base = e.y << a.key_shift;
-        br.tiles_x = (uint16_t)V.tiles_x;
-        br.height = (uint16_t)V.height;
-        a.bins[i] = br;
-        a.ntiles[i] = ntiles;
-        // positive depths order as their bit patterns, and so do their
-        // offsets from depth_base; unbinned entries last
-        uint32_t dk = 0xffffffffu;
-        if (ntiles > 0) {
-            const uint32_t bits = __float_as_uint(zf);
-            if (bits < a.depth_base || bits > a.depth_top) atomicOr(&a.ctr->overflow, kOvDepth);
-            dk = bits - a.depth_base;
-            if (a.view_shift > 0) dk |= e.y << a.view_shift;
+        // tiles reached: a lane's own rows, or the wave's for tall entries
+        const bool tall = seen && (PerTile || a.exact_tiles) && rc.w - rc.y >= kTallRows;
+        const bool help = wave_is_better(tall, rc.w - rc.y + 1u,
+                                         PerTile ? (uint32_t)(rc.z - rc.x + 1) * (uint32_t)(rc.w - rc.y + 1) : 0u,
+                                         a.exact_tiles);
+        auto count_row = [&](uint32_t base, int tiles_x, int ty, int lo, int hi) {
+            if constexpr (PerTile)
+                for (int tx = lo; tx <= hi; ++tx) atomicAdd(&s_count[base + (uint32_t)(ty * tiles_x + tx)], 1u);
+        };
+        if (seen && !(tall && help)) {
+            if (!PerTile && !a.exact_tiles)
+                ntiles = (uint32_t)(rc.z - rc.x + 1) * (uint32_t)(rc.w - rc.y + 1);
+            else
+                rect_rows(p, rc, a.tile_w, a.tile_h, V.height, a.exact_tiles, [&](int ty, int lo, int hi) {
+                    ntiles += hi >= lo ? (uint32_t)(hi - lo + 1) : 0u;
+                    count_row(V.tile_base, V.tiles_x, ty, lo, hi);
+                });
         }
-        a.depth_key[i] = dk;
-        a.depth_val[i] = i | (min(ntiles, kNtSat) << kNtShift);
-        vis += ntiles > 0 ? 1u : 0u;
+        wave_rect_rows(tall && help, p, rc, a.tile_w, a.tile_h, V.height, a.exact_tiles,
+                       [&](int src, int ty0, int, int lo, int hi) {
+                           const uint32_t n = wave_sum(hi >= lo ? (uint32_t)(hi - lo + 1) : 0u);
+                           if (lane_id() == src) ntiles += n;
+                           if constexpr (PerTile)
+                               count_row(__builtin_amdgcn_readlane(V.tile_base, src),
+                                         __builtin_amdgcn_readlane(V.tiles_x, src), ty0 + lane_id(), lo, hi);
+                       });
+        if (ntiles > 0) {
+            const double id = 1.0 / sqrt(dx * dx + dy * dy + dz * dz);
+            float rgb[3];
+            sh_colour<Blend, DEG>(a.sh, g, pg, (float)t, (float)(dx * id), (float)(dy * id), (float)(dz * id), rgb);
+            p.c0 = rgb[0];
+            p.c1 = rgb[1];
+            p.c2 = rgb[2];
+        }
+        if (valid) {
+            a.proj[i] = p;
+            BinRec br;
+            br.rc = rc;
+            br.tile_base = PerTile ? V.tile_base : e.y << a.key_shift;
+            br.tiles_x = (uint16_t)V.tiles_x;
+            br.height = (uint16_t)V.height;
+            a.bins[i] = br;
+            a.ntiles[i] = ntiles;
+            vis += ntiles > 0 ? 1u : 0u;
+            // positive depths order as their bit patterns, and so do their
+            // offsets from depth_base; unbinned entries last
+            uint32_t dk = 0xffffffffu;
+            if (ntiles > 0) {
+                const uint32_t bits = __float_as_uint(zf);
+                if (bits < a.depth_base || bits > a.depth_top) atomicOr(&a.ctr->overflow, kOvDepth);
+                dk = bits - a.depth_base;
+                if (!PerTile && a.view_shift > 0) dk |= e.y << a.view_shift;
+            }
+            a.depth_key[i] = dk;
+            if (!PerTile) a.depth_val[i] = i | (min(ntiles, kNtSat) << kNtShift);
+        }
+        if constexpr (PerTile) {
+            __syncthreads();
+            for (uint32_t t = threadIdx.x; t < a.total_tiles; t += kNT) {
+                const uint32_t n = s_count[t];
+                if (n) {
+                    atomicAdd(a.tile_count + t, n);
+                    s_count[t] = 0;
+                }
+            }
+            __syncthreads();
+        }
     }
+    // binned entries, counted in 64 places that the binning adds up (one
+    // place for all waves costs 10 ns a wave)
     vis = wave_sum(vis);
-    if (lane_id() == 0 && vis) atomicAdd(&a.ctr->visible, vis);
+    if (lane_id() == 0 && vis)
+        atomicAdd(reinterpret_cast<uint32_t*>(a.scan_tmp + kSeenAt) + blockIdx.x % kSeenSlots, vis);
 }
+
+// Binned entries into the counters (one wave).
+__device__ __forceinline__ void sum_seen(const uint4* scan_tmp, Counters* ctr) {
+    const uint32_t n = wave_sum(reinterpret_cast<const uint32_t*>(scan_tmp + kSeenAt)[lane_id()]);
+    if (lane_id() == 0) ctr->visible = n;
+}
+static_assert(kSeenSlots == kWave, "one place per lane");
+
 
 // ---------------------------------------------------------------- emission
 
-struct ScanCtx {
+// Where the pairs of the depth-ordered entries go is the sum of the tile
+// counts before them: kept as sums of 256 entries (u32), 16,384 (u64) and
+// 2^20 (u64), which an emitting workgroup adds up for itself.  (A scan in
+// three launches wrote an offset per entry and cost 13 us in a single view,
+// 43 us and 8 bytes per entry in a 50-view batch.)
+struct TileSums {
     const uint32_t* order;
     const uint32_t* ntiles;
-    const uint32_t* count;
-    uint32_t cap;
-    uint32_t* offsets;
-    uint4* tmp;
-    Counters* ctr;
-    uint32_t pair_cap;
+    uint32_t* fine;
+    unsigned long long* mid;
+    unsigned long long* top;
 };
+
+__device__ __forceinline__ TileSums tile_sums(const EmitArgs& a) {
+    return {a.order, a.ntiles, a.sums,
+            reinterpret_cast<unsigned long long*>(a.sums + (ceil_div(a.cut_cap, 256u) + 1u) / 2u * 2u),
+            reinterpret_cast<unsigned long long*>(a.scan_tmp)};
+}
 
 // Tile count of a depth-sorted value: carried in its top bits unless
 // saturated.
-__device__ __forceinline__ uint32_t tiles_of(const ScanCtx& c, uint32_t val, uint32_t n) {
+__device__ __forceinline__ uint32_t tiles_of(const uint32_t* ntiles, uint32_t val, uint32_t n) {
     const uint32_t nt = val >> kNtShift, e = val & kEntryMask;
-    return nt < kNtSat ? nt : (e < n ? c.ntiles[e] : 0u);
+    return nt < kNtSat ? nt : (e < n ? ntiles[e] : 0u);
 }
 
-__device__ __forceinline__ void chunk_of(uint32_t n, int G, int b, uint32_t* lo, uint32_t* hi) {
-    uint32_t chunk = ceil_div(n, (uint32_t)G);
-    if (chunk < (uint32_t)kNT) chunk = kNT;
-    chunk = ceil_div(chunk, (uint32_t)kNT) * kNT;
-    uint64_t s = (uint64_t)b * chunk, e = s + chunk;
-    *lo = (uint32_t)(s < n ? s : n);
-    *hi = (uint32_t)(e < n ? e : n);
-}
-
-__global__ __launch_bounds__(kNT) void k_scan_reduce(ScanCtx c) {
-    __shared__ uint32_t sh[kNT / kWave + 1];
-    const uint32_t n = min(*c.count, c.cap);
-    uint32_t lo, hi;
-    chunk_of(n, gridDim.x, blockIdx.x, &lo, &hi);
-    uint32_t acc = 0;
-    for (uint32_t i = lo + threadIdx.x; i < hi; i += kNT) acc += tiles_of(c, c.order[i], n);
-    uint32_t tot;
-    block_excl_scan<kNT>(acc, sh, &tot);
-    if (threadIdx.x == 0) c.tmp[blockIdx.x] = make_uint4(tot, 0, 0, 0);
-}
-
-// Exclusive scan of the G <= 4 * 1024 block counts (four consecutive ones
-// per thread); the total is also summed in 64 bits so that pair counts
-// beyond 2^32 are caught as overflow.
-__global__ __launch_bounds__(1024) void k_scan_blocks(ScanCtx c, int G) {
-    __shared__ uint32_t sh[1024 / kWave + 1];
-    __shared__ unsigned long long sh64[1024 / kWave];
-    const int t = threadIdx.x;
-    uint32_t x[4], sum = 0;
-    unsigned long long sum64 = 0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int b = 4 * t + j;
-        x[j] = b < G ? c.tmp[b].x : 0u;
-        sum += x[j];
-        sum64 += x[j];
-    }
-    uint32_t tot;
-    uint32_t ex = block_excl_scan<1024>(sum, sh, &tot);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int b = 4 * t + j;
-        if (b < G) c.tmp[b].x = ex;
-        ex += x[j];
-    }
-    for (int o = kWave / 2; o > 0; o >>= 1) sum64 += __shfl_xor(sum64, o, kWave);
-    if (lane_id() == 0) sh64[t / kWave] = sum64;
-    __syncthreads();
-    if (t == 0) {
-        unsigned long long total = 0;
-        for (int w = 0; w < 1024 / kWave; ++w) total += sh64[w];
-        Counters* k = c.ctr;
-        if (total > c.pair_cap) {
-            k->overflow |= kOvPairs;
-            const uint32_t need = (uint32_t)(total < 0xffffffffull ? total : 0xffffffffull);
-            if (need > k->need_pairs) k->need_pairs = need;
+// A workgroup per 16,384 entries, 16 x 256 of them per wave.
+__global__ __launch_bounds__(kNT) void k_tile_sums(EmitArgs a) {
+    __shared__ unsigned long long s_sum[kNT / kWave];
+    const TileSums s = tile_sums(a);
+    const uint32_t n = min(a.ctr->cut, a.cut_cap);
+    const uint32_t w = threadIdx.x / kWave, l = lane_id();
+    for (uint32_t blk = blockIdx.x; blk * 16384ull < n; blk += gridDim.x) {
+        unsigned long long acc = 0;
+#pragma unroll 4
+        for (uint32_t j = 0; j < 16; ++j) {
+            const uint32_t c = blk * 64 + w * 16 + j, i = c * 256 + 4 * l;
+            uint32_t x = 0;
+            if (i + 4 <= n) {
+                const uint4 v = *reinterpret_cast<const uint4*>(s.order + i);
+                x = tiles_of(s.ntiles, v.x, n) + tiles_of(s.ntiles, v.y, n) + tiles_of(s.ntiles, v.z, n) +
+                    tiles_of(s.ntiles, v.w, n);
+            } else {
+                for (uint32_t k = i; k < n; ++k) x += tiles_of(s.ntiles, s.order[k], n);
+            }
+            x = wave_sum(x);                          // below 2^28: at most 2^20 tiles an entry
+            if (l == 0 && c * 256 < n) s.fine[c] = x;
+            acc += x;
         }
-        k->pairs = total < c.pair_cap ? (uint32_t)total : c.pair_cap;
+        if (l == 0) s_sum[w] = acc;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            unsigned long long t = 0;
+#pragma unroll
+            for (int q = 0; q < kNT / kWave; ++q) t += s_sum[q];
+            s.mid[blk] = t;
+            if (t) atomicAdd(s.top + blk / 64, t);
+        }
+        __syncthreads();
     }
 }
 
-__global__ __launch_bounds__(kNT) void k_scan_write(ScanCtx c) {
-    __shared__ uint32_t sh[kNT / kWave + 1];
-    const uint32_t n = min(*c.count, c.cap);
-    uint32_t lo, hi;
-    chunk_of(n, gridDim.x, blockIdx.x, &lo, &hi);
-    if (lo >= hi) return;
-    uint32_t off = c.tmp[blockIdx.x].x;
-    for (uint32_t s = lo; s < hi; s += kNT) {
-        const uint32_t i = s + threadIdx.x;
-        uint32_t x = 0;
-        if (i < hi) x = tiles_of(c, c.order[i], n);
-        uint32_t tot;
-        const uint32_t ex = block_excl_scan<kNT>(x, sh, &tot);
-        if (i < hi) c.offsets[i] = off + ex;
-        off += tot;
-    }
+// Pairs of the entries before `first` (this thread's part of the sum).
+__device__ __forceinline__ unsigned long long pairs_before(const TileSums& s, uint32_t first, uint32_t n) {
+    const uint32_t t = threadIdx.x, c = first / 256;
+    unsigned long long acc = 0;
+    if (t < (c >> 12)) acc += s.top[t];
+    if (t < ((c >> 6) & 63u)) acc += s.mid[(c >> 12) * 64 + t];
+    if (t >= kWave && t - kWave < (c & 63u)) acc += s.fine[(c & ~63u) + t - kWave];
+    if (c * 256 + t < first) acc += tiles_of(s.ntiles, s.order[c * 256 + t], n);
+    return acc;
 }
 
-// Pairs of one depth-ordered entry, handed to put(k, tile) in order.
+// Pairs of every lane's entry (e, with nt of them; nt = 0: none), handed to
+// put(at, tag, tile): at = pos and up for the entry's pairs in order, tag the
+// entry's.  Every lane of the wave takes part; the calls for an entry of more
+// than kBigPairs come from all of them.
 template <class F>
-__device__ __forceinline__ void entry_tiles(const EmitArgs& a, uint32_t e, uint32_t nt, const BinRec& br, F put) {
+__device__ __forceinline__ void entry_tiles(const EmitArgs& a, uint32_t e, uint32_t nt, const BinRec& br, uint32_t pos,
+                                            uint32_t tag, F put) {
     const ushort4 rc = br.rc;
-    const uint32_t tw = br.tiles_x;
     const uint32_t all = (uint32_t)(rc.z - rc.x + 1) * (uint32_t)(rc.w - rc.y + 1);
-    uint32_t k = 0;
     // the exact set is part of the rectangle: equal counts mean all of it
-    if (!a.exact_tiles || nt == all) {
-        for (int ty = rc.y; ty <= rc.w; ++ty)
-            for (int tx = rc.x; tx <= rc.z; ++tx) put(k++, br.tile_base + (uint32_t)ty * tw + (uint32_t)tx);
-        return;
+    const bool rect = !a.exact_tiles || nt == all;
+    const bool large = nt > kBigPairs;
+    const bool help = wave_is_better(large, rc.w - rc.y + 1u, nt, !rect);
+    const bool big = large && help;
+    Proj p = {};
+    if (nt && !rect) p = a.proj[e];
+    if (nt && !big) {
+        uint32_t at = pos;
+        rect_rows(p, rc, a.tile_w, a.tile_h, br.height, !rect, [&](int ty, int lo, int hi) {
+            const uint32_t row = br.tile_base + (uint32_t)ty * br.tiles_x;
+            for (int tx = lo; tx <= hi; ++tx) put(at++, tag, row + (uint32_t)tx);
+        });
     }
-    const Proj p = a.proj[e];
-    const RowSpan r = row_span_init(p);
-    for (int ty = rc.y; ty <= rc.w; ++ty) {
-        int lo, hi;
-        row_tiles(r, p.u, p.v, ty, a.tile_w, a.tile_h, br.height, rc.x, rc.z, &lo, &hi);
-        for (int tx = lo; tx <= hi; ++tx) put(k++, br.tile_base + (uint32_t)ty * tw + (uint32_t)tx);
+    for (int pass = 0; pass < 2; ++pass) {            // ellipses, then full rectangles
+        uint32_t at = 0;                              // next pair of the entry in turn
+        int last = -1;
+        wave_rect_rows(big && rect == (pass == 1), p, rc, a.tile_w, a.tile_h, br.height, pass == 0,
+                       [&](int src, int ty0, int n, int lo, int hi) {
+                           if (src != last) at = __builtin_amdgcn_readlane(pos, src);
+                           last = src;
+                           const uint32_t its = __builtin_amdgcn_readlane(tag, src);
+                           const uint32_t base = __builtin_amdgcn_readlane(br.tile_base, src);
+                           const uint32_t width = __builtin_amdgcn_readlane((uint32_t)br.tiles_x, src);
+                           for (int j = 0; j < n; ++j) {
+                               const int l = __builtin_amdgcn_readlane(lo, j), h = __builtin_amdgcn_readlane(hi, j);
+                               const uint32_t row = base + (uint32_t)(ty0 + j) * width;
+                               for (int tx = l + lane_id(); tx <= h; tx += kWave)
+                                   put(at + (uint32_t)(tx - l), its, row + (uint32_t)tx);
+                               at += h >= l ? (uint32_t)(h - l + 1) : 0u;
+                           }
+                       });
     }
 }
 
@@ -516,45 +676,63 @@ __device__ __forceinline__ void entry_tiles(const EmitArgs& a, uint32_t e, uint3
 // staging capacity are stored directly.
 constexpr uint32_t kEmitStage = 2048;
 
-__global__ __launch_bounds__(kNT) void k_emit(EmitArgs a) {
+__global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(6))) void k_emit(EmitArgs a) {
     __shared__ uint32_t s_key[kEmitStage];
     __shared__ uint32_t s_val[kEmitStage];
-    __shared__ uint32_t s_base, s_end;
+    __shared__ uint32_t s_scan[kNT / kWave + 1];
+    __shared__ unsigned long long s_before[kNT / kWave];
     const uint32_t m = min(a.ctr->cut, a.cut_cap);
     const uint32_t cap = a.pair_cap;
-    for (uint32_t first = blockIdx.x * kNT; first < m; first += gridDim.x * kNT) {
-        const uint32_t i = first + threadIdx.x;
-        uint32_t e = 0, nt = 0, pos = 0;
-        if (i < m) {
+    const TileSums sums = tile_sums(a);
+    clear_bins(a.clear);
+    if (blockIdx.x == 0 && threadIdx.x < kWave) {
+        sum_seen(a.scan_tmp, a.ctr);
+        unsigned long long total = 0;
+        for (int t = lane_id(); t < kTopSums; t += kWave) total += sums.top[t];
+        for (int o = kWave / 2; o > 0; o >>= 1) total += __shfl_xor(total, o, kWave);
+        if (lane_id() == 0) {
+            Counters* k = a.ctr;
+            if (total > cap) {
+                k->overflow |= kOvPairs;
+                const uint32_t need = (uint32_t)(total < 0xffffffffull ? total : 0xffffffffull);
+                if (need > k->need_pairs) k->need_pairs = need;
+            }
+            k->pairs = total < cap ? (uint32_t)total : cap;
+        }
+    }
+    const uint32_t per = entries_per_block(m, 1024);
+    const uint32_t slot = entry_slot(per);
+    for (uint32_t first = blockIdx.x * per; first < m; first += gridDim.x * per) {
+        const uint32_t i = first + slot;
+        uint32_t e = 0, nt = 0;
+        if (slot < per && i < m) {
             const uint32_t val = a.order[i];
             e = val & kEntryMask;
-            nt = val >> kNtShift;
-            if (nt == kNtSat) nt = e < m ? a.ntiles[e] : 0u;
-            pos = a.offsets[i];
+            nt = tiles_of(a.ntiles, val, m);
         }
-        if (threadIdx.x == 0) {
-            s_base = pos;
-            s_end = pos;
-        }
+        unsigned long long before = pairs_before(sums, first, m);
+        BinRec br = {};
+        if (nt) br = a.bins[e];
+        for (int o = kWave / 2; o > 0; o >>= 1) before += __shfl_xor(before, o, kWave);
+        if (lane_id() == 0) s_before[threadIdx.x / kWave] = before;
+        uint32_t tot;
+        const uint32_t ex = block_excl_scan<kNT>(nt, s_scan, &tot);
+        unsigned long long base64 = 0;
+#pragma unroll
+        for (int q = 0; q < kNT / kWave; ++q) base64 += s_before[q];
+        const bool fits = base64 < cap;               // (else an overflow, reported above)
+        const uint32_t base = (uint32_t)base64;
+        entry_tiles(a, e, fits ? nt : 0u, br, ex, e, [&](uint32_t L, uint32_t who, uint32_t tile) {
+            if (L < kEmitStage) {
+                s_key[L] = tile;
+                s_val[L] = who;
+            } else if (base + L < cap) {
+                a.keys[base + L] = tile;
+                a.vals[base + L] = who;
+            }
+        });
         __syncthreads();
-        const uint32_t base = s_base;
-        if (nt) {
-            atomicMax(&s_end, pos + nt);
-            const BinRec br = a.bins[e];
-            const uint32_t lp = pos - base;
-            entry_tiles(a, e, nt, br, [&](uint32_t k, uint32_t tile) {
-                const uint32_t L = lp + k;
-                if (L < kEmitStage) {
-                    s_key[L] = tile;
-                    s_val[L] = e;
-                } else if (pos + k < cap) {
-                    a.keys[pos + k] = tile;
-                    a.vals[pos + k] = e;
-                }
-            });
-        }
-        __syncthreads();
-        const uint32_t len = min(s_end - base, kEmitStage);
+        const uint32_t len = fits ? min(tot, kEmitStage) : 0u;
         for (uint32_t q = threadIdx.x; q < len; q += kNT) {
             if (base + q < cap) {
                 a.keys[base + q] = s_key[q];
@@ -565,54 +743,240 @@ __global__ __launch_bounds__(kNT) void k_emit(EmitArgs a) {
     }
 }
 
+// ------------------------------------------------------- per-tile lists
+//
+// Few pairs (one small view, say) spend their time in the launches of two
+// radix sorts: 18 of them, and the scan between, for 50,000 to 1,000,000
+// pairs.  Here the projection has counted every tile's entries; one
+// workgroup turns the counts into ranges, every pair takes a place in its
+// tile's range (in any order), and each tile's list is sorted by (depth,
+// entry) -- the order of the stable sorts -- in LDS.  Four launches from the
+// projection to the compositor.  Places come from LDS atomics within a
+// workgroup's 256 entries and one global atomic per workgroup and tile: an
+// atomic per pair on the tile's own counter, which neighbouring entries
+// share, took 58 us for 200,000 pairs of a usual view and 1.5 ms for a view
+// close to a wall.
+
+// Ranges of the tiles from their counts, four tiles per thread and step; the
+// places' cursors start at them.  One workgroup: a few thousand tiles are a
+// few steps.
+__global__ __launch_bounds__(1024) void k_tile_scan(TileListArgs a, const uint4* scan_tmp) {
+    __shared__ uint32_t sh[1024 / kWave + 1];
+    if (threadIdx.x < kWave) sum_seen(scan_tmp, a.ctr);
+    unsigned long long run = 0;
+    for (uint32_t base = 0; base < a.total_tiles; base += 4 * 1024) {
+        const uint32_t t0 = base + 4 * threadIdx.x;
+        uint32_t x[4], sum = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            x[j] = t0 + j < a.total_tiles ? a.tile_count[t0 + j] : 0u;
+            sum += x[j];
+        }
+        uint32_t tot;
+        // a step's sum stays below 2^32: at most 4,096 tiles of 2^20 entries
+        uint32_t ex = block_excl_scan<1024>(sum, sh, &tot);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (t0 + j < a.total_tiles) {
+                const unsigned long long lo = run + ex, hi = lo + x[j], cap = a.pair_cap;
+                const uint32_t start = (uint32_t)(lo < cap ? lo : cap);
+                a.ranges[t0 + j] = make_uint2(start, (uint32_t)(hi < cap ? hi : cap));
+                a.tile_count[t0 + j] = start;
+            }
+            ex += x[j];
+        }
+        run += tot;
+    }
+    if (threadIdx.x == 0) {
+        Counters* k = a.ctr;
+        if (run > a.pair_cap) {
+            k->overflow |= kOvPairs;
+            const uint32_t need = (uint32_t)(run < 0xffffffffull ? run : 0xffffffffull);
+            if (need > k->need_pairs) k->need_pairs = need;
+        }
+        k->pairs = (uint32_t)(run < a.pair_cap ? run : a.pair_cap);
+    }
+}
+
+// Each workgroup lists the pairs of 256 entries in LDS, kTileStage at a
+// time, ranks them within their tiles, takes the tiles' next places and
+// writes the pairs there.
+constexpr uint32_t kTileStage = 4096;
+
+__global__ __launch_bounds__(kNT) void k_emit_tiles(EmitArgs a, TileListArgs l) {
+    __shared__ uint32_t s_count[kTileListMax];
+    // tile | entry of the workgroup << 13 | rank among the workgroup's pairs
+    // of the tile << 21 (an entry reaches a tile once)
+    __shared__ uint32_t s_pair[kTileStage];
+    __shared__ uint32_t s_depth[kNT];
+    __shared__ uint32_t s_scan[kNT / kWave + 1];
+    static_assert(kTileListMax <= 1u << 13 && kNT <= 256, "packed pairs");
+    const uint32_t m = min(a.ctr->cut, a.cut_cap);
+    const uint32_t per = entries_per_block(m, 256);
+    if (blockIdx.x * per >= m) return;
+    for (uint32_t t = threadIdx.x; t < l.total_tiles; t += kNT) s_count[t] = 0;
+    const uint32_t slot = entry_slot(per);
+    for (uint32_t first = blockIdx.x * per; first < m; first += gridDim.x * per) {
+        const uint32_t i = first + slot;
+        const bool valid = slot < per && i < m;
+        const uint32_t nt = valid ? a.ntiles[i] : 0u;
+        if (slot < per) s_depth[slot] = valid ? l.depth[i] : 0u;
+        BinRec br = {};
+        if (nt) br = a.bins[i];
+        uint32_t tot;
+        const uint32_t at = block_excl_scan<kNT>(nt, s_scan, &tot);   // (also orders the cleared counts)
+        for (uint32_t w0 = 0; w0 < tot; w0 += kTileStage) {
+            const bool here = nt && at < w0 + kTileStage && at + nt > w0;
+            entry_tiles(a, i, here ? nt : 0u, br, at - w0, slot, [&](uint32_t L, uint32_t who, uint32_t tile) {
+                // (L wraps past the stage for the pairs of an earlier one)
+                if (L < kTileStage) s_pair[L] = tile | who << 13 | atomicAdd(&s_count[tile], 1u) << 21;
+            });
+            __syncthreads();
+            for (uint32_t t = threadIdx.x; t < l.total_tiles; t += kNT) {
+                const uint32_t n = s_count[t];
+                if (n) s_count[t] = atomicAdd(l.tile_count + t, n);
+            }
+            __syncthreads();
+            const uint32_t len = min(tot - w0, kTileStage);
+            for (uint32_t q = threadIdx.x; q < len; q += kNT) {
+                const uint32_t p = s_pair[q], who = p >> 13 & 255u;
+                const uint32_t pos = s_count[p & 8191u] + (p >> 21);
+                if (pos < l.pair_cap) {                           // else: an overflow the scan has reported
+                    l.keys[0][pos] = s_depth[who];
+                    l.vals[0][pos] = first + who;
+                }
+            }
+            __syncthreads();
+            for (uint32_t t = threadIdx.x; t < l.total_tiles; t += kNT) s_count[t] = 0;
+            __syncthreads();
+        }
+        __syncthreads();
+    }
+}
+
+// One workgroup per tile sorts its list by (depth, entry): up to 256 pairs
+// by ranking (a pair's place is the number of smaller ones, counted over the
+// list in LDS with no barrier in between), up to kSortMax by a bitonic
+// network in LDS; longer lists in runs of kSortMax that are then merged
+// pairwise through memory, every element's place found by a binary search in
+// the other run.
+constexpr uint32_t kSortMax = 4096;
+
+__global__ __launch_bounds__(kNT) void k_sort_tiles(TileListArgs a) {
+    __shared__ unsigned long long s[kSortMax];
+    const uint2 rg = a.ranges[blockIdx.x];
+    const uint32_t n = rg.y - rg.x;
+    if (n == 0) return;
+    uint32_t *k0 = a.keys[0] + rg.x, *v0 = a.vals[0] + rg.x, *k1 = a.keys[1] + rg.x, *v1 = a.vals[1] + rg.x;
+    const uint32_t t = threadIdx.x;
+    if (n <= (uint32_t)kNT) {
+        unsigned long long x = 0ull;
+        if (t < n) {
+            x = (unsigned long long)k0[t] << 32 | v0[t];
+            s[t] = x;
+        }
+        __syncthreads();
+        if (t / kWave * kWave >= n) return;               // whole waves without an element
+        uint32_t r = 0;
+#pragma unroll 8
+        for (uint32_t j = 0; j < n; ++j) r += s[j] < x ? 1u : 0u;
+        if (t < n) v1[r] = (uint32_t)x;
+        return;
+    }
+    for (uint32_t base = 0; base < n; base += kSortMax) {
+        const uint32_t m = min(n - base, kSortMax);
+        uint32_t size = 2;
+        while (size < m) size <<= 1;
+        for (uint32_t i = t; i < size; i += kNT)
+            s[i] = i < m ? (unsigned long long)k0[base + i] << 32 | v0[base + i] : ~0ull;
+        __syncthreads();
+        for (uint32_t k = 2; k <= size; k <<= 1)
+            for (uint32_t j = k >> 1; j > 0; j >>= 1) {
+                for (uint32_t q = t; q < size / 2; q += kNT) {
+                    const uint32_t lo = 2 * q - (q & (j - 1)), hi = lo + j;
+                    const unsigned long long x = s[lo], y = s[hi];
+                    if ((x > y) == ((lo & k) == 0)) {
+                        s[lo] = y;
+                        s[hi] = x;
+                    }
+                }
+                __syncthreads();
+            }
+        for (uint32_t i = t; i < m; i += kNT) {
+            v1[base + i] = (uint32_t)s[i];
+            if (n > kSortMax) k1[base + i] = (uint32_t)(s[i] >> 32);
+        }
+        __syncthreads();
+    }
+    // merge runs of w: an element's place is its index in its own run plus
+    // the number of smaller ones in the other (all elements differ)
+    bool in1 = true;                                      // which buffer holds the runs
+    for (uint64_t w = kSortMax; w < n; w *= 2) {
+        uint32_t *ks = in1 ? k1 : k0, *vs = in1 ? v1 : v0, *kd = in1 ? k0 : k1, *vd = in1 ? v0 : v1;
+        for (uint32_t i = t; i < n; i += kNT) {
+            const unsigned long long x = (unsigned long long)ks[i] << 32 | vs[i];
+            const uint64_t pair = i / (2 * w) * (2 * w), mine = i / w * w;
+            const uint64_t other = mine == pair ? pair + w : pair;
+            uint64_t lo = min(other, (uint64_t)n), hi = min(other + w, (uint64_t)n);
+            const uint64_t o0 = lo;
+            while (lo < hi) {
+                const uint64_t mid = (lo + hi) / 2;
+                if (((unsigned long long)ks[mid] << 32 | vs[mid]) < x) lo = mid + 1; else hi = mid;
+            }
+            const uint64_t to = pair + (i - mine) + (lo - o0);
+            kd[to] = (uint32_t)(x >> 32);
+            vd[to] = (uint32_t)x;
+        }
+        in1 = !in1;
+        __syncthreads();
+    }
+    if (!in1)
+        for (uint32_t i = t; i < n; i += kNT) v1[i] = v0[i];
+}
+
 }  // namespace
 
 __global__ void k_view_keys(const uint32_t* __restrict__ order, const uint2* __restrict__ cut, const uint32_t* count,
-                            uint32_t cap, uint32_t* __restrict__ keys) {
+                            uint32_t cap, uint32_t* __restrict__ keys, SortBins clear) {
     const uint32_t n = min(*count, cap);
+    clear_bins(clear);
     for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
         const uint32_t e = order[i] & kEntryMask;
         keys[i] = e < n ? cut[e].y : 0u;
     }
 }
 
-template <bool Blend>
+template <bool Blend, bool PerTile>
 void launch_project_b(const ProjectArgs& a, hipStream_t s) {
     switch (a.sh_degree) {
-        case 0: k_project<Blend, 0><<<4096, kNT, 0, s>>>(a); break;
-        case 1: k_project<Blend, 1><<<4096, kNT, 0, s>>>(a); break;
-        case 2: k_project<Blend, 2><<<4096, kNT, 0, s>>>(a); break;
-        default: k_project<Blend, 3><<<4096, kNT, 0, s>>>(a); break;
+        case 0: k_project<Blend, 0, PerTile><<<4096, kNT, 0, s>>>(a); break;
+        case 1: k_project<Blend, 1, PerTile><<<4096, kNT, 0, s>>>(a); break;
+        case 2: k_project<Blend, 2, PerTile><<<4096, kNT, 0, s>>>(a); break;
+        default: k_project<Blend, 3, PerTile><<<4096, kNT, 0, s>>>(a); break;
     }
 }
 
 void launch_project(const ProjectArgs& a, hipStream_t s) {
+    const bool tiles = a.tile_count != nullptr;
     if (a.blend)
-        launch_project_b<true>(a, s);
+        tiles ? launch_project_b<true, true>(a, s) : launch_project_b<true, false>(a, s);
     else
-        launch_project_b<false>(a, s);
+        tiles ? launch_project_b<false, true>(a, s) : launch_project_b<false, false>(a, s);
+}
+
+void launch_emit_tiles(const EmitArgs& e, const TileListArgs& a, hipStream_t s) {
+    k_tile_scan<<<1, 1024, 0, s>>>(a, e.scan_tmp);
+    k_emit_tiles<<<2048, kNT, 0, s>>>(e, a);
+    k_sort_tiles<<<a.total_tiles, kNT, 0, s>>>(a);
 }
 
 void launch_view_keys(const uint32_t* order, const uint2* cut, const uint32_t* count, uint32_t cap, uint32_t* keys,
-                      hipStream_t s) {
-    k_view_keys<<<2048, 256, 0, s>>>(order, cut, count, cap, keys);
+                      SortBins clear, hipStream_t s) {
+    k_view_keys<<<2048, 256, 0, s>>>(order, cut, count, cap, keys, clear);
 }
 
 void launch_emit(const EmitArgs& a, hipStream_t s) {
-    const int G = kCutBlocks;
-    static_assert(kCutBlocks <= 4 * 1024, "the block scan takes four counts per thread");
-    ScanCtx c;
-    c.order = a.order;
-    c.ntiles = a.ntiles;
-    c.count = &a.ctr->cut;
-    c.cap = a.cut_cap;
-    c.offsets = a.offsets;
-    c.tmp = a.scan_tmp;
-    c.ctr = a.ctr;
-    c.pair_cap = a.pair_cap;
-    k_scan_reduce<<<G, kNT, 0, s>>>(c);
-    k_scan_blocks<<<1, 1024, 0, s>>>(c, G);
-    k_scan_write<<<G, kNT, 0, s>>>(c);
+    k_tile_sums<<<2048, kNT, 0, s>>>(a);
     k_emit<<<8192, kNT, 0, s>>>(a);
 }
 

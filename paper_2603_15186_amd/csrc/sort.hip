@@ -6,12 +6,14 @@
 // key three to six.  The input is cut into groups (group_size); a workgroup takes groups b, b + G, b + 2G, ... so that the groups in flight
 // at any moment form one contiguous window of the input and each digit's
 // output advances as one front (writes of neighbouring groups land next to
-// each other and fill whole cache lines).  Each pass is three launches with
+// each other and fill whole cache lines).  Each pass is two launches with
 // no inter-workgroup waiting:
 //   upsweep   : the digit histogram of every group (LDS atomics into
-//               per-wave histograms), digit-major;
-//   row scan  : one block per digit scans that digit's per-group counts;
-//   downsweep : each group is ranked stably sub-tile by sub-tile -- lanes
+//               per-wave histograms), also added to the sums of its 16 and
+//               of its 256 neighbours;
+//   downsweep : a group adds up what lies before it (whole 256s, then 16s,
+//               then groups: some 25 reads per digit), then is
+//               ranked stably sub-tile by sub-tile -- lanes
 //               with equal digits are found by ballots over the digit bits,
 //               per-wave counters live in LDS -- and its keys and values are
 //               scattered.
@@ -65,19 +67,29 @@ __device__ __forceinline__ uint64_t match_digit(uint32_t d, uint64_t active) {
     return m;
 }
 
+// Rows of NB counts: one per group, then (bins) one per 16 groups and one
+// per 256 groups.  Two sets of bins take turns: a pass's upsweep clears the
+// other set for the next pass, and the first pass finds its set cleared
+// (sort_bins).
+struct HistDev {
+    uint32_t* group;
+    uint32_t* b16;
+    uint32_t* b256;
+};
+
 // Digit histogram of every group the block owns: per-wave LDS histograms
 // take one atomic add per key (counts do not depend on order), four keys per
 // thread and step with 16-byte loads (groups start at multiples of 1,024).
 template <int DB>
 __global__ __launch_bounds__(kNT) void k_upsweep(const uint32_t* __restrict__ keys, const uint32_t* count,
-                                                 uint32_t cap, int shift, uint32_t MASK, uint32_t* __restrict__ hist,
-                                                 uint32_t stride) {
+                                                 uint32_t cap, int shift, uint32_t MASK, HistDev H, SortBins next) {
     constexpr int NB = 1 << DB;
     __shared__ uint32_t h[kNW][NB];
     const int t = threadIdx.x;
     uint32_t* hw = h[t / kWave];
     const uint32_t n = n_of(count, cap);
     const uint32_t gs = group_size(n), ng = ceil_div(n, gs);
+    for (uint32_t i = blockIdx.x * kNT + t; i < next.n; i += gridDim.x * kNT) next.words[i] = 0;
     for (uint32_t g = blockIdx.x; g < ng; g += gridDim.x) {
         for (int i = t; i < NB; i += kNT) {
 #pragma unroll
@@ -100,31 +112,14 @@ __global__ __launch_bounds__(kNT) void k_upsweep(const uint32_t* __restrict__ ke
             uint32_t c = 0;
 #pragma unroll
             for (int w = 0; w < kNW; ++w) c += h[w][i];
-            hist[(size_t)i * stride + g] = c;   // digit-major
+            H.group[(size_t)g * NB + i] = c;
+            if (c) {
+                atomicAdd(H.b16 + (size_t)(g / 16) * NB + i, c);
+                atomicAdd(H.b256 + (size_t)(g / 256) * NB + i, c);
+            }
         }
         __syncthreads();
     }
-}
-
-// One block per digit: exclusive scan of the digit's per-group counts
-// hist[d][0..groups) in place; the digit total goes to totals[d].
-__global__ __launch_bounds__(1024) void k_rowscan(uint32_t* __restrict__ hist, const uint32_t* count, uint32_t cap,
-                                                  uint32_t stride, uint32_t* __restrict__ totals) {
-    __shared__ uint32_t sh[1024 / kWave + 1];
-    const int d = blockIdx.x, t = threadIdx.x;
-    const uint32_t n = n_of(count, cap);
-    const uint32_t ng = ceil_div(n, group_size(n));
-    uint32_t* row = hist + (size_t)d * stride;
-    uint32_t run = 0;
-    for (uint32_t base = 0; base < ng; base += 1024) {
-        const uint32_t i = base + (uint32_t)t;
-        const uint32_t x = i < ng ? row[i] : 0u;
-        uint32_t tot;
-        const uint32_t ex = block_excl_scan<1024>(x, sh, &tot);
-        if (i < ng) row[i] = run + ex;
-        run += tot;
-    }
-    if (t == 0) totals[d] = run;
 }
 
 // Downsweep with a local reorder: each sub-tile of kItems * kNT elements is
@@ -148,8 +143,7 @@ template <int DB, int ITEMS, class SH>
 __device__ __forceinline__ void downsweep_groups(SH& S, const uint32_t* __restrict__ kin,
                                                  const uint32_t* __restrict__ vin, uint32_t* __restrict__ kout,
                                                  uint32_t* __restrict__ vout, uint32_t n, uint32_t gs, uint32_t ng,
-                                                 int shift, uint32_t MASK, const uint32_t* __restrict__ hist,
-                                                 uint32_t stride) {
+                                                 int shift, uint32_t MASK, const HistDev& H) {
     constexpr int NB = 1 << DB;
     constexpr int PER = NB / kNT > 0 ? NB / kNT : 1;      // digits per thread
     constexpr uint32_t SUB = kNT * ITEMS;
@@ -157,7 +151,34 @@ __device__ __forceinline__ void downsweep_groups(SH& S, const uint32_t* __restri
     const int w = t / kWave, l = lane_id();
     for (uint32_t g = blockIdx.x; g < ng; g += gridDim.x) {
         __syncthreads();
-        for (int d = t; d < NB; d += kNT) S.off[d] = S.start[d] + hist[(size_t)d * stride + g];
+        // elements of each digit in the groups before this one, the rows
+        // dealt to kNT / NB slices of threads when the digits are fewer
+        {
+            const uint32_t q256 = g / 256, q16 = g / 16;
+            constexpr int SL = NB < kNT ? kNT / NB : 1;
+            static_assert(SL <= kNW, "a count row per slice");
+#pragma unroll
+            for (int k = 0; k < PER; ++k) {
+                const int d = NB < kNT ? t % NB : t + k * kNT;
+                const uint32_t sl = NB < kNT ? t / NB : 0;
+                uint32_t c = 0;
+#pragma unroll 4
+                for (uint32_t r = sl; r < q256; r += SL) c += H.b256[(size_t)r * NB + d];
+#pragma unroll 4
+                for (uint32_t r = 16 * q256 + sl; r < q16; r += SL) c += H.b16[(size_t)r * NB + d];
+#pragma unroll 4
+                for (uint32_t r = 16 * q16 + sl; r < g; r += SL) c += H.group[(size_t)r * NB + d];
+                S.cnt[sl][d] = c;
+            }
+            __syncthreads();
+            for (int d = t; d < NB; d += kNT) {
+                uint32_t c = S.start[d];
+#pragma unroll
+                for (int q = 0; q < SL; ++q) c += S.cnt[q][d];
+                S.off[d] = c;
+            }
+            __syncthreads();
+        }
         const uint32_t lo = g * gs;
         const uint32_t hi = min(lo + gs, n);
         for (uint32_t base = lo; base < hi; base += SUB) {
@@ -254,12 +275,13 @@ __device__ __forceinline__ void downsweep_groups(SH& S, const uint32_t* __restri
     }
 }
 
+// (Four waves per SIMD, as many as the LDS of 8-bit digits allows: the
+// registers are capped at that.)
 template <int DB, int ITEMS>
-__global__ __launch_bounds__(kNT) void k_downsweep(const uint32_t* __restrict__ kin, const uint32_t* __restrict__ vin,
+__global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(DB <= 8 ? 4 : 2))) void k_downsweep(const uint32_t* __restrict__ kin, const uint32_t* __restrict__ vin,
                                                    uint32_t* __restrict__ kout, uint32_t* __restrict__ vout,
                                                    const uint32_t* count, uint32_t cap, int shift, uint32_t MASK,
-                                                   const uint32_t* __restrict__ hist, uint32_t stride,
-                                                   const uint32_t* __restrict__ totals) {
+                                                   HistDev H) {
     constexpr int NB = 1 << DB;
     constexpr int PER = NB / kNT > 0 ? NB / kNT : 1;      // digits per thread
     static_assert(kSortGroup % (kNT * ITEMS) == 0, "whole sub-tiles per group");
@@ -274,7 +296,11 @@ __global__ __launch_bounds__(kNT) void k_downsweep(const uint32_t* __restrict__ 
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
             const int d = t * PER + k;
-            mine[k] = d < NB ? totals[d] : 0u;
+            mine[k] = 0;
+            if (d < NB) {
+#pragma unroll 4
+                for (uint32_t r = 0; r < ceil_div(ng, 256u); ++r) mine[k] += H.b256[(size_t)r * NB + d];
+            }
             sum += mine[k];
         }
         uint32_t tot;
@@ -288,45 +314,78 @@ __global__ __launch_bounds__(kNT) void k_downsweep(const uint32_t* __restrict__ 
     }
     // small groups in one sub-tile of fewer elements per thread
     if (gs == 1024u)
-        downsweep_groups<DB, 4>(S, kin, vin, kout, vout, n, gs, ng, shift, MASK, hist, stride);
+        downsweep_groups<DB, 4>(S, kin, vin, kout, vout, n, gs, ng, shift, MASK, H);
     else if (ITEMS > 8 && gs == 2048u)
-        downsweep_groups<DB, 8>(S, kin, vin, kout, vout, n, gs, ng, shift, MASK, hist, stride);
+        downsweep_groups<DB, 8>(S, kin, vin, kout, vout, n, gs, ng, shift, MASK, H);
     else
-        downsweep_groups<DB, ITEMS>(S, kin, vin, kout, vout, n, gs, ng, shift, MASK, hist, stride);
+        downsweep_groups<DB, ITEMS>(S, kin, vin, kout, vout, n, gs, ng, shift, MASK, H);
 }
 
-// One pass over digit bits [shift, shift + nbits) (nbits <= DB).
+// Rows of bins for a sort of at most `cap` elements.
+struct BinRows {
+    uint32_t r16, r256;
+};
+BinRows bin_rows(uint32_t cap) {
+    // groups: at most kSmallGroups up to kSmallGroups * kSortGroup elements
+    const uint64_t g = std::min<uint64_t>(std::max<uint64_t>(kSmallGroups, ((uint64_t)cap + kSortGroup - 1) / kSortGroup),
+                                          (uint64_t)kSortMaxGroups);
+    return {(uint32_t)((g + 15) / 16), (uint32_t)((g + 255) / 256)};
+}
+
+// One pass over digit bits [shift, shift + nbits) (nbits <= DB), pass number
+// p of the sort.
 template <int DB>
-void pass(const SortArgs& a, int cur, int shift, int nbits, hipStream_t s) {
+void pass(const SortArgs& a, int cur, int shift, int nbits, int p, bool last, hipStream_t s) {
     const int G = kSortBlocks;
-    const uint32_t stride = a.hist_stride;
-    uint32_t* hist = a.hist;
-    uint32_t* totals = a.hist + (size_t)kSortBins * stride;
+    constexpr uint32_t NB = 1u << DB;
+    const BinRows rows = bin_rows(a.cap);
+    const size_t set = sort_bin_words(a.hist_stride) / 2;
+    uint32_t* bins = a.hist + (size_t)kSortBins * a.hist_stride;
+    HistDev H;
+    H.group = a.hist;
+    H.b16 = bins + (p & 1) * set;
+    H.b256 = H.b16 + (size_t)rows.r16 * NB;
+    const SortBins next = {bins + ((p + 1) & 1) * set, last ? 0u : (rows.r16 + rows.r256) * NB};
     const uint32_t mask = nbits >= 32 ? 0xffffffffu : ((1u << nbits) - 1u);
-    k_upsweep<DB><<<G, kNT, 0, s>>>(a.keys[cur], a.count, a.cap, shift, mask, hist, stride);
-    k_rowscan<<<1 << DB, 1024, 0, s>>>(hist, a.count, a.cap, stride, totals);
+    k_upsweep<DB><<<G, kNT, 0, s>>>(a.keys[cur], a.count, a.cap, shift, mask, H, next);
     constexpr int ITEMS = DB <= 8 ? 16 : 8;
     k_downsweep<DB, ITEMS><<<G, kNT, 0, s>>>(a.keys[cur], a.vals[cur], a.keys[cur ^ 1], a.vals[cur ^ 1], a.count,
-                                             a.cap, shift, mask, hist, stride, totals);
+                                             a.cap, shift, mask, H);
+}
+
+// Passes over key_bits bits and the digit width (at least 6) of each.
+int plan_passes(const SortArgs& a, int* digit_bits) {
+    const int maxdb = a.max_digit_bits < 6 ? 6 : (a.max_digit_bits > 11 ? 11 : a.max_digit_bits);
+    const int passes = (a.key_bits + maxdb - 1) / maxdb;
+    const int db = (a.key_bits + passes - 1) / passes;
+    *digit_bits = db;
+    return passes;
 }
 
 }  // namespace
 
+SortBins sort_bins(const SortArgs& a) {
+    int db;
+    (void)plan_passes(a, &db);
+    const BinRows rows = bin_rows(a.cap);
+    return {a.hist + (size_t)kSortBins * a.hist_stride, (rows.r16 + rows.r256) << std::max(db, 6)};
+}
+
 int launch_sort(const SortArgs& a, hipStream_t s) {
-    const int maxdb = a.max_digit_bits < 6 ? 6 : (a.max_digit_bits > 11 ? 11 : a.max_digit_bits);
-    const int passes = (a.key_bits + maxdb - 1) / maxdb;
-    const int db = (a.key_bits + passes - 1) / passes;
+    int db;
+    const int passes = plan_passes(a, &db);
     int cur = 0, shift = 0;
     for (int p = 0; p < passes; ++p) {
         // the last pass may cover fewer bits: its mask drops key bits above key_bits
         const int nbits = a.key_bits - shift < db ? a.key_bits - shift : db;
+        const bool last = p == passes - 1;
         switch (db) {
-            case 1: case 2: case 3: case 4: case 5: case 6: pass<6>(a, cur, shift, nbits, s); break;
-            case 7: pass<7>(a, cur, shift, nbits, s); break;
-            case 8: pass<8>(a, cur, shift, nbits, s); break;
-            case 9: pass<9>(a, cur, shift, nbits, s); break;
-            case 10: pass<10>(a, cur, shift, nbits, s); break;
-            default: pass<11>(a, cur, shift, nbits, s); break;
+            case 1: case 2: case 3: case 4: case 5: case 6: pass<6>(a, cur, shift, nbits, p, last, s); break;
+            case 7: pass<7>(a, cur, shift, nbits, p, last, s); break;
+            case 8: pass<8>(a, cur, shift, nbits, p, last, s); break;
+            case 9: pass<9>(a, cur, shift, nbits, p, last, s); break;
+            case 10: pass<10>(a, cur, shift, nbits, p, last, s); break;
+            default: pass<11>(a, cur, shift, nbits, p, last, s); break;
         }
         shift += db;
         cur ^= 1;
