@@ -4,24 +4,31 @@
 // opacities and SH coefficients (the optimisation behind the paper's scene
 // reconstruction, Sec. III-B).
 //
-// Compositing (one 256-thread workgroup per 16x16 tile, a pixel per thread,
-// a 16-lane quarter-wave per 4x4 block as in the forward compositor): the
-// tile's depth-ordered entries are staged in LDS in batches and listed per
-// block exactly as the forward stages and lists them.  Where each pixel
-// stopped and its final transmittance T_N come from the forward compositor
-// when the render kept them; else the pixel replays the forward recurrence
-// over its block's list with the same single-precision operations.  It then
-// walks the lists back to front, recovering T
-// before entry i as T_{i+1} / (1 - alpha_i), with
-//   dL/dalpha_i = sum_c gC_c (c_ic T_i - B_c / (1 - alpha_i))
-//               + gD (z_i T_i - B_D / (1 - alpha_i)) + gA T_N / (1 - alpha_i)
-// where B holds what lies behind entry i (T_N bg for the colour).  Through
-// alpha = o e^{-q/2} (no gradient where capped at 0.99) and q = t1^2 + t2^2,
-// t1 = p dx + r dy, t2 = s dy, each pixel yields ten numbers per entry
-// (2D mean, conic factors p r s, opacity, colour, depth); the 16 lanes of a
-// block, which walk the same entry, sum them with shuffles, blocks add them
-// in LDS, and one global atomic add per number and tile lands them in a
-// per-entry buffer.
+// Compositing (one 128-thread workgroup per 16x16 tile, two adjacent pixels
+// per thread, 8 lanes per 4x4 block): the tile's depth-ordered entries are
+// staged in LDS in batches and listed per block exactly as the forward stages
+// and lists them.  Where each pixel stopped and its final transmittance T_N
+// come from the forward compositor when the render kept them; else the pixel
+// replays the forward recurrence over its block's list with the same
+// single-precision operations.  It then walks the lists back to front,
+// recovering T before entry i as T_{i+1} / (1 - alpha_i), with
+//   dL/dalpha_i = T_i (g . c_i) - (B_i - gA T_N) / (1 - alpha_i)
+// where g . c_i = sum_c gC_c c_ic + gD z_i and B_i = sum of g . c_j alpha_j
+// T_j over the entries behind i plus T_N gC . bg: one number per pixel holds
+// what lies behind.  Through alpha = o e^{-q/2} (no gradient where capped at
+// 0.99) and q = t1^2 + t2^2, t1 = p dx + r dy, t2 = s dy, with h = alpha
+// dL/dalpha, each pixel yields ten numbers per entry: h, h t1, h t1 dx,
+// h t1 dy, h t2, h t2 dy and the four of colour and depth, from which the
+// projection's backward forms the gradients of the 2D mean, the conic factors
+// and the opacity.  The 8 lanes of a block, which walk the same entry, sum
+// them (ten_sums), the blocks add them in LDS, and a tile adds its entries'
+// sums to the per-entry buffer with consecutive lanes on consecutive words.
+//
+// What bounds it: vector issue, about 100 instructions per two pixels and
+// entry, and before that the atomics: with one pixel per thread, ten full row
+// sums per block and entry and ten scattered global atomics per tile and
+// entry, four 640 x 480 views of a 700,000-leaf plan took 650 us here;
+// BWD_FIGURES.
 //
 // Projection (FP64): the cut entries are sorted by Gaussian (the radix sort
 // of the binning); one thread per entry in that order takes the chain rule
@@ -40,52 +47,49 @@ namespace hgs {
 
 namespace {
 
-constexpr int kNT = kTilePx;
 constexpr int kB = 128;                         // entries staged per batch
-constexpr int kNG = 10;                         // per-entry gradient numbers
+constexpr int kNT = kTilePx / 2;                // two pixels per thread
+constexpr int kNW = kNT / kWave;
+constexpr int kLanes = 8;                       // threads per block
+constexpr int kNG = 10;                         // per-entry numbers
+static_assert(kB <= kNT && kNG <= kEntryGrad, "an entry per staging thread");
+
+// Staged records as the forward compositor's: factors scaled by kS, nlo =
+// -log2(opacity).
+struct alignas(16) BwdA { float p, r, c1, s; };
+// The mean (u, v) is relative to the tile.
+struct alignas(16) BwdB { float c2, nlo, u, v; };
+struct alignas(16) BwdC { float col0, col1, col2, z; };
 
 struct BwdShared {
-    StageA a[kB + 1];
-    StageB b[kB + 1];
-    StageC c[kB + 1];
-    float2 uv[kB];                              // tile-relative 2D means
-    float io[kB];                               // inverse opacities
+    BwdA a[kB + 1];
+    BwdB b[kB + 1];
+    BwdC c[kB + 1];
+    float acc[(kB + 1) * kEntryGrad];
     uint32_t entry[kB];
-    float acc[kNG][kB];
     alignas(16) uint16_t idx[kBlocks * kB];
-    uint32_t wc[(kNT / kWave) * kBlocks];
+    uint32_t wc[kNW * kBlocks];
     uint32_t n[kBlocks];
     uint32_t maxlast;
 };
 
-// Q of a staged entry at pixel centre (fx, fy) by the compositor's own
-// operations (its factors scaled by kS as the compositor stages them,
-// -log2(o) folded into the row term), so that alpha and the stop decisions
-// here are the forward pass's bit for bit.
-__device__ __forceinline__ float compositor_q(const StageA& A, const StageB& B, float fx, float fy) {
-    const float t1 = fmaf(kS * A.p, fx, fmaf(kS * A.r, fy, kS * A.c1));
-    const float t2 = fmaf(kS * A.s, fy, kS * B.c2);
-    return fmaf(t1, t1, fmaf(t2, t2, -B.lo));
-}
-
 // Stage entries [base, base + cnt) of the tile's list and build each 4x4
 // block's list of staged offsets (16 B units, depth order), padded with the
-// empty record up to a multiple of four of its wave's longest list.
-// Returns this lane's block list length and writes the padded length.
+// empty record up to a multiple of four of its wave's longest list, whose
+// padded length is returned.
 __device__ __forceinline__ uint32_t stage_lists(const BwdArgs& a, BwdShared& S, uint32_t base, uint32_t cnt,
-                                                double dx0, double dy0, int w, int lane, int gid, int k,
-                                                uint32_t* n_step_out) {
+                                                double dx0, double dy0, int w, int lane, int blk, int k) {
     uint32_t m = 0;
     const int j = threadIdx.x;
     if (j < (int)cnt) {
         const uint32_t e = a.vals[base + j];
         const Proj P = a.proj[e < a.cut_cap ? e : 0u];
+        const float nlo = -__log2f(P.opacity);
         const float u = (float)(P.u - dx0), v = (float)(P.v - dy0);
-        S.a[j] = StageA{P.p, P.r, -fmaf(P.p, u, P.r * v), P.s};
-        S.b[j] = StageB{-P.s * v, __log2f(P.opacity), P.z, P.c0};
-        S.c[j] = StageC{P.c1, P.c2};
-        S.uv[j] = make_float2(u, v);
-        S.io[j] = 1.f / P.opacity;
+        const float c1 = -fmaf(P.p, u, P.r * v), c2 = -P.s * v;
+        S.a[j] = BwdA{kS * P.p, kS * P.r, kS * c1, kS * P.s};
+        S.b[j] = BwdB{kS * c2, nlo, u, v};
+        S.c[j] = BwdC{P.c0, P.c1, P.c2, P.z};
         S.entry[j] = e;
         m = block_mask(u, v, P.p, P.r, P.s);
     }
@@ -100,7 +104,7 @@ __device__ __forceinline__ uint32_t stage_lists(const BwdArgs& a, BwdShared& S, 
     if (threadIdx.x < kBlocks) {
         uint32_t t = 0;
 #pragma unroll
-        for (int ww = 0; ww < kNT / kWave; ++ww) {
+        for (int ww = 0; ww < kNW; ++ww) {
             const uint32_t c = S.wc[ww * kBlocks + threadIdx.x];
             S.wc[ww * kBlocks + threadIdx.x] = t;
             t += c;
@@ -111,39 +115,56 @@ __device__ __forceinline__ uint32_t stage_lists(const BwdArgs& a, BwdShared& S, 
 #pragma unroll
     for (int b = 0; b < kBlocks; ++b)
         if ((m >> b) & 1u) S.idx[b * kB + S.wc[w * kBlocks + b] + pre[b]] = (uint16_t)(j * 16);
-    const uint32_t n_mine = S.n[gid];
-    const uint32_t n_wave = __builtin_amdgcn_readfirstlane(
-        max(max(S.n[w * 4], S.n[w * 4 + 1]), max(S.n[w * 4 + 2], S.n[w * 4 + 3])));
+    uint32_t n_wave = 0;
+#pragma unroll
+    for (int b = 0; b < kBlocks / kNW; ++b) n_wave = max(n_wave, S.n[w * (kBlocks / kNW) + b]);
+    n_wave = __builtin_amdgcn_readfirstlane(n_wave);
     const uint32_t n_step = (n_wave + 3u) & ~3u;
-    uint16_t* list = S.idx + gid * kB;
-    for (uint32_t p = n_mine + (uint32_t)k; p < n_step; p += 16) list[p] = (uint16_t)(kB * 16);
+    uint16_t* list = S.idx + blk * kB;
+    for (uint32_t p = S.n[blk] + (uint32_t)k; p < n_step; p += kLanes) list[p] = (uint16_t)(kB * 16);
     __syncthreads();
-    *n_step_out = n_step;
-    return n_mine;
+    return n_step;
 }
 
-// Sum over the 16 lanes of a DPP row, left in every lane of the row: lane
-// pairs (quad_perm 1,0,3,2), quad pairs (2,3,0,1), then the mirrored half
-// row and the mirrored row.
 template <int CTRL>
 __device__ __forceinline__ float dpp_f(float x) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, false));
 }
 
-__device__ __forceinline__ float group_sum(float x) {
-    x += dpp_f<0xb1>(x);      // quad_perm [1, 0, 3, 2]
-    x += dpp_f<0x4e>(x);      // quad_perm [2, 3, 0, 1]
-    x += dpp_f<0x141>(x);     // row_half_mirror
-    x += dpp_f<0x140>(x);     // row_mirror
-    return x;
+// Sums of ten values over 8 consecutive lanes, spread over lanes 0-3 of the
+// eight: lane k gets those of values k and 4 + k in *s0 and *s1, lanes 0 and
+// 1 those of values 8 and 9 in *s2.  Each exchange keeps one of two values
+// and sends the other, so the work halves from step to step: 25 instructions
+// where ten separate sums take 30 and ten adds to LDS after them.
+__device__ __forceinline__ void ten_sums(const float (&v)[kNG], bool odd1, bool odd2, float* s0, float* s1, float* s2) {
+    float r[5];
+#pragma unroll
+    for (int i = 0; i < 5; ++i) {
+        const float keep = odd1 ? v[2 * i + 1] : v[2 * i], send = odd1 ? v[2 * i] : v[2 * i + 1];
+        r[i] = keep + dpp_f<0xb1>(send);                  // quad_perm [1, 0, 3, 2]
+    }
+    float q[3];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const float keep = odd2 ? r[2 * i + 1] : r[2 * i], send = odd2 ? r[2 * i] : r[2 * i + 1];
+        q[i] = keep + dpp_f<0x4e>(send);                  // quad_perm [2, 3, 0, 1]
+    }
+    q[2] = r[4] + dpp_f<0x4e>(r[4]);
+    *s0 = q[0] + dpp_f<0x104>(q[0]);                      // row_shl:4
+    *s1 = q[1] + dpp_f<0x104>(q[1]);
+    *s2 = q[2] + dpp_f<0x104>(q[2]);
 }
 
-// Batches of 128 entries and a register budget of eight waves per SIMD: the
-// reverse walk is a chain of row reductions and LDS adds whose latency only
-// more resident waves hide.
-__global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8))) void k_composite_bwd(BwdArgs a) {
+// Batches of 128 entries and a register budget of six waves per SIMD: the
+// reverse walk is a chain of LDS reads, exponentials and LDS adds whose
+// latency only more resident waves hide.
+template <bool KEPT>
+__global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(6))) void k_composite_bwd(BwdArgs a) {
     __shared__ BwdShared S;
     const uint32_t tile = blockIdx.x;
+    const uint2 rg = a.ranges[tile];
+    const uint32_t n = rg.y - rg.x;
+    if (n == 0) return;                             // nothing drawn: no gradient
     const uint32_t view = a.tile_view[tile];
     const ViewDev& V = a.views[view];
     const ImgGrad G = a.dimg[view];
@@ -151,153 +172,168 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8))) void k
     const int tx = (int)(local % (uint32_t)V.tiles_x), ty = (int)(local / (uint32_t)V.tiles_x);
     const int x0 = tx * kTile, y0 = ty * kTile;
     const int w = threadIdx.x / kWave, lane = lane_id();
-    const int g = lane >> 4, k = lane & 15;
-    const int gid = w * 4 + g;
-    const int lx = g * 4 + (k & 3), ly = w * 4 + (k >> 2);
-    const int px = x0 + lx, py = y0 + ly;
-    const bool inside = px < V.width && py < V.height;
-    const float fx = (float)lx + 0.5f, fy = (float)ly + 0.5f;
+    const int k = lane % kLanes, blk = w * (kBlocks / kNW) + lane / kLanes;
+    const int lx0 = (blk % 4) * 4 + (k % 2) * 2, ly = (blk / 4) * 4 + k / 2;
+    const int py = y0 + ly;
+    const float fy = (float)ly + 0.5f;
     const double dx0 = (double)x0, dy0 = (double)y0;
-    const uint2 rg = a.ranges[tile];
-    const uint32_t n = rg.y - rg.x;
+    float fx[2], Tc[2];
+    bool inside[2];
+    uint32_t last[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        fx[q] = (float)(lx0 + q) + 0.5f;
+        inside[q] = x0 + lx0 + q < V.width && py < V.height;
+        Tc[q] = 1.f;
+        last[q] = n;
+    }
     if (threadIdx.x == 0) {
-        S.a[kB] = StageA{0.f, 0.f, 0.f, 0.f};
-        S.b[kB] = StageB{0.f, -__builtin_inff(), 0.f, 0.f};
-        S.c[kB] = StageC{0.f, 0.f};
+        S.a[kB] = BwdA{0.f, 0.f, 0.f, 0.f};
+        S.b[kB] = BwdB{0.f, __builtin_inff(), 0.f, 0.f};    // Q = inf: above any bound
+        S.c[kB] = BwdC{0.f, 0.f, 0.f, 0.f};
         S.maxlast = 0;
     }
+    const char* ra = reinterpret_cast<const char*>(S.a);
+    const char* rb = reinterpret_cast<const char*>(S.b);
+    const char* rc = reinterpret_cast<const char*>(S.c);
+    const uint2* list4 = reinterpret_cast<const uint2*>(S.idx + blk * kB);
 
-    // 1. where the pixel stopped and its final transmittance: kept by the
+    // 1. where the pixels stopped and their final transmittance: kept by the
     // forward compositor, else a forward replay over the block lists (the
     // forward's operations)
-    float T = 1.f;
-    bool live = inside;
-    uint32_t last = n;
-    if (a.state) {
-        const uint2 st = a.state[(size_t)tile * kNT + threadIdx.x];
-        last = st.x;
-        T = __uint_as_float(st.y);
-        __syncthreads();                            // S.maxlast is set
-    }
-    for (uint32_t b0 = 0; !a.state && b0 < n; b0 += kB) {
-        const uint32_t cnt = min((uint32_t)kB, n - b0);
-        uint32_t n_step;
-        stage_lists(a, S, rg.x + b0, cnt, dx0, dy0, w, lane, gid, k, &n_step);
-        const uint16_t* list = S.idx + gid * kB;
-        for (uint32_t p = 0; p < n_step; ++p) {
-            const uint32_t off = list[p];
-            const StageA A = *reinterpret_cast<const StageA*>(reinterpret_cast<const char*>(S.a) + off);
-            const StageB B = *reinterpret_cast<const StageB*>(reinterpret_cast<const char*>(S.b) + off);
-            const float Q = compositor_q(A, B, fx, fy);
-            const float al = fminf(0.99f, __builtin_amdgcn_exp2f(-Q));
-            const float Tn = T - al * T;
-            const bool add = live && Q <= entry_qmax(-B.lo);
-            if (add && Tn < 1e-4f) {
-                live = false;
-                last = b0 + off / 16;
-            }
-            T = add && live ? Tn : T;
-            if ((p & 3u) == 3u && __ballot(live) == 0) break;
+    if constexpr (KEPT) {
+        // (the forward's thread of a pixel: blocks of 16 pixels, row-major)
+        const uint2* st = a.state + (size_t)tile * kTilePx + blk * 16 + (k / 2) * 4 + (k % 2) * 2;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const uint2 x = st[q];
+            last[q] = x.x;
+            Tc[q] = __uint_as_float(x.y);
         }
-        if (__syncthreads_count(live ? 1 : 0) == 0) break;
+        __syncthreads();                            // S.maxlast is set
+    } else {
+        bool live[2] = {inside[0], inside[1]};
+        for (uint32_t b0 = 0; b0 < n; b0 += kB) {
+            const uint32_t n_step = stage_lists(a, S, rg.x + b0, min((uint32_t)kB, n - b0), dx0, dy0, w, lane, blk, k);
+            for (uint32_t i = 0; i < n_step; i += 4) {
+                const uint2 q4 = list4[i >> 2];
+                const uint32_t id4[4] = {q4.x & 0xffffu, q4.x >> 16, q4.y & 0xffffu, q4.y >> 16};
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const BwdA A = *reinterpret_cast<const BwdA*>(ra + id4[u]);
+                    const BwdB B = *reinterpret_cast<const BwdB*>(rb + id4[u]);
+                    const float ry = fmaf(A.r, fy, A.c1), t2 = fmaf(A.s, fy, B.c2), t22 = fmaf(t2, t2, B.nlo);
+#pragma unroll
+                    for (int q = 0; q < 2; ++q) {
+                        const float t1 = fmaf(A.p, fx[q], ry);
+                        const float Q = fmaf(t1, t1, t22);
+                        const float al = fminf(0.99f, __builtin_amdgcn_exp2f(-Q));
+                        const float Tn = Tc[q] - al * Tc[q];
+                        const bool add = live[q] && Q <= entry_qmax(B.nlo);
+                        if (add && Tn < 1e-4f) {
+                            live[q] = false;
+                            last[q] = b0 + id4[u] / 16;
+                        }
+                        Tc[q] = add && live[q] ? Tn : Tc[q];
+                    }
+                }
+                if (__ballot(live[0] || live[1]) == 0) break;
+            }
+            if (__syncthreads_count(live[0] || live[1] ? 1 : 0) == 0) break;
+        }
     }
-    if (!inside) last = 0;
-    atomicMax(&S.maxlast, last);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) last[q] = inside[q] ? last[q] : 0u;
+    atomicMax(&S.maxlast, max(last[0], last[1]));
 
     // 2. back to front over the same lists
     const size_t plane = (size_t)V.width * V.height;
-    const size_t pix = (size_t)py * V.width + px;
-    float gC0 = 0.f, gC1 = 0.f, gC2 = 0.f, gD = 0.f, gA = 0.f;
-    if (inside) {
-        gC0 = G.rgb ? G.rgb[pix] : 0.f;
-        gC1 = G.rgb ? G.rgb[plane + pix] : 0.f;
-        gC2 = G.rgb ? G.rgb[2 * plane + pix] : 0.f;
-        gD = G.depth ? G.depth[pix] : 0.f;
-        gA = G.alpha ? G.alpha[pix] : 0.f;
+    float gC0[2], gC1[2], gC2[2], gD[2], behind[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const size_t pix = (size_t)py * V.width + (x0 + lx0 + q);
+        const bool in = inside[q];
+        gC0[q] = in && G.rgb ? G.rgb[pix] : 0.f;
+        gC1[q] = in && G.rgb ? G.rgb[plane + pix] : 0.f;
+        gC2[q] = in && G.rgb ? G.rgb[2 * plane + pix] : 0.f;
+        gD[q] = in && G.depth ? G.depth[pix] : 0.f;
+        const float gA = in && G.alpha ? G.alpha[pix] : 0.f;
+        behind[q] = Tc[q] * (gC0[q] * V.bg[0] + gC1[q] * V.bg[1] + gC2[q] * V.bg[2] - gA);
     }
-    const float TN = T;
-    float Tc = T;
-    float B0 = T * V.bg[0], B1 = T * V.bg[1], B2 = T * V.bg[2], BD = 0.f;
-    for (int i = threadIdx.x; i < kNG * kB; i += kNT) (&S.acc[0][0])[i] = 0.f;
+    for (int i = threadIdx.x; i < kB * kEntryGrad; i += kNT) S.acc[i] = 0.f;
     __syncthreads();
     const uint32_t maxlast = S.maxlast;
-    const int nb = (int)((maxlast + kB - 1) / kB);
-    for (int bi = nb - 1; bi >= 0; --bi) {
+    const bool odd1 = k & 1, odd2 = k & 2;
+    for (int bi = (int)((maxlast + kB - 1) / kB) - 1; bi >= 0; --bi) {
         const uint32_t b0 = (uint32_t)bi * kB;
         const uint32_t cnt = min((uint32_t)kB, n - b0);
-        uint32_t n_step;
-        stage_lists(a, S, rg.x + b0, cnt, dx0, dy0, w, lane, gid, k, &n_step);
-        const uint16_t* list = S.idx + gid * kB;
-        for (int p = (int)n_step - 1; p >= 0; --p) {
-            const uint32_t off = list[p];
-            const uint32_t j = off / 16;
-            float gr[kNG];
+        const uint32_t n_step = stage_lists(a, S, rg.x + b0, cnt, dx0, dy0, w, lane, blk, k);
+        // offsets below lim are entries before the pixel's stop
+        uint32_t lim[2];
 #pragma unroll
-            for (int t = 0; t < kNG; ++t) gr[t] = 0.f;
-            bool has = false;
-            if (j < kB && b0 + j < last) {
-                const StageA A = S.a[j];
-                const StageB B = S.b[j];
-                const StageC C = S.c[j];
-                const float t1 = fmaf(A.p, fx, fmaf(A.r, fy, A.c1));
-                const float t2 = fmaf(A.s, fy, B.c2);
-                const float Q = compositor_q(A, B, fx, fy);
-                const float al0 = fminf(0.99f, __builtin_amdgcn_exp2f(-Q));
-                const float al = Q <= entry_qmax(-B.lo) ? al0 : 0.f;
-                if (al > 0.f) {
-                    has = true;
+        for (int q = 0; q < 2; ++q) lim[q] = last[q] > b0 ? min(last[q] - b0, (uint32_t)kB) * 16u : 0u;
+        for (int i = (int)n_step - 4; i >= 0; i -= 4) {
+            const uint2 q4 = list4[i >> 2];
+            const uint32_t id4[4] = {q4.x & 0xffffu, q4.x >> 16, q4.y & 0xffffu, q4.y >> 16};
+#pragma unroll
+            for (int u = 3; u >= 0; --u) {
+                const uint32_t off = id4[u];
+                const BwdA A = *reinterpret_cast<const BwdA*>(ra + off);
+                const BwdB B = *reinterpret_cast<const BwdB*>(rb + off);
+                const BwdC C = *reinterpret_cast<const BwdC*>(rc + off);
+                const float qmax = entry_qmax(B.nlo);
+                const float ry = fmaf(A.r, fy, A.c1), t2 = fmaf(A.s, fy, B.c2), t22 = fmaf(t2, t2, B.nlo);
+                float v[kNG];
+#pragma unroll
+                for (int t = 0; t < kNG; ++t) v[t] = 0.f;
+                bool has = false;
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const float t1 = fmaf(A.p, fx[q], ry);
+                    const float Q = fmaf(t1, t1, t22);
+                    const float al0 = fminf(0.99f, __builtin_amdgcn_exp2f(-Q));
+                    const bool on = Q <= qmax && off < lim[q];
+                    has = has || on;
+                    const float al = on ? al0 : 0.f;
                     const float iom = __builtin_amdgcn_rcpf(1.f - al);
-                    const float Ti = Tc * iom;
-                    const float c0 = B.col0, c1 = C.col1, c2 = C.col2, z = B.z;
+                    const float Ti = Tc[q] * iom;
                     const float wgt = al * Ti;
-                    const float dLda = gC0 * (c0 * Ti - B0 * iom) + gC1 * (c1 * Ti - B1 * iom) +
-                                       gC2 * (c2 * Ti - B2 * iom) + gD * (z * Ti - BD * iom) + gA * TN * iom;
-                    gr[6] = gC0 * wgt;
-                    gr[7] = gC1 * wgt;
-                    gr[8] = gC2 * wgt;
-                    gr[9] = gD * wgt;
-                    B0 = fmaf(c0, wgt, B0);
-                    B1 = fmaf(c1, wgt, B1);
-                    B2 = fmaf(c2, wgt, B2);
-                    BD = fmaf(z, wgt, BD);
-                    Tc = Ti;
-                    if (al0 < 0.99f) {
-                        const float gq = -0.5f * al * dLda;
-                        const float2 uv = S.uv[j];
-                        const float dx = fx - uv.x, dy = fy - uv.y;
-                        gr[0] = gq * (-2.f * t1 * A.p);
-                        gr[1] = gq * (-2.f * (t1 * A.r + t2 * A.s));
-                        gr[2] = gq * (2.f * t1 * dx);
-                        gr[3] = gq * (2.f * t1 * dy);
-                        gr[4] = gq * (2.f * t2 * dy);
-                        gr[5] = dLda * al * S.io[j];
-                    }
+                    const float gc = fmaf(gC0[q], C.col0, fmaf(gC1[q], C.col1, fmaf(gC2[q], C.col2, gD[q] * C.z)));
+                    const float dLda = fmaf(Ti, gc, -iom * behind[q]);
+                    behind[q] = fmaf(wgt, gc, behind[q]);
+                    Tc[q] = on ? Ti : Tc[q];
+                    const float h = al0 < 0.99f ? al * dLda : 0.f;
+                    const float s1 = h * t1;
+                    v[0] += h;
+                    v[1] += s1;
+                    v[2] = fmaf(s1, fx[q] - B.u, v[2]);
+                    v[6] = fmaf(gC0[q], wgt, v[6]);
+                    v[7] = fmaf(gC1[q], wgt, v[7]);
+                    v[8] = fmaf(gC2[q], wgt, v[8]);
+                    v[9] = fmaf(gD[q], wgt, v[9]);
                 }
-            }
-            // the 16 lanes of a block share the entry: sum them when any
-            // contributes (a block-uniform branch)
-            const uint32_t gbits = (uint32_t)(__ballot(has) >> (16 * g)) & 0xffffu;
-            if (gbits) {
-#pragma unroll
-                for (int t = 0; t < kNG; ++t) {
-                    const float sum = group_sum(gr[t]);
-                    if (k == 0 && sum != 0.f) atomicAdd(&S.acc[t][j], sum);
+                if (__ballot(has) == 0) continue;
+                const float dy = fy - B.v;                  // shared by the thread's pixels, as t2
+                v[3] = v[1] * dy;
+                v[4] = v[0] * t2;
+                v[5] = v[4] * dy;
+                float s0, s1, s2;
+                ten_sums(v, odd1, odd2, &s0, &s1, &s2);
+                float* acc = S.acc + off / 16 * kEntryGrad;
+                if (k < 4) {
+                    if (s0 != 0.f) atomicAdd(acc + k, s0);
+                    if (s1 != 0.f) atomicAdd(acc + 4 + k, s1);
+                    if (k < 2 && s2 != 0.f) atomicAdd(acc + 8 + k, s2);
                 }
             }
         }
         __syncthreads();
-        const int jj = threadIdx.x;
-        if (jj < (int)cnt) {
-            const uint32_t e = S.entry[jj];
-            if (e < a.cut_cap) {
-                float* dst = a.egrad + (size_t)e * kEntryGrad;
-#pragma unroll
-                for (int t = 0; t < kNG; ++t) {
-                    const float x = S.acc[t][jj];
-                    if (x != 0.f) atomicAdd(dst + t, x);
-                    S.acc[t][jj] = 0.f;
-                }
-            }
+        // the tile's sums: twelve consecutive words per entry
+        for (uint32_t i = threadIdx.x; i < cnt * kEntryGrad; i += kNT) {
+            const float x = S.acc[i];
+            const uint32_t e = S.entry[i / kEntryGrad];
+            if (x != 0.f && e < a.cut_cap) atomicAdd(a.egrad + (size_t)e * kEntryGrad + i % kEntryGrad, x);
+            S.acc[i] = 0.f;
         }
         __syncthreads();
     }
@@ -405,9 +441,16 @@ __global__ __launch_bounds__(256) void k_project_bwd(ProjBwdArgs a) {
         if (!(det > 0.0)) continue;
         // conic factors p = sqrt(s11 / det), r = -s01 / sqrt(det s11),
         // s = 1 / sqrt(s11) and their derivatives
-        const double gp = gin[2], gr = gin[3], gs = gin[4];
         const double pp = sqrt(s11 / det), idet2 = 1.0 / (det * det);
         const double mm = det * s11, im12 = 1.0 / sqrt(mm), im32 = im12 / mm;
+        // the entry's sums h, h t1, h t1 dx, h t1 dy, h t2, h t2 dy (t1 and t2
+        // scaled by kS) to the gradients of the 2D mean and the factors:
+        // dL/dq = -h / 2
+        const double iks = 1.0 / (double)kS;
+        const double st1 = gin[1] * iks, st2 = gin[4] * iks;
+        const double rf = -s01 * im12, sf = 1.0 / sqrt(s11);
+        const double gu = pp * st1, gv = rf * st1 + sf * st2;
+        const double gp = -gin[2] * iks, gr = -gin[3] * iks, gs = -gin[5] * iks;
         const double h00 = gp * (0.5 / pp) * (-s11 * s11 * idet2) + gr * 0.5 * s01 * im32 * s11 * s11;
         const double h01 = gp * (0.5 / pp) * (2.0 * s11 * s01 * idet2) + gr * (-im12 - s01 * s01 * s11 * im32);
         const double h11 = gp * (0.5 / pp) * (-s01 * s01 * idet2) + gr * 0.5 * s01 * im32 * (det + s00 * s11) +
@@ -440,7 +483,6 @@ __global__ __launch_bounds__(256) void k_project_bwd(ProjBwdArgs a) {
                                  2.0 * qz * gR[1][1] + qy * gR[1][2] + qx * gR[2][0] + qy * gR[2][1]);
         const double qd = qw * gw + qx * gx + qy * gy + qz * gz;
         // camera-space mean: 2D mean, depth, Jacobian
-        const double gu = gin[0], gv = gin[1];
         double gt0 = gu * V.fx * iz, gt1 = gv * V.fy * iz;
         double gt2 = -(gu * V.fx * tx + gv * V.fy * ty) * iz * iz + gin[9];
         const double iz2 = iz * iz;
@@ -493,7 +535,7 @@ __global__ __launch_bounds__(256) void k_project_bwd(ProjBwdArgs a) {
         float4* rec = reinterpret_cast<float4*>(a.rec + (size_t)p * kEntryRec);
         rec[0] = make_float4((float)gmu[0], (float)gmu[1], (float)gmu[2], (float)gsc[0]);
         rec[1] = make_float4((float)gsc[1], (float)gsc[2], (float)((gw - qw * qd) / qn), (float)((gx - qx * qd) / qn));
-        rec[2] = make_float4((float)((gy - qy * qd) / qn), (float)((gz - qz * qd) / qn), (float)gin[5], (float)gcm[0]);
+        rec[2] = make_float4((float)((gy - qy * qd) / qn), (float)((gz - qz * qd) / qn), (float)(gin[0] / (double)g0.w), (float)gcm[0]);
         rec[3] = make_float4((float)gcm[1], (float)gcm[2], (float)ux, (float)uy);
         rec[4] = make_float4((float)uz, 0.f, 0.f, 0.f);
     }
@@ -565,7 +607,11 @@ __global__ void k_entry_keys(const uint2* cut, const Counters* ctr, uint32_t cap
 
 void launch_backward_composite(const BwdArgs& b, const Counters* ctr, hipStream_t s) {
     k_zero_egrad<<<1024, 256, 0, s>>>(b.egrad, ctr, b.cut_cap);
-    if (b.total_tiles) k_composite_bwd<<<b.total_tiles, kNT, 0, s>>>(b);
+    if (!b.total_tiles) return;
+    if (b.state)
+        k_composite_bwd<true><<<b.total_tiles, kNT, 0, s>>>(b);
+    else
+        k_composite_bwd<false><<<b.total_tiles, kNT, 0, s>>>(b);
 }
 
 void launch_backward_params(ProjBwdArgs p, SortArgs sa, GatherArgs ga, hipStream_t s) {

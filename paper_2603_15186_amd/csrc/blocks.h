@@ -1,5 +1,5 @@
-// Shared by the compositor and its backward pass: the staged per-entry
-// record and the 4x4 pixel blocks of a 16x16 tile an entry's 3-sigma
+// Shared by the compositor and its backward pass: the bound on an entry's
+// exponent and the 4x4 pixel blocks of a 16x16 tile an entry's 3-sigma
 // ellipse may reach.
 #pragma once
 
@@ -26,12 +26,6 @@ constexpr float kQCap = 7.99435343685885793f;           // -log2(1/255)
 
 // The bound on Q of an entry with nlo = -log2(opacity).
 __device__ __forceinline__ float entry_qmax(float nlo) { return fminf(kQCap, fmaf(kQMax, kS2, nlo)); }
-
-// One staged Gaussian: t1 = p x + r y + c1, t2 = s y + c2 over tile-relative
-// pixel centres (x, y); lo = log2(opacity).
-struct alignas(16) StageA { float p, r, c1, s; };
-struct alignas(16) StageB { float c2, lo, z, col0; };
-struct alignas(16) StageC { float col1, col2; };
 
 // Blocks of a TW x TH tile (TW, TH in {8, 16, 32} x {8, 16}) that may hold
 // a pixel centre with q <= kQMask, numbered cell-major: a cell is the tile's

@@ -371,7 +371,9 @@ struct DiscArgs {
 void launch_disc_collision(const DiscArgs& d, hipStream_t s);
 
 // backward pass (backward.hip)
-constexpr int kEntryGrad = 12;       // floats per cut entry: u, v, p, r, s, opacity, rgb, depth, 2 spare
+// floats per cut entry: sums over its pixels of h = alpha dL/dalpha, h t1,
+// h t1 dx, h t1 dy, h t2, h t2 dy, the colour's and depth's gradients; 2 spare
+constexpr int kEntryGrad = 12;
 struct ImgGrad {
     const float* rgb;                // [3][h][w] or null
     const float* depth;              // [h][w] or null
