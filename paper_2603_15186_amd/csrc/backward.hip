@@ -28,7 +28,7 @@
 // entry, and before that the atomics: with one pixel per thread, ten full row
 // sums per block and entry and ten scattered global atomics per tile and
 // entry, four 640 x 480 views of a 700,000-leaf plan took 650 us here;
-// BWD_FIGURES.
+// 444 this way.
 //
 // Projection (FP64): the cut entries are sorted by Gaussian (the radix sort
 // of the binning); one thread per entry in that order takes the chain rule
