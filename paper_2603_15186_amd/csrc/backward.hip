@@ -73,17 +73,31 @@ struct BwdShared {
     uint32_t maxlast;
 };
 
-// Stage entries [base, base + cnt) of the tile's list and build each 4x4
+// This thread's entry of a batch, on its way from memory: loaded while the
+// batch before it is walked, since a tile's time is its batches' and a batch
+// starts with two dependent gathers.
+struct Fetched {
+    uint32_t e;
+    Proj P;
+};
+__device__ __forceinline__ void fetch(const BwdArgs& a, uint32_t base, uint32_t cnt, Fetched* f) {
+    if (threadIdx.x < cnt) {
+        f->e = a.vals[base + threadIdx.x];
+        f->P = a.proj[f->e < a.cut_cap ? f->e : 0u];
+    }
+}
+
+// Stage a batch of cnt entries (f: this thread's) and build each 4x4
 // block's list of staged offsets (16 B units, depth order), padded with the
 // empty record up to a multiple of four of its wave's longest list, whose
 // padded length is returned.
-__device__ __forceinline__ uint32_t stage_lists(const BwdArgs& a, BwdShared& S, uint32_t base, uint32_t cnt,
-                                                double dx0, double dy0, int w, int lane, int blk, int k) {
+__device__ __forceinline__ uint32_t stage_lists(const Fetched& f, BwdShared& S, uint32_t cnt, double dx0, double dy0,
+                                                int w, int lane, int blk, int k) {
     uint32_t m = 0;
     const int j = threadIdx.x;
     if (j < (int)cnt) {
-        const uint32_t e = a.vals[base + j];
-        const Proj P = a.proj[e < a.cut_cap ? e : 0u];
+        const uint32_t e = f.e;
+        const Proj& P = f.P;
         const float nlo = -__log2f(P.opacity);
         const float u = (float)(P.u - dx0), v = (float)(P.v - dy0);
         const float c1 = -fmaf(P.p, u, P.r * v), c2 = -P.s * v;
@@ -213,8 +227,11 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(6))) void k
         __syncthreads();                            // S.maxlast is set
     } else {
         bool live[2] = {inside[0], inside[1]};
+        Fetched f;
+        fetch(a, rg.x, min((uint32_t)kB, n), &f);
         for (uint32_t b0 = 0; b0 < n; b0 += kB) {
-            const uint32_t n_step = stage_lists(a, S, rg.x + b0, min((uint32_t)kB, n - b0), dx0, dy0, w, lane, blk, k);
+            const uint32_t n_step = stage_lists(f, S, min((uint32_t)kB, n - b0), dx0, dy0, w, lane, blk, k);
+            if (b0 + kB < n) fetch(a, rg.x + b0 + kB, min((uint32_t)kB, n - b0 - kB), &f);
             for (uint32_t i = 0; i < n_step; i += 4) {
                 const uint2 q4 = list4[i >> 2];
                 const uint32_t id4[4] = {q4.x & 0xffffu, q4.x >> 16, q4.y & 0xffffu, q4.y >> 16};
@@ -264,10 +281,14 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(6))) void k
     __syncthreads();
     const uint32_t maxlast = S.maxlast;
     const bool odd1 = k & 1, odd2 = k & 2;
-    for (int bi = (int)((maxlast + kB - 1) / kB) - 1; bi >= 0; --bi) {
+    const int nb = (int)((maxlast + kB - 1) / kB);
+    Fetched f;
+    if (nb > 0) fetch(a, rg.x + (nb - 1) * kB, min((uint32_t)kB, n - (nb - 1) * kB), &f);
+    for (int bi = nb - 1; bi >= 0; --bi) {
         const uint32_t b0 = (uint32_t)bi * kB;
         const uint32_t cnt = min((uint32_t)kB, n - b0);
-        const uint32_t n_step = stage_lists(a, S, rg.x + b0, cnt, dx0, dy0, w, lane, blk, k);
+        const uint32_t n_step = stage_lists(f, S, cnt, dx0, dy0, w, lane, blk, k);
+        if (bi > 0) fetch(a, rg.x + b0 - kB, kB, &f);
         // offsets below lim are entries before the pixel's stop
         uint32_t lim[2];
 #pragma unroll
@@ -275,12 +296,22 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(6))) void k
         for (int i = (int)n_step - 4; i >= 0; i -= 4) {
             const uint2 q4 = list4[i >> 2];
             const uint32_t id4[4] = {q4.x & 0xffffu, q4.x >> 16, q4.y & 0xffffu, q4.y >> 16};
+            // the four records together, ahead of the sums' LDS adds
+            BwdA A4[4];
+            BwdB B4[4];
+            BwdC C4[4];
+#pragma unroll
+            for (int u = 3; u >= 0; --u) {
+                A4[u] = *reinterpret_cast<const BwdA*>(ra + id4[u]);
+                B4[u] = *reinterpret_cast<const BwdB*>(rb + id4[u]);
+                C4[u] = *reinterpret_cast<const BwdC*>(rc + id4[u]);
+            }
 #pragma unroll
             for (int u = 3; u >= 0; --u) {
                 const uint32_t off = id4[u];
-                const BwdA A = *reinterpret_cast<const BwdA*>(ra + off);
-                const BwdB B = *reinterpret_cast<const BwdB*>(rb + off);
-                const BwdC C = *reinterpret_cast<const BwdC*>(rc + off);
+                const BwdA A = A4[u];
+                const BwdB B = B4[u];
+                const BwdC C = C4[u];
                 const float qmax = entry_qmax(B.nlo);
                 const float ry = fmaf(A.r, fy, A.c1), t2 = fmaf(A.s, fy, B.c2), t22 = fmaf(t2, t2, B.nlo);
                 float v[kNG];
