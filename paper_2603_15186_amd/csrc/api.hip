@@ -495,7 +495,7 @@ void enqueue_pass(hgs_ctx* c, hipStream_t s, int g) {
     pa.sh_degree = c->sh_degree;
     pa.views = ca.views;
     pa.n_views = ca.n_views;
-    pa.lds_views = ca.group_children && ca.n_views <= kProjectLdsViews;
+    pa.lds_views = ca.group_children;
     pa.proj = P<Proj>(W.proj);
     pa.depth_key = P<uint32_t>(W.dkey[0]);
     // Binned depths lie in (znear, distance to the farthest corner of the
@@ -540,9 +540,10 @@ void enqueue_pass(hgs_ctx* c, hipStream_t s, int g) {
     pa.tile_w = c->ropts.tile_w;
     pa.tile_h = c->ropts.tile_h;
     pa.key_shift = key_shift;
-    // When the view fits above the depth bits, one sort on (view, depth)
-    // gives the view-grouped depth order; otherwise a stable pass on the
-    // entries' views (read from the cut) follows the depth sort.
+    // One sort on (view, depth) gives the view-grouped depth order: the view
+    // in the key where it fits above the depth bits, else added to it by the
+    // sort's first pass, which makes room, from the cut; where even that does
+    // not fit, a stable pass on the entries' views follows the depth sort.
     const int view_bits = ca.n_views > 1 ? bits_for((uint32_t)ca.n_views) : 0;
     const bool view_in_key = ca.n_views > 1 && depth_bits + view_bits <= 32;
     pa.view_shift = view_in_key ? depth_bits : 0;
@@ -559,6 +560,15 @@ void enqueue_pass(hgs_ctx* c, hipStream_t s, int g) {
     sa.key_bits = view_in_key ? depth_bits + view_bits : depth_bits;
     sa.max_digit_bits = c->sort_digit_bits;
     sa.hist = P<uint32_t>(W.hist);
+    bool view_pass = false;
+    if (ca.n_views > 1 && !view_in_key) {
+        SortArgs wide = sa;
+        wide.top = ca.cut;
+        wide.low_bits = depth_bits;
+        wide.key_bits = depth_bits + view_bits;
+        if (wide_sort_fits(wide)) sa = wide;
+        else view_pass = true;
+    }
     if (!lists) pa.clear = sort_bins(sa);
     launch_project(pa, s);
     mark(c, 2, s);
@@ -607,7 +617,7 @@ void enqueue_pass(hgs_ctx* c, hipStream_t s, int g) {
         ta.ctr = ctr;
         launch_emit_tiles(ea, ta, s);
     } else {
-        pr = bin_sorted(c, W, pa, ea, xa, ctr, sa, ca.n_views > 1 && !view_in_key, s);
+        pr = bin_sorted(c, W, pa, ea, xa, ctr, sa, view_pass, s);
     }
     xa.vals = P<uint32_t>(W.pval[pr]);
     c->last_pair_buf = pr;

@@ -125,12 +125,16 @@ __device__ __forceinline__ uint4 counts_of(const LevelCtx& c, uint32_t d, int nc
 // work is negligible, so the group is not compacted).  The network keeps a
 // candidate (emits it) unless its probability reaches p*.
 //
-// With node-grouped frontiers, the pass's views are staged in LDS when
-// there are at most kLdsViews: a wave's entries span several views (a
-// node's views are next to each other), and LDS serves a lane's own view
-// without a gather.  Staged are the leading words through the side-plane
-// normals and keep_node, all that the node test and the features read.
-constexpr int kLdsViews = 64;
+// With node-grouped frontiers, views are staged in LDS: a wave's entries span
+// several views (a node's views are next to each other), and LDS serves a
+// lane's own view without a gather.  A window of kLdsViews views holds them
+// all in most passes; with more, it starts at the view group of the step's
+// first entry and moves with the frontier, whose groups follow one another
+// (the entries of a step that lie outside it read their view from memory).
+// Without the window the leaf level of a 96-view batch took 648 us, with it 290.
+// Staged are the leading words through the side-plane normals and keep_node,
+// all that the node test and the features read.
+constexpr uint32_t kLdsViews = 2 * kCutViewGroup;
 constexpr int kCutViewWords = (int)((offsetof(ViewDev, nb) + sizeof(double)) / 8);
 static_assert(offsetof(ViewDev, o) == 0 && offsetof(ViewDev, nb) % 8 == 0, "views start with their FP64 words");
 
@@ -142,52 +146,59 @@ struct CountShared {
     int32_t keep[kLdsViews];
 };
 
-// (view-major frontiers keep a wave on one view: scalar loads serve it)
-__device__ __forceinline__ bool use_lds_views(const LevelCtx& c) { return c.group && c.n_views <= kLdsViews; }
-
+// The window of views from v0 on (view-major frontiers keep a wave on one
+// view: scalar loads serve it).
 template <bool DEFER, int NT>
-__device__ __forceinline__ void stage_count(const LevelCtx& c, CountShared<DEFER, NT>& S) {
-    if (DEFER)
-        for (int k = threadIdx.x; k < kMlpParams; k += NT) S.w[k] = c.w32[k];
-    if (use_lds_views(c)) {
-        const uint64_t* src = reinterpret_cast<const uint64_t*>(c.views);
-        for (int k = threadIdx.x; k < c.n_views * kCutViewWords; k += NT) {
-            const int v = k / kCutViewWords, q = k - v * kCutViewWords;
+__device__ __forceinline__ void stage_views(const LevelCtx& c, CountShared<DEFER, NT>& S, uint32_t v0) {
+    if (c.group) {
+        const uint32_t n = min((uint32_t)c.n_views - v0, kLdsViews);
+        const uint64_t* src = reinterpret_cast<const uint64_t*>(c.views + v0);
+        for (uint32_t k = threadIdx.x; k < n * kCutViewWords; k += NT) {
+            const uint32_t v = k / kCutViewWords, q = k - v * kCutViewWords;
             S.view[k] = src[(size_t)v * (sizeof(ViewDev) / 8) + q];
         }
-        for (int v = threadIdx.x; v < c.n_views; v += NT) S.keep[v] = c.views[v].keep_node;
+        for (uint32_t v = threadIdx.x; v < n; v += NT) S.keep[v] = c.views[v0 + v].keep_node;
     }
     __syncthreads();
 }
 
-// f applied to view v (the staged words; the others, which neither the node
-// test nor the features read, stay zero).
+template <bool DEFER, int NT>
+__device__ __forceinline__ void stage_weights(const LevelCtx& c, CountShared<DEFER, NT>& S) {
+    if (DEFER)
+        for (int k = threadIdx.x; k < kMlpParams; k += NT) S.w[k] = c.w32[k];
+}
+
+// f applied to view v, the staged window starting at v0 (the staged words;
+// the others, which neither the node test nor the features read, stay zero).
 template <bool DEFER, int NT, class F>
-__device__ __forceinline__ auto with_view(const LevelCtx& c, const CountShared<DEFER, NT>& S, uint32_t v, F&& f) {
-    if (use_lds_views(c)) {
+__device__ __forceinline__ auto with_view(const LevelCtx& c, const CountShared<DEFER, NT>& S, uint32_t v0, uint32_t v,
+                                          F&& f) {
+    if (c.group && v - v0 < kLdsViews) {
+        const uint32_t at = v - v0;
         uint64_t wd[sizeof(ViewDev) / 8];
 #pragma unroll
         for (int q = 0; q < (int)(sizeof(ViewDev) / 8); ++q)
-            wd[q] = q < kCutViewWords ? S.view[v * kCutViewWords + q] : 0ull;
+            wd[q] = q < kCutViewWords ? S.view[at * kCutViewWords + q] : 0ull;
         ViewDev V;
         __builtin_memcpy(&V, wd, sizeof V);
-        V.keep_node = S.keep[v];
+        V.keep_node = S.keep[at];
         return f(V);
     }
     return on_view(c.views, v, f);
 }
 
 template <bool DEFER, int NT>
-__device__ __forceinline__ uint32_t decide(const LevelCtx& c, const CountShared<DEFER, NT>& S, bool valid, uint2 e,
-                                           float4 b, int nchild) {
+__device__ __forceinline__ uint32_t decide(const LevelCtx& c, const CountShared<DEFER, NT>& S, uint32_t v0, bool valid,
+                                           uint2 e, float4 b, int nchild) {
     if (!valid) return kDrop;
-    return with_view(c, S, e.y, [&](const ViewDev& V) { return node_decision(V, (int)e.x, b, nchild, c.s_hi); });
+    return with_view(c, S, v0, e.y, [&](const ViewDev& V) { return node_decision(V, (int)e.x, b, nchild, c.s_hi); });
 }
 
 // The network's say on the candidates among one entry per thread (every
 // thread of the workgroup takes part).
 template <int NT>
-__device__ __forceinline__ uint32_t settle(const LevelCtx& c, CountShared<true, NT>& S, uint32_t d, uint2 e, float4 b) {
+__device__ __forceinline__ uint32_t settle(const LevelCtx& c, CountShared<true, NT>& S, uint32_t v0, uint32_t d, uint2 e,
+                                           float4 b) {
     const bool cand = (d & kCandidate) != 0;
     if (!__syncthreads_or(cand)) return d;         // also orders S.x's reuse and publishes S.w
     const LodMlpDev& m = *(const LodMlpDev*)c.mlp;
@@ -195,7 +206,7 @@ __device__ __forceinline__ uint32_t settle(const LevelCtx& c, CountShared<true, 
 #pragma unroll
     for (int k = 0; k < kMlpIn; ++k) f[k] = 0.f;
     if (cand) {
-        with_view(c, S, e.y, [&](const ViewDev& V) {
+        with_view(c, S, v0, e.y, [&](const ViewDev& V) {
             NodeGeom g;
             node_geometry(V, b, &g);
             lod_features(m, V, (int)e.x, b, g, c.level, f);
@@ -210,8 +221,8 @@ __device__ __forceinline__ uint32_t settle(const LevelCtx& c, CountShared<true, 
     return (cand && !(1.f / (1.f + __expf(-z)) >= m.p_star)) ? (uint32_t)kEmit : d;
 }
 
-// Decide entries [lo, hi), the staged views and weights in S; returns this
-// thread's share of the counts.
+// Decide entries [lo, hi), the weights staged in S; returns this thread's
+// share of the counts.
 template <bool DEFER>
 __device__ __forceinline__ uint4 count_chunk(const LevelCtx& c, uint32_t lo, uint32_t hi, CountShared<DEFER, kNT>& S) {
     uint4 acc = make_uint4(0, 0, 0, 0);
@@ -224,7 +235,14 @@ __device__ __forceinline__ uint4 count_chunk(const LevelCtx& c, uint32_t lo, uin
         acc.z += r.z;
     };
     // two entries per lane and step: their gathers are in flight together
+    uint32_t win = ~0u;                            // first staged view
     for (uint32_t s = lo; s < hi; s += 2 * kNT) {
+        const uint32_t v0w = c.n_views <= (int)kLdsViews ? 0u : c.in[s].y / kCutViewGroup * kCutViewGroup;
+        if (v0w != win) {
+            if (win != ~0u) __syncthreads();
+            stage_views(c, S, v0w);
+            win = v0w;
+        }
         const uint32_t i0 = s + threadIdx.x, i1 = i0 + kNT;
         const bool v0 = i0 < hi, v1 = i1 < hi;
         const uint2 e0 = v0 ? c.in[i0] : make_uint2(0, 0);
@@ -232,11 +250,11 @@ __device__ __forceinline__ uint4 count_chunk(const LevelCtx& c, uint32_t lo, uin
         const float4 b0 = c.bound[e0.x], b1 = c.bound[e1.x];
         const int2 ch0 = c.leaves ? make_int2(0, 0) : c.child[e0.x];
         const int2 ch1 = c.leaves ? make_int2(0, 0) : c.child[e1.x];
-        uint32_t d0 = decide(c, S, v0, e0, b0, ch0.y);
-        uint32_t d1 = decide(c, S, v1, e1, b1, ch1.y);
+        uint32_t d0 = decide(c, S, win, v0, e0, b0, ch0.y);
+        uint32_t d1 = decide(c, S, win, v1, e1, b1, ch1.y);
         if constexpr (DEFER) {
-            d0 = settle(c, S, d0, e0, b0);
-            d1 = settle(c, S, d1, e1, b1);
+            d0 = settle(c, S, win, d0, e0, b0);
+            d1 = settle(c, S, win, d1, e1, b1);
         }
         count(i0, v0, d0, ch0);
         count(i1, v1, d1, ch1);
@@ -257,7 +275,7 @@ __global__ __launch_bounds__(kNT) void k_level_count(LevelCtx c) {
     uint32_t lo, hi;
     chunk_of(n, gridDim.x, blockIdx.x, &lo, &hi);
     if (lo >= hi) return;                          // no block at or after this one is read
-    stage_count(c, S);
+    stage_weights(c, S);
     const uint4 acc = wave_sum3(count_chunk<DEFER>(c, lo, hi, S));
     if (lane_id() == 0) s_tot[threadIdx.x / kWave] = acc;
     __syncthreads();
@@ -322,12 +340,6 @@ __device__ __forceinline__ uint4 finish_level(const LevelCtx& c, uint32_t n_in, 
 // the second and later views.  Each view's entries keep their order.
 constexpr int kEmitPer = 4;
 constexpr uint32_t kEmitStage = 4096;
-// Views are grouped kCutViewGroup at a time; within a group the frontier
-// is node-major (a node's views next to each other).  Larger groups share
-// more of a node's reads between views; smaller ones keep fewer views in a
-// wave (32 measured best on 50-view batches, between 16 and 64).
-constexpr uint32_t kCutViewGroup = 32;
-
 __global__ __launch_bounds__(kNT) void k_level_emit(LevelCtx c) {
     __shared__ uint4 sh[kNT / kWave + 1];
     __shared__ uint4 s_off[2];
@@ -535,7 +547,8 @@ __global__ __launch_bounds__(kTopEntries) void k_cut_top(LevelCtx c, uint2* out,
     for (int i = t; i < n_clear; i += NT) clear[i] = make_uint4(0, 0, 0, 0);
     for (uint32_t i = t; i < c.n_zero; i += NT) c.zero[i] = 0;
     if (t == 0) start_counters(c.ctr, total, c.in_cap);
-    stage_count(c, S);                             // (also orders the roots' entries)
+    stage_weights(c, S);
+    stage_views(c, S, 0);                          // (also orders the roots' entries)
     for (int L = 0; L < levels; ++L) {
         c.level = L;
         const bool leaves = L == n_levels - 1, last = L == levels - 1;
@@ -544,8 +557,8 @@ __global__ __launch_bounds__(kTopEntries) void k_cut_top(LevelCtx c, uint2* out,
         const uint2 prev = valid && t > 0 ? s_f[L & 1][t - 1] : make_uint2(~0u, ~0u);
         const float4 b = c.bound[e.x];
         const int2 ch = leaves ? make_int2(0, 0) : c.child[e.x];
-        uint32_t d = decide(c, S, valid, e, b, ch.y);
-        if constexpr (DEFER) d = settle(c, S, d, e, b);
+        uint32_t d = decide(c, S, 0u, valid, e, b, ch.y);
+        if constexpr (DEFER) d = settle(c, S, 0u, d, e, b);
         uint4 r = counts_of(c, d, ch.y);
         // a group starts where the node or the view group changes; ungrouped,
         // every entry is one

@@ -17,6 +17,11 @@ namespace hgs {
 constexpr int kTile = 16;                 // default tile edge in pixels (the backward pass's tile)
 constexpr int kTilePx = kTile * kTile;    // pixels per default tile
 constexpr int kMaxViews = 4096;
+// Views are grouped kCutViewGroup at a time; within a group a node-grouped
+// frontier is node-major (a node's views next to each other).  Larger groups
+// share more of a node's reads between views; smaller ones keep fewer views
+// in a wave (32 measured best on 50-view batches, between 16 and 64).
+constexpr uint32_t kCutViewGroup = 32;
 // Cut entries are addressed by 28-bit indices: the depth-sorted values
 // carry the entry index in the low 28 bits and min(tile count, 15) in the
 // top 4, so the pair-count scan reads tile counts in depth order without
@@ -223,6 +228,10 @@ struct SortArgs {
     uint32_t cap;
     int key_bits;
     int max_digit_bits = 11;         // 6..11
+    // non-null: the keys hold the low low_bits of the key_bits, value e & kEntryMask
+    // has top[e].y above them (wide_sort_fits)
+    const uint2* top = nullptr;
+    int low_bits = 0;
     uint32_t* hist;                  // sort_hist_bytes(hist_stride) bytes
     uint32_t hist_stride = kSortMaxGroups;   // at least the sort's group count
 };
@@ -233,6 +242,9 @@ struct SortBins {
     uint32_t n;
 };
 SortBins sort_bins(const SortArgs& a);
+// Whether a sort on key_bits bits of which top supplies those above low_bits
+// can hold what is left of a key after its first pass in 32 bits.
+bool wide_sort_fits(const SortArgs& a);
 int launch_sort(const SortArgs& a, hipStream_t s);
 
 struct ProjectArgs {
@@ -262,8 +274,8 @@ struct ProjectArgs {
     const int2* child;
     int tile_w, tile_h;              // tile shape in pixels
     int key_shift;                   // pair sort keys: view << key_shift | tile within the view
-    // the pass's views staged in LDS (at most kProjectLdsViews; for
-    // node-grouped cuts, whose waves span several views)
+    // views staged in LDS, kProjectLdsViews at a time (for node-grouped
+    // cuts, whose waves span several views)
     bool lds_views;
     int n_views;
     // per-tile lists: entries of every tile of the pass, zero before (null: off)
@@ -272,7 +284,7 @@ struct ProjectArgs {
     uint4* scan_tmp;                 // the cut's scratch: counts of binned entries
     SortBins clear;                  // bins of the depth sort
 };
-constexpr int kProjectLdsViews = 64;
+constexpr uint32_t kProjectLdsViews = 2 * kCutViewGroup;
 constexpr uint32_t kTileListMax = 8192;   // tiles of a pass that per-tile lists serve (their counts fit in LDS)
 void launch_project(const ProjectArgs& a, hipStream_t s);
 

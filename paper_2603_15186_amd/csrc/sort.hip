@@ -122,6 +122,24 @@ __global__ __launch_bounds__(kNT) void k_upsweep(const uint32_t* __restrict__ ke
     }
 }
 
+// Keys of more than 32 bits, the ones above `low` in the cut: the first pass
+// (digit bits [0, digit)) drops the bits it has sorted by and sets those of
+// the value's entry above what is left.  (The values are still almost in
+// entry order, so these reads hit: 38 M entries of 96 views add 130 us to the
+// pass.  A pass of its own on the entries' views, gathered in depth order,
+// cost 717 us for the gather; the digits are the same in number.)
+struct TopBits {
+    const uint2* src;
+    int low, digit;
+    __device__ __forceinline__ uint32_t at(uint32_t val, uint32_t n) const {
+        const uint32_t e = val & kEntryMask;
+        return e < n ? src[e].y : 0u;
+    }
+    __device__ __forceinline__ uint32_t key(uint32_t k, uint32_t t) const {
+        return ((low < 32 ? k & ((1u << low) - 1u) : k) >> digit) | t << (low - digit);
+    }
+};
+
 // Downsweep with a local reorder: each sub-tile of kItems * kNT elements is
 // ranked (stable within the sub-tile), placed in LDS in digit order, then
 // written out in that order so that consecutive lanes store consecutive
@@ -139,11 +157,11 @@ struct DownShared {
 };
 
 // The groups of this workgroup in sub-tiles of ITEMS elements per thread.
-template <int DB, int ITEMS, class SH>
+template <int DB, int ITEMS, bool TOP, class SH>
 __device__ __forceinline__ void downsweep_groups(SH& S, const uint32_t* __restrict__ kin,
                                                  const uint32_t* __restrict__ vin, uint32_t* __restrict__ kout,
                                                  uint32_t* __restrict__ vout, uint32_t n, uint32_t gs, uint32_t ng,
-                                                 int shift, uint32_t MASK, const HistDev& H) {
+                                                 int shift, uint32_t MASK, const HistDev& H, const TopBits& top) {
     constexpr int NB = 1 << DB;
     constexpr int PER = NB / kNT > 0 ? NB / kNT : 1;      // digits per thread
     constexpr uint32_t SUB = kNT * ITEMS;
@@ -256,11 +274,22 @@ __device__ __forceinline__ void downsweep_groups(SH& S, const uint32_t* __restri
             }
             __syncthreads();
             const uint32_t n_sub = (hi - base) < SUB ? (hi - base) : SUB;
-            for (uint32_t p = t; p < n_sub; p += kNT) {
+            uint32_t over[TOP ? ITEMS : 1];       // (loaded together)
+            if constexpr (TOP) {
+#pragma unroll
+                for (int r = 0; r < ITEMS; ++r) {
+                    const uint32_t p = t + r * kNT;
+                    over[r] = p < n_sub ? top.at(S.val[p], n) : 0u;
+                }
+            }
+#pragma unroll (TOP ? ITEMS : 1)
+            for (int r = 0; r < ITEMS; ++r) {
+                const uint32_t p = t + r * kNT;
+                if (p >= n_sub) break;
                 const uint32_t k = S.key[p];
                 const uint32_t d = (k >> shift) & MASK;
                 const uint32_t pos = S.off[d] + (p - S.loc[d]);
-                kout[pos] = k;
+                kout[pos] = TOP ? top.key(k, over[TOP ? r : 0]) : k;
                 vout[pos] = S.val[p];
             }
             if (base + SUB >= hi) break;
@@ -277,11 +306,11 @@ __device__ __forceinline__ void downsweep_groups(SH& S, const uint32_t* __restri
 
 // (Four waves per SIMD, as many as the LDS of 8-bit digits allows: the
 // registers are capped at that.)
-template <int DB, int ITEMS>
+template <int DB, int ITEMS, bool TOP>
 __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(DB <= 8 ? 4 : 2))) void k_downsweep(const uint32_t* __restrict__ kin, const uint32_t* __restrict__ vin,
                                                    uint32_t* __restrict__ kout, uint32_t* __restrict__ vout,
                                                    const uint32_t* count, uint32_t cap, int shift, uint32_t MASK,
-                                                   HistDev H) {
+                                                   HistDev H, TopBits top) {
     constexpr int NB = 1 << DB;
     constexpr int PER = NB / kNT > 0 ? NB / kNT : 1;      // digits per thread
     static_assert(kSortGroup % (kNT * ITEMS) == 0, "whole sub-tiles per group");
@@ -314,11 +343,11 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(DB <= 8 ? 4
     }
     // small groups in one sub-tile of fewer elements per thread
     if (gs == 1024u)
-        downsweep_groups<DB, 4>(S, kin, vin, kout, vout, n, gs, ng, shift, MASK, H);
+        downsweep_groups<DB, 4, TOP>(S, kin, vin, kout, vout, n, gs, ng, shift, MASK, H, top);
     else if (ITEMS > 8 && gs == 2048u)
-        downsweep_groups<DB, 8>(S, kin, vin, kout, vout, n, gs, ng, shift, MASK, H);
+        downsweep_groups<DB, 8, TOP>(S, kin, vin, kout, vout, n, gs, ng, shift, MASK, H, top);
     else
-        downsweep_groups<DB, ITEMS>(S, kin, vin, kout, vout, n, gs, ng, shift, MASK, H);
+        downsweep_groups<DB, ITEMS, TOP>(S, kin, vin, kout, vout, n, gs, ng, shift, MASK, H, top);
 }
 
 // Rows of bins for a sort of at most `cap` elements.
@@ -349,8 +378,9 @@ void pass(const SortArgs& a, int cur, int shift, int nbits, int p, bool last, hi
     const uint32_t mask = nbits >= 32 ? 0xffffffffu : ((1u << nbits) - 1u);
     k_upsweep<DB><<<G, kNT, 0, s>>>(a.keys[cur], a.count, a.cap, shift, mask, H, next);
     constexpr int ITEMS = DB <= 8 ? 16 : 8;
-    k_downsweep<DB, ITEMS><<<G, kNT, 0, s>>>(a.keys[cur], a.vals[cur], a.keys[cur ^ 1], a.vals[cur ^ 1], a.count,
-                                             a.cap, shift, mask, H);
+    auto down = p == 0 && a.top ? k_downsweep<DB, ITEMS, true> : k_downsweep<DB, ITEMS, false>;
+    down<<<G, kNT, 0, s>>>(a.keys[cur], a.vals[cur], a.keys[cur ^ 1], a.vals[cur ^ 1], a.count, a.cap, shift, mask, H,
+                           TopBits{a.top, a.low_bits, nbits});
 }
 
 // Passes over key_bits bits and the digit width (at least 6) of each.
@@ -371,13 +401,18 @@ SortBins sort_bins(const SortArgs& a) {
     return {a.hist + (size_t)kSortBins * a.hist_stride, (rows.r16 + rows.r256) << std::max(db, 6)};
 }
 
+bool wide_sort_fits(const SortArgs& a) {
+    int db;
+    return plan_passes(a, &db) > 1 && db < a.low_bits && a.key_bits - db <= 32;
+}
+
 int launch_sort(const SortArgs& a, hipStream_t s) {
     int db;
     const int passes = plan_passes(a, &db);
     int cur = 0, shift = 0;
     for (int p = 0; p < passes; ++p) {
         // the last pass may cover fewer bits: its mask drops key bits above key_bits
-        const int nbits = a.key_bits - shift < db ? a.key_bits - shift : db;
+        const int nbits = std::min(a.key_bits - p * db, db);
         const bool last = p == passes - 1;
         switch (db) {
             case 1: case 2: case 3: case 4: case 5: case 6: pass<6>(a, cur, shift, nbits, p, last, s); break;
@@ -387,7 +422,7 @@ int launch_sort(const SortArgs& a, hipStream_t s) {
             case 10: pass<10>(a, cur, shift, nbits, p, last, s); break;
             default: pass<11>(a, cur, shift, nbits, p, last, s); break;
         }
-        shift += db;
+        if (p > 0 || !a.top) shift += db;              // (top: the first pass drops its digit)
         cur ^= 1;
     }
     return cur;
