@@ -42,6 +42,21 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t x) {
     return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(x), kWave - 1);
 }
 
+// 1 / x and 1 / sqrt(x) in FP64 for positive normal x: the hardware's
+// estimates (23 bits or more) and one step of Householder's third-order
+// iteration, whose error is the cube of the estimate's; the last roundings
+// remain: 0.50 ulp for 1 / x, 0.97 for 1 / sqrt(x) (the two IEEE operations:
+// 1.44).  The IEEE sequences, which also serve every other x, are 12 to 20
+// instructions, these 4 and 6.
+__device__ __forceinline__ double rcp64(double x) {
+    const double y = __builtin_amdgcn_rcp(x), e = fma(-x, y, 1.0);
+    return fma(y, fma(e, e, e), y);
+}
+__device__ __forceinline__ double rsqrt64(double x) {
+    const double y = __builtin_amdgcn_rsq(x), e = fma(-(x * y), y, 1.0);
+    return fma(y * e, fma(0.375, e, 0.5), y);
+}
+
 // Exclusive scan over a block of NT threads; returns the thread's exclusive
 // prefix and writes the block total to *total.  `sh` holds NT/64 + 1 words.
 template <int NT>
