@@ -2009,7 +2009,12 @@ hgs_status check_grid(hgs_ctx* c, int32_t nx, int32_t ny) {
 }
 
 constexpr int kNavBatch = 32;          // relaxation rounds between convergence checks (settled rounds return at once)
-constexpr int64_t kNavMaxRounds = 1 << 22;
+// A round lasts as long as its longest wave, so in the first rounds a tile
+// leaves after one sweep phase each way (25 -> 17 us a round on a 400 x 300
+// floor, three rounds more); maps that need more rounds than these wind
+// through their tiles, and settle each tile in turn.
+constexpr int64_t kNavShort = 4 * kNavBatch;
+constexpr int64_t kNavMaxRounds = (1 << 22) + kNavShort;
 
 }  // namespace
 
@@ -2040,7 +2045,7 @@ hgs_status hgs_distance_fields(hgs_ctx* c, void* stream, const uint8_t* nav, int
     const int tx = (nx + T - 1) / T, ty = (ny + T - 1) / T;
     const size_t tiles = (size_t)tx * ty;
     hgs_status s;
-    if ((s = ensure(c, c->nav_goals, (size_t)n_goals * 4)) || (s = ensure(c, c->nav_flags, 2 * tiles * n_goals)) ||
+    if ((s = ensure(c, c->nav_goals, (size_t)n_goals * 4)) || (s = ensure(c, c->nav_flags, 2 * tiles * n_goals + (size_t)nx * ny)) ||
         (s = ensure(c, c->nav_active, kNavBatch * 4)))
         return s;
     if (!c->nav_active_host)
@@ -2057,13 +2062,14 @@ hgs_status hgs_distance_fields(hgs_ctx* c, void* stream, const uint8_t* nav, int
     d.dist = dist;
     d.flags[0] = P<uint8_t>(c->nav_flags);
     d.flags[1] = P<uint8_t>(c->nav_flags) + tiles * n_goals;
+    d.moves = P<uint8_t>(c->nav_flags) + 2 * tiles * n_goals;
     d.active = P<uint32_t>(c->nav_active);
     launch_dist_init(d, st);
     HIP_TRY(c, hipGetLastError());
     // rounds in batches; a round in which no tile changed is a fixed point
     int64_t done = -1;
     for (int64_t r0 = 0; r0 < kNavMaxRounds && done < 0; r0 += kNavBatch) {
-        launch_dist_rounds(d, (int)(r0 & 1), kNavBatch, st);
+        launch_dist_rounds(d, (int)(r0 & 1), kNavBatch, r0 < kNavShort ? 2 : INT32_MAX, st);
         HIP_TRY(c, hipGetLastError());
         HIP_TRY(c, hipMemcpyAsync(c->nav_active_host, c->nav_active.p, kNavBatch * 4, hipMemcpyDeviceToHost, st));
         HIP_TRY(c, hipStreamSynchronize(st));

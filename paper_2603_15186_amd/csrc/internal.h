@@ -446,6 +446,7 @@ struct DistArgs {
     int n_goals;
     const int32_t* goals;            // device [n_goals] cell indices
     uint64_t* dist;                  // [n_goals][ny][nx]: a | b << 32, ~0 unreached
+    uint8_t* moves;                  // scratch [ny][nx]: legal moves of every cell
     uint8_t* flags[2];               // [n_goals][tiles]: tile changed in the last round
     uint32_t* active;                // per round of a batch: tiles that changed
 };
@@ -466,7 +467,8 @@ struct TraceArgs {
 int dist_tile();
 void launch_navigable(const NavArgs& a, hipStream_t s);
 void launch_dist_init(const DistArgs& d, hipStream_t s);
-void launch_dist_rounds(const DistArgs& d, int round0, int n_rounds, hipStream_t s);
+// n_rounds rounds; a tile that changed stops after `phases` sweep phases.
+void launch_dist_rounds(const DistArgs& d, int round0, int n_rounds, int phases, hipStream_t s);
 void launch_trace(const TraceArgs& a, hipStream_t s);
 
 // learned-LOD network (mlp.hip)

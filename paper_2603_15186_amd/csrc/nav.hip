@@ -73,6 +73,24 @@ __global__ __launch_bounds__(kNT) void k_dist_init(DistArgs d) {
     const int64_t N = (int64_t)d.nx * d.ny;
     const int64_t tiles = (int64_t)d.tiles_x * d.tiles_y;
     const int64_t total = N * d.n_goals;
+    // bit m of a cell's moves: move m of E, W, S, N, SE, SW, NE, NW leads to a
+    // navigable cell (diagonals between navigable side cells)
+    for (int64_t c = blockIdx.x * (int64_t)kNT + threadIdx.x; c < N; c += (int64_t)gridDim.x * kNT) {
+        const int i = (int)(c % d.nx), j = (int)(c / d.nx);
+        uint32_t m = 0;
+        if (d.nav[c]) {
+            auto nav = [&](int u, int v) {
+                return u >= 0 && v >= 0 && u < d.nx && v < d.ny && d.nav[(size_t)v * d.nx + u] != 0;
+            };
+            const bool e = nav(i + 1, j), w = nav(i - 1, j), so = nav(i, j + 1), no = nav(i, j - 1);
+            m = (e ? 1u : 0u) | (w ? 2u : 0u) | (so ? 4u : 0u) | (no ? 8u : 0u);
+            if (e && so && nav(i + 1, j + 1)) m |= 16u;
+            if (w && so && nav(i - 1, j + 1)) m |= 32u;
+            if (e && no && nav(i + 1, j - 1)) m |= 64u;
+            if (w && no && nav(i - 1, j - 1)) m |= 128u;
+        }
+        d.moves[c] = (uint8_t)m;
+    }
     for (int64_t k = blockIdx.x * (int64_t)kNT + threadIdx.x; k < total; k += (int64_t)gridDim.x * kNT) {
         const int64_t g = k / N, c = k % N;
         const int32_t goal = d.goals[g];
@@ -102,6 +120,67 @@ __device__ __forceinline__ double pair_cost(uint64_t p) {
     return fma((double)(uint32_t)(p >> 32), kSqrt2, (double)(uint32_t)p);
 }
 
+// What the relaxation keeps of a cell: its pair (PairCost), or on grids of at
+// most kFixedCells cells its cost as the whole number 2^29 a + R b with R =
+// 759,250,125, the integer nearest 2^29 sqrt 2 (FixedCost).  The numbers order
+// like the costs: with e = R / 2^29 - sqrt 2 (|e| < 1.1154e-11), pairs that
+// differ by (da, db) differ in cost by da + db sqrt 2 and in number by 2^29
+// (da + db sqrt 2 + db e).  Both have one sign where |da + db sqrt 2| > |db e|:
+// clear where da and db have one sign or the costs differ by 1 or more;
+// otherwise |da| < sqrt 2 |db| + 1, so that |da + db sqrt 2| >= |da^2 - 2 db^2| /
+// (2 sqrt 2 |db| + 1) >= 1 / (2 sqrt 2 |db| + 1), which exceeds |db e| for
+// |db| < 178,000, and |db| < (|da| + 1) / sqrt 2 with |da| at most the moves
+// of a path: fewer than cells.  They stay below 2^48, where FP64 sums of
+// whole numbers are exact, and R is odd, so a number gives back its pair (R b
+// modulo 2^29 determines b).  A relaxation is then three additions and three
+// minima, an illegal one adding NaN, which a minimum passes over.
+struct PairCost {
+    typedef uint64_t T;
+    static __device__ __forceinline__ T unreached() { return kUnreached; }
+    static __device__ __forceinline__ T of(uint64_t pair) { return pair; }
+    static __device__ __forceinline__ uint64_t pair(T v) { return v; }
+    static __device__ __forceinline__ T from_bits(uint64_t b) { return b; }
+    static __device__ __forceinline__ uint64_t bits(T v) { return v; }
+    static __device__ __forceinline__ T relax(T cur, uint32_t m, T v0, int b0, T v1, int b1, T v2, int b2);
+};
+
+constexpr int64_t kFixedCells = 250000;
+struct FixedCost {
+    typedef double T;
+    static constexpr uint32_t kR = 759250125u, kMask = (1u << 29) - 1u;
+    static constexpr uint32_t inverse() {              // of kR modulo 2^29 (Newton's iteration)
+        uint32_t x = kR;
+        for (int k = 0; k < 5; ++k) x *= 2u - kR * x;
+        return x & kMask;
+    }
+    static __device__ __forceinline__ T unreached() { return __builtin_huge_val(); }
+    static __device__ __forceinline__ T of(uint64_t p) {
+        return p == kUnreached ? unreached()
+                               : fma((double)(uint32_t)(p >> 32), (double)kR, (double)(uint32_t)p * 536870912.0);
+    }
+    static __device__ __forceinline__ uint64_t pair(T v) {
+        if (!(v < 281474976710656.0)) return kUnreached;           // 2^48
+        const uint64_t k = (uint64_t)__double_as_longlong(v + 4503599627370496.0) & 0xfffffffffffffull;
+        const uint32_t b = ((uint32_t)k * inverse()) & kMask;
+        return (uint64_t)b << 32 | (k - (uint64_t)b * kR) >> 29;
+    }
+    static __device__ __forceinline__ T from_bits(uint64_t b) { return __longlong_as_double((long long)b); }
+    static __device__ __forceinline__ uint64_t bits(T v) { return (uint64_t)__double_as_longlong(v); }
+    static __device__ __forceinline__ T relax(T cur, uint32_t m, T v0, int b0, T v1, int b1, T v2, int b2) {
+        // (legal: the move's number, else a NaN that keeps its low half)
+        constexpr uint64_t diag = __builtin_bit_cast(uint64_t, (double)kR);
+        constexpr uint32_t kNan = 0x7ff80000u;
+        const uint32_t h0 = (m >> b0) & 1u ? 0x41c00000u : kNan;   // 2^29
+        const uint32_t h1 = (m >> b1) & 1u ? (uint32_t)(diag >> 32) : kNan;
+        const uint32_t h2 = (m >> b2) & 1u ? (uint32_t)(diag >> 32) : kNan;
+        const double c0 = v0 + from_bits((uint64_t)h0 << 32);
+        const double c1 = v1 + from_bits((uint64_t)h1 << 32 | (uint32_t)diag);
+        const double c2 = v2 + from_bits((uint64_t)h2 << 32 | (uint32_t)diag);
+        return fmin(fmin(cur, c0), fmin(c1, c2));
+    }
+};
+static_assert((uint32_t)(FixedCost::inverse() * FixedCost::kR) % (1u << 29) == 1u, "an inverse");
+
 // One round: block (tile, group of kGW goals), one wave per goal.  The
 // tile's navigability and each interior cell's legal moves are shared by
 // the goals; each wave loads its goal's tile and halo into LDS and relaxes
@@ -115,9 +194,9 @@ __device__ __forceinline__ double pair_cost(uint64_t p) {
 // monotone.  The wave stops after two phases in a row that change nothing.
 constexpr int kGW = kNT / kWave;           // goals per workgroup
 
+template <class C>
 struct DistShared {
-    uint64_t d[kGW][kH * kH];              // pairs, one 64-bit LDS access each
-    uint8_t nav[kH * kH];
+    typename C::T d[kGW][kH * kH];         // costs, one 64-bit LDS access each
     uint8_t mv[kH * kH];                   // legal moves of interior cells
 };
 
@@ -128,8 +207,8 @@ struct DistShared {
 // The cheaper of (cur, c0) and of (c1, c2) are found side by side, then the
 // cheaper of the two: equal costs mean equal pairs, so the grouping of the
 // tests does not change the pair returned.
-__device__ __forceinline__ uint64_t relax_pair(uint64_t cur, uint32_t m, uint64_t v0, int b0, uint64_t v1, int b1,
-                                               uint64_t v2, int b2) {
+__device__ __forceinline__ uint64_t PairCost::relax(uint64_t cur, uint32_t m, uint64_t v0, int b0, uint64_t v1, int b1,
+                                                    uint64_t v2, int b2) {
     const double inf = __builtin_huge_val();
     const uint64_t c0 = v0 + kOrth, c1 = v1 + kDiag, c2 = v2 + kDiag;
     const double kc = cur == kUnreached ? inf : pair_cost(cur);
@@ -145,13 +224,13 @@ __device__ __forceinline__ uint64_t relax_pair(uint64_t cur, uint32_t m, uint64_
 // The value of lane l - 1 (from_below) or l + 1 (from_above) in the wave;
 // lanes 0 and 63 receive zero.
 __device__ __forceinline__ uint64_t from_below(uint64_t v) {
-    const uint32_t lo = __builtin_amdgcn_update_dpp(0u, (uint32_t)v, 0x138, 0xf, 0xf, false);   // wave_shr:1
-    const uint32_t hi = __builtin_amdgcn_update_dpp(0u, (uint32_t)(v >> 32), 0x138, 0xf, 0xf, false);
+    const uint32_t lo = __builtin_amdgcn_mov_dpp((uint32_t)v, 0x138, 0xf, 0xf, true);   // wave_shr:1
+    const uint32_t hi = __builtin_amdgcn_mov_dpp((uint32_t)(v >> 32), 0x138, 0xf, 0xf, true);
     return (uint64_t)hi << 32 | lo;
 }
 __device__ __forceinline__ uint64_t from_above(uint64_t v) {
-    const uint32_t lo = __builtin_amdgcn_update_dpp(0u, (uint32_t)v, 0x130, 0xf, 0xf, false);   // wave_shl:1
-    const uint32_t hi = __builtin_amdgcn_update_dpp(0u, (uint32_t)(v >> 32), 0x130, 0xf, 0xf, false);
+    const uint32_t lo = __builtin_amdgcn_mov_dpp((uint32_t)v, 0x130, 0xf, 0xf, true);   // wave_shl:1
+    const uint32_t hi = __builtin_amdgcn_mov_dpp((uint32_t)(v >> 32), 0x130, 0xf, 0xf, true);
     return (uint64_t)hi << 32 | lo;
 }
 
@@ -169,9 +248,10 @@ __device__ __forceinline__ uint64_t from_above(uint64_t v) {
 // reads follow the first half's writes, every pair used equals what a read
 // at the step itself would return, and storing a cell's pair unchanged
 // overwrites nothing newer.  Returns whether the lane changed a cell.
-template <int L, int A>
-__device__ __forceinline__ bool sweep(uint64_t* sd, const uint8_t* mv, int li, int fwd, int x0, int b0, int b1,
+template <class C, int L, int A>
+__device__ __forceinline__ bool sweep(typename C::T* sd, const uint8_t* mv, int li, int fwd, int x0, int b0, int b1,
                                       int b2) {
+    typedef typename C::T T;
     constexpr int kHalf = kT / 2, kChunk = 4, kChunks = kHalf / kChunk;
     int q0 = li * A + x0 * L, dq = fwd * L;
     // formed anew at every call: nothing derived from them is hoisted out
@@ -183,12 +263,12 @@ __device__ __forceinline__ bool sweep(uint64_t* sd, const uint8_t* mv, int li, i
     // (compiler-only) fences keep later chunks from being hoisted into the
     // registers, and the second half's reads after the first half's writes.
     __asm__ volatile("" ::: "memory");
-    uint64_t best = sd[q0 + o0];
-    const uint64_t up0 = sd[q0 + o1], dn0 = sd[q0 + o2];
+    T best = sd[q0 + o0];
+    const T up0 = sd[q0 + o1], dn0 = sd[q0 + o2];
     bool ch = false;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-        uint64_t cur[2][kChunk], hal[2][kChunk];
+        T cur[2][kChunk], hal[2][kChunk];
         uint32_t m[2][kChunk];
         int qb[2];
         auto load = [&](int c) {
@@ -214,13 +294,13 @@ __device__ __forceinline__ bool sweep(uint64_t* sd, const uint8_t* mv, int li, i
 #pragma unroll
             for (int s = 0; s < kChunk; ++s) {
                 const int st = h * kHalf + c * kChunk + s;
-                uint64_t v1 = up0, v2 = dn0;
+                T v1 = up0, v2 = dn0;
                 if (st > 0) {
-                    const uint64_t lb = from_below(best), la = from_above(best);
+                    const T lb = C::from_bits(from_below(C::bits(best))), la = C::from_bits(from_above(C::bits(best)));
                     v1 = li == 1 ? hal[c & 1][s] : lb;
                     v2 = li == kT ? hal[c & 1][s] : la;
                 }
-                const uint64_t nb = relax_pair(cur[c & 1][s], m[c & 1][s], best, b0, v1, b1, v2, b2);
+                const T nb = C::relax(cur[c & 1][s], m[c & 1][s], best, b0, v1, b1, v2, b2);
                 sd[qb[c & 1] + dq * s] = nb;
                 ch |= nb != cur[c & 1][s];
                 best = nb;
@@ -231,67 +311,64 @@ __device__ __forceinline__ bool sweep(uint64_t* sd, const uint8_t* mv, int li, i
     return ch;
 }
 
-__global__ __launch_bounds__(kNT) void k_dist_round(DistArgs d, int round, int slot) {
+template <class C>
+__global__ __launch_bounds__(kNT) void k_dist_round(DistArgs d, int round, int slot, int phases) {
     // After a round of the batch that changed no tile the fields are
-    // settled: the rest of the batch returns at once (its counts stay zero,
-    // and the host stops at the first zero count, so the tile flags these
-    // rounds leave as they were are never read).
-    if (slot > 0 && d.active[slot - 1] == 0) return;
-    __shared__ DistShared S;
+    // settled: the rest of the batch returns (its counts stay zero, and the
+    // host stops at the first zero count, so the tile flags these rounds
+    // leave as they were are never read).
+    const uint32_t before = slot > 0 ? d.active[slot - 1] : 1u;
+    __shared__ DistShared<C> S;
     const int t = blockIdx.x;
     const int tx = t % d.tiles_x, ty = t / d.tiles_x;
     const int64_t tiles = (int64_t)d.tiles_x * d.tiles_y;
     const int gx0 = tx * kT - 1, gy0 = ty * kT - 1;
-    for (int k = threadIdx.x; k < kH * kH; k += kNT) {
-        const int gx = gx0 + k % kH, gy = gy0 + k / kH;
-        const bool in = gx >= 0 && gy >= 0 && gx < d.nx && gy < d.ny;
-        S.nav[k] = (in && d.nav[(size_t)gy * d.nx + gx] != 0) ? 1 : 0;
+    // the legal moves of the tile's cells and, one wave per goal, whether the
+    // goal's tile is active
+    constexpr int kCells = kT * kT / kNT;
+    uint8_t mv[kCells];
+#pragma unroll
+    for (int j = 0; j < kCells; ++j) {
+        const int k = threadIdx.x + j * kNT;
+        const int gx = tx * kT + k % kT, gy = ty * kT + k / kT;
+        mv[j] = gx < d.nx && gy < d.ny ? d.moves[(size_t)gy * d.nx + gx] : 0;
     }
-    __syncthreads();
-    // bit m: move m of E, W, S, N, SE, SW, NE, NW leads to a navigable
-    // cell (diagonals between navigable side cells)
-    for (int k = threadIdx.x; k < kH * kH; k += kNT) {
-        const int lx = k % kH, ly = k / kH;
-        uint32_t m = 0;
-        if (lx >= 1 && lx <= kT && ly >= 1 && ly <= kT && S.nav[k]) {
-            const bool e = S.nav[k + 1], w = S.nav[k - 1], so = S.nav[k + kH], no = S.nav[k - kH];
-            m = (e ? 1u : 0u) | (w ? 2u : 0u) | (so ? 4u : 0u) | (no ? 8u : 0u);
-            if (e && so && S.nav[k + kH + 1]) m |= 16u;
-            if (w && so && S.nav[k + kH - 1]) m |= 32u;
-            if (e && no && S.nav[k - kH + 1]) m |= 64u;
-            if (w && no && S.nav[k - kH - 1]) m |= 128u;
-        }
-        S.mv[k] = (uint8_t)m;
-    }
-    __syncthreads();
-    // from here each wave works alone on its goal
     const int w = threadIdx.x / kWave, lane = lane_id();
     const int g = blockIdx.y * kGW + w;
-    if (g >= d.n_goals) return;
-    const uint8_t* prev = d.flags[round & 1] + g * tiles;
+    const bool mine = g < d.n_goals;
+    const uint8_t* prev = d.flags[round & 1] + (mine ? g : 0) * tiles;
     uint8_t* next = d.flags[(round + 1) & 1] + g * tiles;
     int act = 0;
-    for (int v = max(ty - 1, 0); v <= min(ty + 1, d.tiles_y - 1); ++v)
-        for (int u = max(tx - 1, 0); u <= min(tx + 1, d.tiles_x - 1); ++u) act |= prev[v * d.tiles_x + u];
-    if (!act) {
-        if (lane == 0) next[t] = 0;
-        return;
+    if (mine && lane < 9) {
+        const int u = tx - 1 + lane % 3, v = ty - 1 + lane / 3;
+        if (u >= 0 && v >= 0 && u < d.tiles_x && v < d.tiles_y) act = prev[v * d.tiles_x + u];
     }
-    uint64_t* D = d.dist + (size_t)g * d.nx * d.ny;
-    uint64_t* sd = S.d[w];
-    // all of a lane's loads in flight together, then the LDS stores
+    if (before == 0) return;
+    const bool active = __ballot(act) != 0;
+    if (mine && !active && lane == 0) next[t] = 0;
+    // all of a lane's loads in flight together
+    uint64_t* D = d.dist + (size_t)(mine ? g : 0) * d.nx * d.ny;
+    typename C::T* sd = S.d[w];
     constexpr int kLoads = (kH * kH + kWave - 1) / kWave;
     uint64_t ld[kLoads];
 #pragma unroll
     for (int j = 0; j < kLoads; ++j) {
         const int k = lane + j * kWave;
         const int gx = gx0 + k % kH, gy = gy0 + k / kH;
-        const bool in = k < kH * kH && gx >= 0 && gy >= 0 && gx < d.nx && gy < d.ny;
+        const bool in = active && k < kH * kH && gx >= 0 && gy >= 0 && gx < d.nx && gy < d.ny;
         ld[j] = in ? load_relaxed(D + (size_t)gy * d.nx + gx) : kUnreached;
     }
 #pragma unroll
+    for (int j = 0; j < kCells; ++j) {
+        const int k = threadIdx.x + j * kNT;
+        S.mv[(k / kT + 1) * kH + k % kT + 1] = mv[j];
+    }
+    __syncthreads();
+    // from here each wave works alone on its goal
+    if (!active) return;
+#pragma unroll
     for (int j = 0; j < kLoads; ++j)
-        if (lane + j * kWave < kH * kH) sd[lane + j * kWave] = ld[j];
+        if (lane + j * kWave < kH * kH) sd[lane + j * kWave] = C::of(ld[j]);
     // lanes 0-31 sweep east / south, lanes 32-63 west / north; li is the
     // lane's row (x phase) or column (y phase), 1..32
     const int fwd = lane < 32 ? 1 : -1, li = (lane & 31) + 1;
@@ -304,32 +381,30 @@ __global__ __launch_bounds__(kNT) void k_dist_round(DistArgs d, int round, int s
     // and the four diagonals, a y phase over N, S and the diagonals: two
     // phases in a row that change nothing, in either order, mark a fixed
     // point over all eight moves.
+    // The wave stops there or, having changed a cell, after `phases` phases:
+    // what it leaves to do, it does in the next round, in which every tile
+    // that changed is active.
     bool any = false;
-    for (int quiet = 0, ph = 0; quiet < 2; ph ^= 1) {
-        const bool ch = ph == 0 ? sweep<1, kH>(sd, S.mv, li, fwd, x0, xb0, xb1, xb2)
-                                : sweep<kH, 1>(sd, S.mv, li, fwd, x0, yb0, yb1, yb2);
-        any |= ch;
-        quiet = __ballot(ch) ? 0 : quiet + 1;
+    for (int quiet = 0, ph = 0; quiet < 2 && (ph < phases || !any); ++ph) {
+        const bool ch = (ph & 1) == 0 ? sweep<C, 1, kH>(sd, S.mv, li, fwd, x0, xb0, xb1, xb2)
+                                      : sweep<C, kH, 1>(sd, S.mv, li, fwd, x0, yb0, yb1, yb2);
+        const bool some = __ballot(ch) != 0;
+        any |= some;
+        quiet = some ? 0 : quiet + 1;
     }
+    // (no other wave writes this goal's tile: the cells loaded are still there)
     bool wrote = false;
-    if (__ballot(any)) {
-        constexpr int kCells = kT * kT / kWave;
-        uint64_t old[kCells];
+    if (any) {
 #pragma unroll
-        for (int j = 0; j < kCells; ++j) {
+        for (int j = 0; j < kLoads; ++j) {
             const int k = lane + j * kWave;
-            const int gx = gx0 + k % kT + 1, gy = gy0 + k / kT + 1;
-            old[j] = gx < d.nx && gy < d.ny ? load_relaxed(D + (size_t)gy * d.nx + gx) : 0u;
-        }
-#pragma unroll
-        for (int j = 0; j < kCells; ++j) {
-            const int k = lane + j * kWave;
-            const int q = (k / kT + 1) * kH + k % kT + 1;
-            const int gx = gx0 + k % kT + 1, gy = gy0 + k / kT + 1;
-            const uint64_t v = sd[q];
-            if (gx < d.nx && gy < d.ny && v != old[j]) {
-                store_relaxed(D + (size_t)gy * d.nx + gx, v);
-                wrote = true;
+            const int lx = k % kH, ly = k / kH, gx = gx0 + lx, gy = gy0 + ly;
+            if (lx >= 1 && lx <= kT && ly >= 1 && ly <= kT && gx < d.nx && gy < d.ny) {
+                const uint64_t v = C::pair(sd[k]);
+                if (v != ld[j]) {
+                    store_relaxed(D + (size_t)gy * d.nx + gx, v);
+                    wrote = true;
+                }
             }
         }
     }
@@ -484,10 +559,11 @@ void launch_dist_init(const DistArgs& d, hipStream_t s) {
     k_dist_init<<<grid_for((int64_t)d.nx * d.ny * d.n_goals), kNT, 0, s>>>(d);
 }
 
-void launch_dist_rounds(const DistArgs& d, int round0, int n_rounds, hipStream_t s) {
+void launch_dist_rounds(const DistArgs& d, int round0, int n_rounds, int phases, hipStream_t s) {
     k_zero_u32<<<1, 64, 0, s>>>(d.active, n_rounds);
     const dim3 grid((unsigned)(d.tiles_x * d.tiles_y), (unsigned)((d.n_goals + kGW - 1) / kGW));
-    for (int r = 0; r < n_rounds; ++r) k_dist_round<<<grid, kNT, 0, s>>>(d, round0 + r, r);
+    auto round = (int64_t)d.nx * d.ny <= kFixedCells ? k_dist_round<FixedCost> : k_dist_round<PairCost>;
+    for (int r = 0; r < n_rounds; ++r) round<<<grid, kNT, 0, s>>>(d, round0 + r, r, phases);
 }
 
 void launch_trace(const TraceArgs& a, hipStream_t s) {
