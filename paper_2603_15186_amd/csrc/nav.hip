@@ -457,17 +457,17 @@ __global__ __launch_bounds__(kNT) void k_steps(TraceArgs a) {
 // kept in registers), a quarter of the scattered stores.
 template <class Rd>
 __device__ __forceinline__ int32_t walk(const TraceArgs& a, int64_t q, int32_t s, Rd rd) {
-    const int64_t N = (int64_t)a.nx * a.ny;
+    const int32_t N = a.nx * a.ny;         // at most 2^24
     int32_t* out = a.paths + q * a.cap;
     const bool vec = (a.cap & 3) == 0 && (reinterpret_cast<uintptr_t>(a.paths) & 15) == 0;
-    int64_t c = s, m = 0;
+    int32_t c = s, m = 0;
     int32_t c0 = 0, c1 = 0, c2 = 0, c3 = 0;   // the last four cells, c3 the latest
     uint32_t st;
     for (;;) {
         c0 = c1;
         c1 = c2;
         c2 = c3;
-        c3 = (int32_t)c;
+        c3 = c;
         if (!vec) {
             if (m < a.cap) out[m] = c3;
         } else if ((m & 3) == 3 && m < a.cap) {
@@ -476,15 +476,15 @@ __device__ __forceinline__ int32_t walk(const TraceArgs& a, int64_t q, int32_t s
         ++m;
         st = rd(c);
         if (st >= kGoal || m > N) break;      // kGoal and kNone are the codes above the moves
-        c += (int64_t)step_dy(st) * a.nx + step_dx(st);
+        c += __mul24(step_dy(st), a.nx) + step_dx(st);
     }
     if (vec) {                             // the cells after the last full four
-        const int r = (int)(m & 3);
+        const int r = m & 3;
         if (r >= 3 && m - 3 < a.cap) out[m - 3] = c1;
         if (r >= 2 && m - 2 < a.cap) out[m - 2] = c2;
         if (r >= 1 && m - 1 < a.cap) out[m - 1] = c3;
     }
-    return st == kGoal ? (int32_t)m : -1;
+    return st == kGoal ? m : -1;
 }
 
 __device__ __forceinline__ bool query_ok(const TraceArgs& a, int32_t s, int32_t slot) {
@@ -499,7 +499,7 @@ __global__ __launch_bounds__(kNT) void k_trace(TraceArgs a) {
         int32_t len = 0;
         if (query_ok(a, s, slot)) {
             const uint8_t* S = a.steps + (size_t)slot * a.stride;
-            len = walk(a, q, s, [&](int64_t c) { return S[c]; });
+            len = walk(a, q, s, [&](int32_t c) { return S[c]; });
         }
         a.lengths[q] = len;
     }
@@ -521,7 +521,19 @@ __global__ __launch_bounds__(kNT) void k_trace_lds(TraceArgs a) {
     __shared__ uint32_t cnt;
     const int g = blockIdx.x / kTraceSplit, part = blockIdx.x % kTraceSplit;
     const uint4* src = reinterpret_cast<const uint4*>(a.steps + (size_t)g * a.stride);
-    for (int k = threadIdx.x; k < (int)(a.stride / 16); k += kNT) reinterpret_cast<uint4*>(L)[k] = src[k];
+    // (eight loads in flight: one after the other, the 120 kB of a 400 x 300
+    // floor took 30 round trips to memory)
+    constexpr int kStage = 8;
+    const int n16 = (int)(a.stride / 16);
+    for (int k0 = threadIdx.x; k0 < n16; k0 += kStage * kNT) {
+        uint4 v[kStage];
+#pragma unroll
+        for (int j = 0; j < kStage; ++j)
+            if (k0 + j * kNT < n16) v[j] = src[k0 + j * kNT];
+#pragma unroll
+        for (int j = 0; j < kStage; ++j)
+            if (k0 + j * kNT < n16) reinterpret_cast<uint4*>(L)[k0 + j * kNT] = v[j];
+    }
     for (int64_t base = 0; base < a.n; base += kTraceList) {
         if (threadIdx.x == 0) cnt = 0;
         __syncthreads();                   // (first pass: also the staged moves)
@@ -536,7 +548,7 @@ __global__ __launch_bounds__(kNT) void k_trace_lds(TraceArgs a) {
         for (uint32_t i = threadIdx.x; i < k; i += kNT) {
             const int64_t q = base + list[i];
             const int32_t s = a.starts[q], slot = a.slots[q];
-            a.lengths[q] = query_ok(a, s, slot) ? walk(a, q, s, [&](int64_t c) { return L[c]; }) : 0;
+            a.lengths[q] = query_ok(a, s, slot) ? walk(a, q, s, [&](int32_t c) { return L[c]; }) : 0;
         }
         __syncthreads();                   // list and count are reused
     }

@@ -32,14 +32,17 @@ namespace {
 
 constexpr int kNT = 256;
 
-__global__ void k_fill_zero(uint4* p, size_t n16) {
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n16; i += (size_t)gridDim.x * blockDim.x)
-        p[i] = make_uint4(0, 0, 0, 0);
-}
-
-__global__ void k_fill_zero_tail(uint8_t* p, size_t from, size_t n) {
-    for (size_t i = from + blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-        p[i] = 0;
+// Zeros to two byte ranges, 16 bytes a thread between their ends.
+__global__ __launch_bounds__(kNT) void k_fill_zero(uint8_t* p0, size_t n0, uint8_t* p1, size_t n1) {
+    for (int r = 0; r < 2; ++r) {
+        uint8_t* p = r ? p1 : p0;
+        const size_t n = r ? n1 : n0, head = min(n, (size_t)(-reinterpret_cast<uintptr_t>(p) & 15u));
+        const size_t n16 = (n - head) / 16, t = blockIdx.x * (size_t)kNT + threadIdx.x, stride = (size_t)gridDim.x * kNT;
+        for (size_t i = t; i < n16; i += stride) reinterpret_cast<uint4*>(p + head)[i] = make_uint4(0, 0, 0, 0);
+        if (t < head) p[t] = 0;
+        const size_t tail = head + 16 * n16;
+        if (t < n - tail) p[tail + t] = 0;
+    }
 }
 
 // Least of q(d) = a dx^2 + 2 b dx dy + c dy^2 over the square
@@ -207,12 +210,11 @@ __global__ __launch_bounds__(kNT) void k_slice(SliceArgs s) {
                 // (a c / det: what det and the rows lose to cancellation)
                 G.ip = 0.0;
                 if (det > 1e-5 * (G.a * G.c) && G.a > 1e-30 && G.a < 1e30 && G.c > 1e-30 && G.c < 1e30) {
-                    const double p = sqrt(G.a);
-                    G.ip = 1.0 / p;
+                    G.ip = rsqrt64(G.a);
                     G.r = G.b * G.ip;
-                    G.s = sqrt(det) * G.ip;
-                    G.is = 1.0 / G.s;
-                    G.yr = -G.r * G.is / sqrt(G.r * G.r + G.s * G.s);
+                    G.s = det * rsqrt64(det) * G.ip;
+                    G.is = rcp64(G.s);
+                    G.yr = -G.r * G.is * rsqrt64(G.r * G.r + G.s * G.s);
                 }
                 S[threadIdx.x] = G;
             } else {
@@ -252,15 +254,6 @@ __global__ __launch_bounds__(kNT) void k_disc_collision(DiscArgs d) {
         d.out[q] = disc_hits(d.map, d.x0, d.y0, d.cell, d.nx, d.ny, d.xy[2 * q], d.xy[2 * q + 1], d.radius) ? 1 : 0;
 }
 
-void zero_bytes(uint8_t* p, size_t n, hipStream_t st) {
-    if (!p || n == 0) return;
-    const size_t n16 = (reinterpret_cast<uintptr_t>(p) % 16 == 0) ? n / 16 : 0;
-    if (n16) k_fill_zero<<<1024, 256, 0, st>>>(reinterpret_cast<uint4*>(p), n16);
-    const size_t rest = n - n16 * 16;
-    if (rest) k_fill_zero_tail<<<(unsigned)((rest + 255) / 256 < 4096 ? (rest + 255) / 256 : 4096), 256, 0, st>>>(
-        p, n16 * 16, n);
-}
-
 }  // namespace
 
 void launch_disc_collision(const DiscArgs& d, hipStream_t st) {
@@ -270,8 +263,8 @@ void launch_disc_collision(const DiscArgs& d, hipStream_t st) {
 }
 
 void launch_slice(const SliceArgs& a, hipStream_t st) {
-    zero_bytes(a.occ, (size_t)a.n_planes * a.nx * a.ny, st);
-    zero_bytes(a.map, (size_t)a.nx * a.ny, st);
+    const size_t plane = (size_t)a.nx * a.ny;
+    k_fill_zero<<<1024, kNT, 0, st>>>(a.occ, a.occ ? a.n_planes * plane : 0, a.map, a.map ? plane : 0);
     if (a.n) k_slice<<<2048, kNT, 0, st>>>(a);
 }
 
