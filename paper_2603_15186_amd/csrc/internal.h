@@ -114,7 +114,7 @@ struct alignas(16) BinRec {
     ushort4 rc;                      // tile rectangle x0, y0, x1, y1 (inclusive)
     uint32_t tile_base;              // sort key of the view's first tile: view << key_shift
     uint16_t tiles_x;
-    uint16_t height;                 // image height in pixels
+    uint16_t height;                 // image height in pixels; of a small rectangle the mask of its tiles
 };
 
 // Device counters of one render.
