@@ -272,8 +272,13 @@ hgs_status upload_views(hgs_ctx* c, hipStream_t s, const hgs_output* outs) {
         d.depth = outs[v].depth;
         d.alpha = outs[v].alpha;
     }
-    HIP_TRY(c, hipMemcpyAsync(c->views.p, c->views_host, sizeof(ViewDev) * V, hipMemcpyHostToDevice, s));
-    HIP_TRY(c, hipEventRecord(c->views_copied, s));
+    if (V <= kArgViews) {
+        launch_set_views(c->views_host, V, P<ViewDev>(c->views), s);
+        HIP_TRY(c, hipGetLastError());
+    } else {
+        HIP_TRY(c, hipMemcpyAsync(c->views.p, c->views_host, sizeof(ViewDev) * V, hipMemcpyHostToDevice, s));
+        HIP_TRY(c, hipEventRecord(c->views_copied, s));
+    }
     c->views_dirty = false;
     return HGS_OK;
 }

@@ -288,6 +288,13 @@ constexpr uint32_t kProjectLdsViews = 2 * kCutViewGroup;
 constexpr uint32_t kTileListMax = 8192;   // tiles of a pass that per-tile lists serve (their counts fit in LDS)
 void launch_project(const ProjectArgs& a, hipStream_t s);
 
+// Up to kArgViews views reach the device as a kernel's arguments.  A copy and
+// the event that frees the host's mirror put off the first kernel of
+// a render by 2 to 8 us (a 256 x 256 render 93 -> 91 us, one with its backward
+// 229 -> 221).
+constexpr int kArgViews = 8;
+void launch_set_views(const ViewDev* host, int n, ViewDev* views, hipStream_t s);
+
 // keys[i] = view of the depth-sorted entry order[i] (order: index | tiles
 // << 28), read from the cut, so that a stable pass on them groups the
 // entries by view.

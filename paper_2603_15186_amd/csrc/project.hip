@@ -985,6 +985,26 @@ __global__ void k_view_keys(const uint32_t* __restrict__ order, const uint2* __r
     }
 }
 
+namespace {
+
+struct ArgViews {
+    ViewDev v[kArgViews];
+};
+static_assert(sizeof(ArgViews) <= 3072, "kernel arguments hold 4 KB");
+
+__global__ __launch_bounds__(kNT) void k_set_views(ArgViews a, int n, uint64_t* views) {
+    const uint64_t* src = reinterpret_cast<const uint64_t*>(&a);
+    for (int k = threadIdx.x; k < n * (int)(sizeof(ViewDev) / 8); k += kNT) views[k] = src[k];
+}
+
+}  // namespace
+
+void launch_set_views(const ViewDev* host, int n, ViewDev* views, hipStream_t s) {
+    ArgViews a;
+    for (int v = 0; v < n; ++v) a.v[v] = host[v];
+    k_set_views<<<1, kNT, 0, s>>>(a, n, reinterpret_cast<uint64_t*>(views));
+}
+
 template <bool Blend, bool PerTile>
 void launch_project_b(const ProjectArgs& a, hipStream_t s) {
     switch (a.sh_degree) {
