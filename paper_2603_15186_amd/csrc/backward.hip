@@ -28,7 +28,7 @@
 // entry, and before that the atomics: with one pixel per thread, ten full row
 // sums per block and entry and ten scattered global atomics per tile and
 // entry, four 640 x 480 views of a 700,000-leaf plan took 650 us here;
-// 444 this way.
+// 401 this way.
 //
 // Projection (FP64): the cut entries are sorted by Gaussian (the radix sort
 // of the binning); one thread per entry in that order takes the chain rule
@@ -169,11 +169,12 @@ __device__ __forceinline__ void ten_sums(const float (&v)[kNG], bool odd1, bool 
     *s2 = q[2] + dpp_f<0x104>(q[2]);
 }
 
-// Batches of 128 entries and a register budget of six waves per SIMD: the
-// reverse walk is a chain of LDS reads, exponentials and LDS adds whose
-// latency only more resident waves hide.
+// Batches of 128 entries and the 121 registers of four waves per SIMD: the
+// reverse walk is a chain of LDS reads, exponentials and LDS adds, whose latency
+// the other waves, the records read four at a time and the next batch fetched
+// ahead hide (444 -> 401 us with these two at the size above).
 template <bool KEPT>
-__global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(6))) void k_composite_bwd(BwdArgs a) {
+__global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(4))) void k_composite_bwd(BwdArgs a) {
     __shared__ BwdShared S;
     const uint32_t tile = blockIdx.x;
     const uint2 rg = a.ranges[tile];
