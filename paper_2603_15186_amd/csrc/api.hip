@@ -2128,8 +2128,11 @@ hgs_status hgs_render_backward(hgs_ctx* c, void* stream, const hgs_image_grad* g
         (s = ensure(c, c->brec, (size_t)c->cut_cap * kEntryRec * sizeof(float))) ||
         (s = ensure(c, c->dimg, (size_t)nv * sizeof(ImgGrad))))
         return s;
-    HIP_TRY(c, hipMemcpyAsync(c->dimg.p, c->dimg_host, (size_t)nv * sizeof(ImgGrad), hipMemcpyHostToDevice, st));
-    HIP_TRY(c, hipEventRecord(c->dimg_copied, st));
+    const int n_few = nv <= kArgViews ? nv : 0;        // the others by a copy
+    if (!n_few) {
+        HIP_TRY(c, hipMemcpyAsync(c->dimg.p, c->dimg_host, (size_t)nv * sizeof(ImgGrad), hipMemcpyHostToDevice, st));
+        HIP_TRY(c, hipEventRecord(c->dimg_copied, st));
+    }
     BwdArgs b{};
     Work& W = c->w[c->last_lane];
     b.vals = P<uint32_t>(W.pval[c->last_pair_buf]);
@@ -2179,7 +2182,7 @@ hgs_status hgs_render_backward(hgs_ctx* c, void* stream, const hgs_image_grad* g
             if (hipEventCreate(&e) != hipSuccess) e = nullptr;
         if (ev[0]) HIP_TRY(c, hipEventRecord(ev[0], st));
     }
-    launch_backward_composite(b, p.ctr, st);
+    launch_backward_composite(b, p.ctr, c->dimg_host, n_few, st);
     if (ev[1]) HIP_TRY(c, hipEventRecord(ev[1], st));
     launch_backward_params(p, sa, ga, st);
     if (ev[2]) HIP_TRY(c, hipEventRecord(ev[2], st));

@@ -371,7 +371,16 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(4))) void k
     }
 }
 
-__global__ void k_zero_egrad(float* g, const Counters* ctr, uint32_t cap) {
+// Zeros to the entries' sums; the image gradients of up to kArgViews views come
+// along as arguments (with a copy and its event a 253 x 191 step took 222 us, so
+// 214).
+struct ArgGrads {
+    ImgGrad g[kArgViews];
+};
+__global__ void k_zero_egrad(float* g, const Counters* ctr, uint32_t cap, ArgGrads few, int n_few, uint64_t* dimg) {
+    const int words = n_few * (int)(sizeof(ImgGrad) / 8);
+    const uint64_t* src = reinterpret_cast<const uint64_t*>(&few);
+    if (blockIdx.x == 0 && (int)threadIdx.x < words) dimg[threadIdx.x] = src[threadIdx.x];
     const uint64_t n = (uint64_t)min(ctr->cut, cap) * kEntryGrad;
     for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
         g[i] = 0.f;
@@ -637,8 +646,12 @@ __global__ void k_entry_keys(const uint2* cut, const Counters* ctr, uint32_t cap
 
 }  // namespace
 
-void launch_backward_composite(const BwdArgs& b, const Counters* ctr, hipStream_t s) {
-    k_zero_egrad<<<1024, 256, 0, s>>>(b.egrad, ctr, b.cut_cap);
+void launch_backward_composite(const BwdArgs& b, const Counters* ctr, const ImgGrad* few, int n_few, hipStream_t s) {
+    ArgGrads args{};
+    for (int v = 0; v < n_few; ++v) args.g[v] = few[v];
+    static_assert(sizeof(ArgGrads) / 8 <= 256, "a thread per word");
+    k_zero_egrad<<<1024, 256, 0, s>>>(b.egrad, ctr, b.cut_cap, args, n_few,
+                                      const_cast<uint64_t*>(reinterpret_cast<const uint64_t*>(b.dimg)));
     if (!b.total_tiles) return;
     if (b.state)
         k_composite_bwd<true><<<b.total_tiles, kNT, 0, s>>>(b);

@@ -436,7 +436,8 @@ struct GatherArgs {
     float* g_opacity;                // [n]
     float* g_sh;                     // [n][K][3]
 };
-void launch_backward_composite(const BwdArgs& b, const Counters* ctr, hipStream_t s);
+// few: image gradients of n_few <= kArgViews views that are not in b.dimg yet.
+void launch_backward_composite(const BwdArgs& b, const Counters* ctr, const ImgGrad* few, int n_few, hipStream_t s);
 void launch_backward_params(ProjBwdArgs p, SortArgs sa, GatherArgs ga, hipStream_t s);
 
 // shortest-path planning (nav.hip)
