@@ -372,6 +372,7 @@ struct SliceArgs {
     int nx, ny, n_planes;
     double rho_min;
     float heights[256];              // plane heights (passed by value)
+    double low, high, reach;         // their range; reach = 2 ln(1 / rho_min), with a relative margin
     uint8_t* occ;
     uint8_t* map;
 };
