@@ -85,6 +85,8 @@ struct hgs_ctx {
     int64_t regrows = 0;
     int64_t seen_pairs = -1;          // pairs of the last render whose counters were read (-1: none since the
                                       // scene, LOD or tile layout changed)
+    bool shape_set = false;           // the compositor's launch shape was chosen by an option or a plan
+    bool wide_shape = false;          // the last render (and the captured graph) used two pixels per thread by itself
     bool tile_lists = false;          // passes of the last render (and of the captured graph) used per-tile lists
     uint32_t forced_cap = 0;          // test hook: start from this capacity
     int sort_digit_bits = 8;          // widest radix digit
@@ -438,6 +440,24 @@ bool per_tile_lists(const hgs_ctx* c) {
     return !c->hier && n <= 65536 && n <= 128 * (int64_t)c->total_tiles;
 }
 
+// Whether the compositor runs two pixels per thread in batches of 128 where
+// nobody chose its shape (images do not depend on it).  Half the threads per
+// tile share the per-entry work, which pays in launches of many tiles with
+// lists of ordinary length; where single tiles hold thousands of entries,
+// those are over sooner at one pixel per thread.  One against two, us:
+// 1280 x 720 views, 190 to 210 pairs a tile: 14,400 tiles 119 and 120, 28,800
+// 223 and 194, 57,600 430 and 344; 1920 x 1080, 270 a tile, 48,960: 382 and 299;
+// 640 x 480, 640 to 700 a tile: 48,000 675 and 734, 115,200 1,545 and 1,458;
+// 320 x 240, 860 a tile, 76,800: 1,344 and 1,481.  (The pairs are those of the
+// last counted render; a change of mind needs a third more or less, for the
+// sake of recorded graphs.)
+constexpr int64_t kWideTiles = 24576;
+bool wide_shape(const hgs_ctx* c) {
+    if (c->shape_set || c->ropts.keep_state || c->ropts.count_nalg || c->seen_pairs < 0) return false;
+    const int64_t tiles = c->total_tiles, slack = c->wide_shape ? 4 : 3;
+    return tiles / n_passes(c) >= kWideTiles && c->seen_pairs <= slack * 128 * tiles;
+}
+
 // One pipeline pass over the views of pass g (counters slot g).
 void enqueue_pass(hgs_ctx* c, hipStream_t s, int g) {
     Work& W = c->w[lane_of(c, g)];
@@ -604,6 +624,10 @@ void enqueue_pass(hgs_ctx* c, hipStream_t s, int g) {
     xa.n_views = ca.n_views;
     xa.key_shift = key_shift;
     xa.opts = c->ropts;
+    if (c->wide_shape) {
+        xa.opts.px = 2;
+        xa.opts.batch = 128;
+    }
     xa.ctr = ctr;
     xa.state = c->ropts.keep_state ? P<uint2>(c->px_state) + (size_t)t0 * kTilePx : nullptr;
 
@@ -1190,9 +1214,13 @@ hgs_status hgs_set_option(hgs_ctx* c, int32_t opt, int64_t val) {
         case HGS_OPT_BATCH_DEPTH:
             if (val != 64 && val != 128 && val != 256) return fail(c, HGS_E_INVALID, "batch depth must be 64, 128 or 256");
             c->ropts.batch = (int)val;
+            c->shape_set = true;
             return HGS_OK;
         case HGS_OPT_USE_GRAPH: c->use_graph = val != 0; return HGS_OK;
-        case HGS_OPT_PERSISTENT: c->ropts.persistent = val != 0; return HGS_OK;
+        case HGS_OPT_PERSISTENT:
+            c->ropts.persistent = val != 0;
+            c->shape_set = true;
+            return HGS_OK;
         case HGS_OPT_EXACT_TILES: c->ropts.exact_tiles = val != 0; return HGS_OK;
         case HGS_OPT_LOD_BLEND: c->ropts.lod_blend = val != 0; return HGS_OK;
         case HGS_OPT_KEEP_STATE:
@@ -1207,6 +1235,7 @@ hgs_status hgs_set_option(hgs_ctx* c, int32_t opt, int64_t val) {
                             "(or does not allow %d pixels per thread)", tw, th, c->ropts.px);
             if (c->ropts.keep_state && (tw != kTile || th != kTile))
                 return fail(c, HGS_E_UNSUPPORTED, "kept pixel states need %dx%d tiles", kTile, kTile);
+            c->shape_set = true;
             if (tw == c->ropts.tile_w && th == c->ropts.tile_h) return HGS_OK;
             c->ropts.tile_w = tw;
             c->ropts.tile_h = th;
@@ -1217,6 +1246,7 @@ hgs_status hgs_set_option(hgs_ctx* c, int32_t opt, int64_t val) {
                 return fail(c, HGS_E_INVALID, "%lld pixels per thread: 1, 2 or 4, at least 64 threads per %dx%d tile",
                             (long long)val, c->ropts.tile_w, c->ropts.tile_h);
             c->ropts.px = (int)val;
+            c->shape_set = true;
             return HGS_OK;
         case HGS_OPT_LANES: {
             if (val != 1 && val != 2) return fail(c, HGS_E_INVALID, "lanes must be 1 or 2");
@@ -1300,6 +1330,10 @@ hgs_status hgs_render(hgs_ctx* c, void* stream, const hgs_output* outs) {
         if (const bool lists = per_tile_lists(c); lists != c->tile_lists) {
             invalidate_graph(c);
             c->tile_lists = lists;
+        }
+        if (const bool wide = wide_shape(c); wide != c->wide_shape) {
+            invalidate_graph(c);
+            c->wide_shape = wide;
         }
         if (c->use_graph && !c->stage_timing) {
             if (!c->graph_valid) {
@@ -1538,6 +1572,7 @@ hgs_status hgs_autotune(hgs_ctx* c, void* stream, const char* cache_path, int32_
         c->ropts.px = px;
         c->ropts.batch = batch;
         c->ropts.persistent = pers != 0;
+        c->shape_set = true;
         c->sort_digit_bits = digits;
         return HGS_OK;
     };
