@@ -110,9 +110,10 @@ typedef int32_t hgs_status;
                                        then cut order).  Kept pixel states and the
                                        backward pass need 16x16. */
 #define HGS_OPT_PIXELS_PER_THREAD 16 /* pixels each compositing thread evaluates: 1
-                                       (default), 2 or 4 horizontally adjacent pixels,
-                                       at least 64 threads per tile.  Images do not
-                                       depend on it. */
+                                       (default; while no shape was chosen, renders of
+                                       many tiles take 2 by themselves), 2 or 4
+                                       horizontally adjacent pixels, at least 64 threads
+                                       per tile.  Images do not depend on it. */
 
 typedef struct hgs_ctx hgs_ctx;
 
