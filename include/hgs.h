@@ -114,6 +114,11 @@ typedef int32_t hgs_status;
                                        many tiles take 2 by themselves), 2 or 4
                                        horizontally adjacent pixels, at least 64 threads
                                        per tile.  Images do not depend on it. */
+#define HGS_OPT_BINNING 17          /* how passes group their (tile, Gaussian) pairs: 0
+                                       (default) chosen by the pairs of earlier renders,
+                                       1 by radix sorts, 2 by per-tile lists wherever a
+                                       pass has at most 8,192 tiles.  Images do not
+                                       depend on it. */
 
 typedef struct hgs_ctx hgs_ctx;
 
@@ -255,6 +260,12 @@ hgs_status hgs_get_projected(hgs_ctx* ctx, int32_t view, float* host_out, int64_
 
 /* Counters of the last render (synchronises with it). */
 hgs_status hgs_get_stats(hgs_ctx* ctx, hgs_stats* out);
+
+/* What the last render chose for itself: *lists = 1 if its passes were binned
+ * through per-tile lists, 0 if through the sorts (HGS_OPT_BINNING), and the
+ * pixels per compositing thread (HGS_OPT_PIXELS_PER_THREAD).  Either pointer
+ * may be NULL.  HGS_E_STATE before the first render. */
+hgs_status hgs_get_route(hgs_ctx* ctx, int32_t* lists, int32_t* pixels_per_thread);
 
 /* Launch plan chosen by hgs_autotune. */
 typedef struct {

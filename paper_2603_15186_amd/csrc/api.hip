@@ -88,6 +88,8 @@ struct hgs_ctx {
     bool shape_set = false;           // the compositor's launch shape was chosen by an option or a plan
     bool wide_shape = false;          // the last render (and the captured graph) used two pixels per thread by itself
     bool tile_lists = false;          // passes of the last render (and of the captured graph) used per-tile lists
+    int binning = 0;                  // HGS_OPT_BINNING
+    int last_px = 0;                  // pixels per thread of the last render (0: none yet)
     uint32_t forced_cap = 0;          // test hook: start from this capacity
     int sort_digit_bits = 8;          // widest radix digit
     double mean_lo[3] = {0, 0, 0}, mean_hi[3] = {0, 0, 0};   // bounding box of every node's mean
@@ -433,6 +435,7 @@ bool per_tile_lists(const hgs_ctx* c) {
     uint32_t tiles = 0;
     for (int g = 0; g + 1 < (int)c->pass_v0.size(); ++g) tiles = std::max(tiles, pass_tile0(c, g + 1) - pass_tile0(c, g));
     if (tiles == 0 || tiles > kTileListMax) return false;
+    if (c->binning) return c->binning == 2;
     const int64_t slack = c->tile_lists ? 2 : 1;
     if (c->seen_pairs >= 0)
         return c->seen_pairs <= slack * kTileListPairs && c->seen_pairs <= slack * 256 * (int64_t)c->total_tiles;
@@ -1278,6 +1281,10 @@ hgs_status hgs_set_option(hgs_ctx* c, int32_t opt, int64_t val) {
             if (val < 6 || val > 11) return fail(c, HGS_E_INVALID, "digit bits must be 6..11");
             c->sort_digit_bits = (int)val;
             return HGS_OK;
+        case HGS_OPT_BINNING:
+            if (val < 0 || val > 2) return fail(c, HGS_E_INVALID, "binning must be 0, 1 (sorts) or 2 (per-tile lists)");
+            c->binning = (int)val;
+            return HGS_OK;
         case HGS_OPT_STAGE_TIMING: {
             hgs_status s = harvest_events(c);
             if (s) return s;
@@ -1355,6 +1362,7 @@ hgs_status hgs_render(hgs_ctx* c, void* stream, const hgs_output* outs) {
         }
         HIP_TRY(c, hipGetLastError());
         c->last_valid = true;
+        c->last_px = c->wide_shape ? 2 : c->ropts.px;
         if (!c->sync_check) return HGS_OK;
         if ((st = read_counters(c, s))) return st;
         uint64_t need_sum = 0;
@@ -1495,6 +1503,14 @@ hgs_status hgs_get_stats(hgs_ctx* c, hgs_stats* out) {
     out->timed_backwards = c->bwd_n;
     out->ms_bwd_composite = c->bwd_ms[0];
     out->ms_bwd_total = c->bwd_ms[1];
+    return HGS_OK;
+}
+
+hgs_status hgs_get_route(hgs_ctx* c, int32_t* lists, int32_t* px) {
+    if (!c) return HGS_E_INVALID;
+    if (!c->last_px) return fail(c, HGS_E_STATE, "no render yet");
+    if (lists) *lists = c->tile_lists ? 1 : 0;
+    if (px) *px = c->last_px;
     return HGS_OK;
 }
 

@@ -44,6 +44,7 @@ HGS_OPT_LANES = 13
 HGS_OPT_KEEP_STATE = 14
 HGS_OPT_TILE_SHAPE = 15
 HGS_OPT_PIXELS_PER_THREAD = 16
+HGS_OPT_BINNING = 17
 
 PROJECTED_FIELDS = ("u", "v", "A", "B", "C", "r", "g", "b", "depth", "opacity", "ntiles", "valid")
 
@@ -124,6 +125,7 @@ EXPORTS = [
     ("hgs_get_cut", ctypes.c_int32, [_P, ctypes.c_int32, _P, ctypes.c_int64, ctypes.POINTER(ctypes.c_int64)]),
     ("hgs_get_projected", ctypes.c_int32, [_P, ctypes.c_int32, _P, ctypes.c_int64, ctypes.POINTER(ctypes.c_int64)]),
     ("hgs_get_stats", ctypes.c_int32, [_P, ctypes.POINTER(hgs_stats)]),
+    ("hgs_get_route", ctypes.c_int32, [_P, ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_int32)]),
     ("hgs_autotune", ctypes.c_int32, [_P, _P, ctypes.c_char_p, ctypes.c_int32, ctypes.POINTER(hgs_plan)]),
     ("hgs_sort_pairs", ctypes.c_int32, [_P, _P, _P, _P, ctypes.c_int64, ctypes.c_int32]),
     ("hgs_sort_pairs_noalloc", ctypes.c_int32, [_P, _P, _P, _P, ctypes.c_int64, ctypes.c_int32]),
@@ -337,6 +339,13 @@ class Renderer:
         s = hgs_stats()
         self._check(self.lib.hgs_get_stats(self.ctx, ctypes.byref(s)))
         return {k: getattr(s, k) for k, _ in hgs_stats._fields_}
+
+    def route(self) -> dict:
+        """What the last render chose by itself: binning through per-tile
+        lists (else through the sorts) and pixels per compositing thread."""
+        lists, px = ctypes.c_int32(), ctypes.c_int32()
+        self._check(self.lib.hgs_get_route(self.ctx, ctypes.byref(lists), ctypes.byref(px)))
+        return dict(lists=bool(lists.value), pixels_per_thread=px.value)
 
     def set_tile_shape(self, width, height, pixels_per_thread=1):
         """Tile shape (HGS_OPT_TILE_SHAPE) and pixels per compositing thread
