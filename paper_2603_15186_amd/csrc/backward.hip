@@ -39,6 +39,8 @@
 // thread per Gaussian then sums its run of records, forming the SH
 // coefficients' gradients sum g_c Y_k(d) on the way: no scattered atomics on
 // the parameter arrays.
+#include <type_traits>
+
 #include "blocks.h"
 #include "device_util.h"
 #include "internal.h"
@@ -267,6 +269,7 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(4))) void k
     // 2. back to front over the same lists
     const size_t plane = (size_t)V.width * V.height;
     float gC0[2], gC1[2], gC2[2], gD[2], behind[2];
+    bool bad = false;
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
         const size_t pix = (size_t)py * V.width + (x0 + lx0 + q);
@@ -277,7 +280,13 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(4))) void k
         gD[q] = in && G.depth ? G.depth[pix] : 0.f;
         const float gA = in && G.alpha ? G.alpha[pix] : 0.f;
         behind[q] = Tc[q] * (gC0[q] * V.bg[0] + gC1[q] * V.bg[1] + gC2[q] * V.bg[2] - gA);
+        bad |= !(fabsf(gC0[q]) + fabsf(gC1[q]) + fabsf(gC2[q]) + fabsf(gD[q]) < __builtin_inff());
     }
+    // An entry that a pixel does not take has al = wgt = 0 there, and h and
+    // what lies behind are passed by; its colour and depth terms are zero by
+    // the product, except with a gradient that is not finite: waves that hold
+    // such a pixel select them too (eight selects, in a loop of their own).
+    const bool bad_wave = __ballot(bad) != 0;
     for (int i = threadIdx.x; i < kB * kEntryGrad; i += kNT) S.acc[i] = 0.f;
     __syncthreads();
     const uint32_t maxlast = S.maxlast;
@@ -294,71 +303,75 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(4))) void k
         uint32_t lim[2];
 #pragma unroll
         for (int q = 0; q < 2; ++q) lim[q] = last[q] > b0 ? min(last[q] - b0, (uint32_t)kB) * 16u : 0u;
-        for (int i = (int)n_step - 4; i >= 0; i -= 4) {
-            const uint2 q4 = list4[i >> 2];
-            const uint32_t id4[4] = {q4.x & 0xffffu, q4.x >> 16, q4.y & 0xffffu, q4.y >> 16};
-            // the four records together, ahead of the sums' LDS adds
-            BwdA A4[4];
-            BwdB B4[4];
-            BwdC C4[4];
+        auto walk = [&](auto bad_pixels) {
+            using Bad = decltype(bad_pixels);
+            for (int i = (int)n_step - 4; i >= 0; i -= 4) {
+                const uint2 q4 = list4[i >> 2];
+                const uint32_t id4[4] = {q4.x & 0xffffu, q4.x >> 16, q4.y & 0xffffu, q4.y >> 16};
+                // the four records together, ahead of the sums' LDS adds
+                BwdA A4[4];
+                BwdB B4[4];
+                BwdC C4[4];
 #pragma unroll
-            for (int u = 3; u >= 0; --u) {
-                A4[u] = *reinterpret_cast<const BwdA*>(ra + id4[u]);
-                B4[u] = *reinterpret_cast<const BwdB*>(rb + id4[u]);
-                C4[u] = *reinterpret_cast<const BwdC*>(rc + id4[u]);
-            }
-#pragma unroll
-            for (int u = 3; u >= 0; --u) {
-                const uint32_t off = id4[u];
-                const BwdA A = A4[u];
-                const BwdB B = B4[u];
-                const BwdC C = C4[u];
-                const float qmax = entry_qmax(B.nlo);
-                const float ry = fmaf(A.r, fy, A.c1), t2 = fmaf(A.s, fy, B.c2), t22 = fmaf(t2, t2, B.nlo);
-                float v[kNG];
-#pragma unroll
-                for (int t = 0; t < kNG; ++t) v[t] = 0.f;
-                bool has = false;
-#pragma unroll
-                for (int q = 0; q < 2; ++q) {
-                    const float t1 = fmaf(A.p, fx[q], ry);
-                    const float Q = fmaf(t1, t1, t22);
-                    const float al0 = fminf(0.99f, __builtin_amdgcn_exp2f(-Q));
-                    const bool on = Q <= qmax && off < lim[q];
-                    has = has || on;
-                    const float al = on ? al0 : 0.f;
-                    const float iom = __builtin_amdgcn_rcpf(1.f - al);
-                    const float Ti = Tc[q] * iom;
-                    const float wgt = al * Ti;
-                    const float gc = fmaf(gC0[q], C.col0, fmaf(gC1[q], C.col1, fmaf(gC2[q], C.col2, gD[q] * C.z)));
-                    const float dLda = fmaf(Ti, gc, -iom * behind[q]);
-                    behind[q] = fmaf(wgt, gc, behind[q]);
-                    Tc[q] = on ? Ti : Tc[q];
-                    const float h = al0 < 0.99f ? al * dLda : 0.f;
-                    const float s1 = h * t1;
-                    v[0] += h;
-                    v[1] += s1;
-                    v[2] = fmaf(s1, fx[q] - B.u, v[2]);
-                    v[6] = fmaf(gC0[q], wgt, v[6]);
-                    v[7] = fmaf(gC1[q], wgt, v[7]);
-                    v[8] = fmaf(gC2[q], wgt, v[8]);
-                    v[9] = fmaf(gD[q], wgt, v[9]);
+                for (int u = 3; u >= 0; --u) {
+                    A4[u] = *reinterpret_cast<const BwdA*>(ra + id4[u]);
+                    B4[u] = *reinterpret_cast<const BwdB*>(rb + id4[u]);
+                    C4[u] = *reinterpret_cast<const BwdC*>(rc + id4[u]);
                 }
-                if (__ballot(has) == 0) continue;
-                const float dy = fy - B.v;                  // shared by the thread's pixels, as t2
-                v[3] = v[1] * dy;
-                v[4] = v[0] * t2;
-                v[5] = v[4] * dy;
-                float s0, s1, s2;
-                ten_sums(v, odd1, odd2, &s0, &s1, &s2);
-                float* acc = S.acc + off / 16 * kEntryGrad;
-                if (k < 4) {
-                    if (s0 != 0.f) atomicAdd(acc + k, s0);
-                    if (s1 != 0.f) atomicAdd(acc + 4 + k, s1);
-                    if (k < 2 && s2 != 0.f) atomicAdd(acc + 8 + k, s2);
+#pragma unroll
+                for (int u = 3; u >= 0; --u) {
+                    const uint32_t off = id4[u];
+                    const BwdA A = A4[u];
+                    const BwdB B = B4[u];
+                    const BwdC C = C4[u];
+                    const float qmax = entry_qmax(B.nlo);
+                    const float ry = fmaf(A.r, fy, A.c1), t2 = fmaf(A.s, fy, B.c2), t22 = fmaf(t2, t2, B.nlo);
+                    float v[kNG];
+#pragma unroll
+                    for (int t = 0; t < kNG; ++t) v[t] = 0.f;
+                    bool has = false;
+#pragma unroll
+                    for (int q = 0; q < 2; ++q) {
+                        const float t1 = fmaf(A.p, fx[q], ry);
+                        const float Q = fmaf(t1, t1, t22);
+                        const float al0 = fminf(0.99f, __builtin_amdgcn_exp2f(-Q));
+                        const bool on = Q <= qmax && off < lim[q];
+                        has = has || on;
+                        const float al = on ? al0 : 0.f;
+                        const float iom = __builtin_amdgcn_rcpf(1.f - al);
+                        const float Ti = Tc[q] * iom;
+                        const float wgt = al * Ti;
+                        const float gc = fmaf(gC0[q], C.col0, fmaf(gC1[q], C.col1, fmaf(gC2[q], C.col2, gD[q] * C.z)));
+                        const float dLda = fmaf(Ti, gc, -iom * behind[q]);
+                        behind[q] = on ? fmaf(wgt, gc, behind[q]) : behind[q];
+                        Tc[q] = on ? Ti : Tc[q];
+                        const float h = on && al0 < 0.99f ? al * dLda : 0.f;
+                        const float s1 = h * t1;
+                        v[0] += h;
+                        v[1] += s1;
+                        v[2] = fmaf(s1, fx[q] - B.u, v[2]);
+                        v[6] = !Bad::value || on ? fmaf(gC0[q], wgt, v[6]) : v[6];
+                        v[7] = !Bad::value || on ? fmaf(gC1[q], wgt, v[7]) : v[7];
+                        v[8] = !Bad::value || on ? fmaf(gC2[q], wgt, v[8]) : v[8];
+                        v[9] = !Bad::value || on ? fmaf(gD[q], wgt, v[9]) : v[9];
+                    }
+                    if (__ballot(has) == 0) continue;
+                    const float dy = fy - B.v;                  // shared by the thread's pixels, as t2
+                    v[3] = v[1] * dy;
+                    v[4] = v[0] * t2;
+                    v[5] = v[4] * dy;
+                    float s0, s1, s2;
+                    ten_sums(v, odd1, odd2, &s0, &s1, &s2);
+                    float* acc = S.acc + off / 16 * kEntryGrad;
+                    if (k < 4) {
+                        if (s0 != 0.f) atomicAdd(acc + k, s0);
+                        if (s1 != 0.f) atomicAdd(acc + 4 + k, s1);
+                        if (k < 2 && s2 != 0.f) atomicAdd(acc + 8 + k, s2);
+                    }
                 }
             }
-        }
+        };
+        if (bad_wave) walk(std::true_type{}); else walk(std::false_type{});
         __syncthreads();
         // the tile's sums: twelve consecutive words per entry
         for (uint32_t i = threadIdx.x; i < cnt * kEntryGrad; i += kNT) {
