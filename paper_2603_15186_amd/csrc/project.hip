@@ -800,31 +800,34 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(6))) void k
 // places' cursors start at them.  One workgroup: a few thousand tiles are a
 // few steps.
 __global__ __launch_bounds__(1024) void k_tile_scan(TileListArgs a, const uint4* scan_tmp) {
-    __shared__ uint32_t sh[1024 / kWave + 1];
+    __shared__ uint4 sh[1024 / kWave + 1];
     if (threadIdx.x < kWave) sum_seen(scan_tmp, a.ctr);
     unsigned long long run = 0;
     for (uint32_t base = 0; base < a.total_tiles; base += 4 * 1024) {
         const uint32_t t0 = base + 4 * threadIdx.x;
-        uint32_t x[4], sum = 0;
+        // a tile may hold every entry of the cut (2^28), so a step's sums need
+        // 40 bits: the counts' low and high halves are scanned side by side
+        uint32_t x[4], lo16 = 0, hi16 = 0;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             x[j] = t0 + j < a.total_tiles ? a.tile_count[t0 + j] : 0u;
-            sum += x[j];
+            lo16 += x[j] & 0xffffu;
+            hi16 += x[j] >> 16;
         }
-        uint32_t tot;
-        // a step's sum stays below 2^32: at most 4,096 tiles of 2^20 entries
-        uint32_t ex = block_excl_scan<1024>(sum, sh, &tot);
+        uint4 tot;
+        const uint4 ex = block_excl_scan4<1024>(make_uint4(lo16, hi16, 0, 0), sh, &tot);
+        unsigned long long lo = run + ((unsigned long long)ex.y << 16) + ex.x;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
+            const unsigned long long hi = lo + x[j], cap = a.pair_cap;
             if (t0 + j < a.total_tiles) {
-                const unsigned long long lo = run + ex, hi = lo + x[j], cap = a.pair_cap;
                 const uint32_t start = (uint32_t)(lo < cap ? lo : cap);
                 a.ranges[t0 + j] = make_uint2(start, (uint32_t)(hi < cap ? hi : cap));
                 a.tile_count[t0 + j] = start;
             }
-            ex += x[j];
+            lo = hi;
         }
-        run += tot;
+        run += ((unsigned long long)tot.y << 16) + tot.x;
     }
     if (threadIdx.x == 0) {
         Counters* k = a.ctr;
