@@ -171,13 +171,18 @@ struct RowSpan {
     double ip, r, s, ey, ymax_at_x;          // 1 / p; ymax_at_x: height of the rightmost point
 };
 
+// These functions are compiled into every place that counts an entry's tiles
+// or lists them, by its own lane or by its wave, and all of them must find the
+// same tiles, else a pair lands outside its run: the sums' roundings are
+// written out, none is left to the compiler.
 __device__ __forceinline__ RowSpan row_span_init(const Proj& p) {
+#pragma clang fp contract(off)
     RowSpan r;
     r.ip = rcp64(p.p);
     r.r = p.r;
     r.s = p.s;
     r.ey = kBinReach * rcp64(r.s);
-    r.ymax_at_x = -r.r * r.ey * rsqrt64(r.r * r.r + r.s * r.s);
+    r.ymax_at_x = -r.r * r.ey * rsqrt64(fma(r.r, r.r, r.s * r.s));
     return r;
 }
 
@@ -185,15 +190,16 @@ __device__ __forceinline__ RowSpan row_span_init(const Proj& p) {
 // pixel-centre heights [ya, yb] (absolute); false if they do not meet.
 __device__ __forceinline__ bool band_span(const RowSpan& r, double u, double v, double ya, double yb, double* xa,
                                           double* xb) {
+#pragma clang fp contract(off)
     double y0 = fmax(ya - v, -r.ey);
     double y1 = fmin(yb - v, r.ey);
     if (y0 > y1) return false;
     const double yr = fmin(fmax(r.ymax_at_x, y0), y1);
     const double yl = fmin(fmax(-r.ymax_at_x, y0), y1);
     const double tr = r.s * yr, tl = r.s * yl;
-    const double sr = fmax(kBinQ - tr * tr, 1e-30), sl = fmax(kBinQ - tl * tl, 1e-30);
-    *xb = u + (sr * rsqrt64(sr) - r.r * yr) * r.ip + 1e-7;
-    *xa = u - (sl * rsqrt64(sl) + r.r * yl) * r.ip - 1e-7;
+    const double sr = fmax(fma(-tr, tr, kBinQ), 1e-30), sl = fmax(fma(-tl, tl, kBinQ), 1e-30);
+    *xb = fma(fma(sr, rsqrt64(sr), -(r.r * yr)), r.ip, u) + 1e-7;
+    *xa = fma(-fma(sl, rsqrt64(sl), r.r * yl), r.ip, u) - 1e-7;
     return true;
 }
 
@@ -201,6 +207,7 @@ __device__ __forceinline__ bool band_span(const RowSpan& r, double u, double v, 
 // reaches, within [tx_lo, tx_hi]; lo > hi when none.
 __device__ __forceinline__ void row_tiles(const RowSpan& r, double u, double v, int ty, int tw, int th, int H,
                                           int tx_lo, int tx_hi, int* lo, int* hi) {
+#pragma clang fp contract(off)
     double xa, xb;
     const double ya = ty * th + 0.5, yb = fmin((double)(ty * th + th - 1), (double)(H - 1)) + 0.5;
     if (!band_span(r, u, v, ya, yb, &xa, &xb)) {
