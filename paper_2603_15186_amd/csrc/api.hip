@@ -83,8 +83,11 @@ struct hgs_ctx {
     Counters* ctr_host = nullptr;     // pinned
     bool last_valid = false;
     int64_t regrows = 0;
-    int64_t seen_pairs = -1;          // pairs of the last render whose counters were read (-1: none since the
-                                      // scene, LOD or tile layout changed)
+    int64_t seen_pairs = -1;          // pairs of the last render that is known to have counted them (-1: none
+                                      // since the scene, LOD or tile layout changed)
+    unsigned long long* seen_host = nullptr;   // pinned: each pass's count, which the binning stores here with epoch
+    unsigned long long* seen_dev = nullptr;    // above it (the same memory, as the device addresses it)
+    uint32_t epoch = 1;               // of the scene, LOD, tile layout and passes: older counts are passed over
     bool shape_set = false;           // the compositor's launch shape was chosen by an option or a plan
     bool wide_shape = false;          // the last render (and the captured graph) used two pixels per thread by itself
     bool tile_lists = false;          // passes of the last render (and of the captured graph) used per-tile lists
@@ -363,6 +366,7 @@ hgs_status plan_passes(hgs_ctx* c, int want, bool upload_table) {
     if (upload_table || v0 != c->pass_v0) {
         upload_table = true;
         invalidate_graph(c);
+        ++c->epoch;
     }
     c->pass_v0 = v0;
     c->want_passes = want;
@@ -422,8 +426,8 @@ int bin_sorted(hgs_ctx* c, Work& W, const ProjectArgs& pa, EmitArgs ea, Composit
 
 // Whether the passes bin through per-tile lists (launch_emit_tiles) or
 // through the depth and pair sorts.  Both give the same lists; the choice
-// follows the pairs the last counted render had (a flat scene's entries when
-// none was counted yet), since the host does not know a render's own.
+// follows the pairs that the last render counted (a flat scene's entries when
+// none has counted any yet), since the host does not know a render's own.
 // Blocking renders of one view, by the sorts and by the lists: 120,000 pairs
 // in 1,200 tiles 224 and 169 us, 203,000 in 3,600 tiles 255 and 192, 472,000
 // in 1,200 273 and 272, 761,000 in 1,200 337 and 411, 921,000 of large
@@ -613,6 +617,8 @@ void enqueue_pass(hgs_ctx* c, hipStream_t s, int g) {
     ea.exact_tiles = c->ropts.exact_tiles;
     ea.scan_tmp = ca.scan_tmp;
     ea.ctr = ctr;
+    ea.seen = c->seen_dev + g;
+    ea.epoch = c->epoch;
     ea.tile_w = c->ropts.tile_w;
     ea.tile_h = c->ropts.tile_h;
 
@@ -698,17 +704,29 @@ Counters merge_passes(const hgs_ctx* c, uint64_t* need_cut_sum) {
     return m;
 }
 
-// The counters of a render have arrived: remember its pairs (per_tile_lists).
-void note_pairs(hgs_ctx* c) {
+// The pairs of the last render whose binning has ended (per_tile_lists),
+// whether or not the host has waited for it or read its counters, which other
+// calls use too.
+void learn_pairs(hgs_ctx* c) {
     int64_t pairs = 0;
-    for (int g = 0; g < n_passes(c); ++g) pairs += std::max(c->ctr_host[g].pairs, c->ctr_host[g].need_pairs);
+    for (int g = 0; g < n_passes(c); ++g) {
+        const unsigned long long v = __atomic_load_n(&c->seen_host[g], __ATOMIC_RELAXED);
+        if (v >> 32 != c->epoch) return;
+        pairs += (int64_t)(v & 0xffffffffull);
+    }
     c->seen_pairs = pairs;
+}
+
+// What the counts were counted on has changed (and with it every captured
+// render, which stores the epoch it was recorded in).
+void forget_pairs(hgs_ctx* c) {
+    ++c->epoch;
+    c->seen_pairs = -1;
 }
 
 hgs_status read_counters(hgs_ctx* c, hipStream_t s) {
     HIP_TRY(c, hipMemcpyAsync(c->ctr_host, c->counters.p, sizeof(Counters) * n_passes(c), hipMemcpyDeviceToHost, s));
     HIP_TRY(c, hipStreamSynchronize(s));
-    note_pairs(c);
     return HGS_OK;
 }
 
@@ -886,6 +904,8 @@ hgs_status hgs_create(int32_t device, hgs_ctx** out) {
     c->scratch = scr;
     if (ensure(c, c->counters, sizeof(Counters) * kMaxViews) != HGS_OK ||
         hipHostMalloc((void**)&c->ctr_host, sizeof(Counters) * kMaxViews, hipHostMallocDefault) != hipSuccess ||
+        hipHostMalloc((void**)&c->seen_host, sizeof(*c->seen_host) * kMaxViews, hipHostMallocDefault) != hipSuccess ||
+        hipHostGetDevicePointer((void**)&c->seen_dev, c->seen_host, 0) != hipSuccess ||
         hipEventCreateWithFlags(&c->views_copied, hipEventDisableTiming) != hipSuccess ||
         hipHostMalloc((void**)&c->dimg_host, sizeof(ImgGrad) * kMaxViews, hipHostMallocDefault) != hipSuccess ||
         hipEventCreateWithFlags(&c->dimg_copied, hipEventDisableTiming) != hipSuccess) {
@@ -893,6 +913,7 @@ hgs_status hgs_create(int32_t device, hgs_ctx** out) {
         return HGS_E_HIP;
     }
     std::memset(c->ctr_host, 0, sizeof(Counters) * kMaxViews);
+    std::memset(c->seen_host, 0, sizeof(*c->seen_host) * kMaxViews);
     *out = c;
     return HGS_OK;
 }
@@ -916,6 +937,7 @@ void hgs_destroy(hgs_ctx* c) {
     if (c->nav_active_host) (void)hipHostFree(c->nav_active_host);
     if (c->views_host) (void)hipHostFree(c->views_host);
     if (c->ctr_host) (void)hipHostFree(c->ctr_host);
+    if (c->seen_host) (void)hipHostFree(c->seen_host);
     if (c->views_copied) (void)hipEventDestroy(c->views_copied);
     if (c->dimg_copied) (void)hipEventDestroy(c->dimg_copied);
     if (c->dimg_host) (void)hipHostFree(c->dimg_host);
@@ -1045,7 +1067,7 @@ hgs_status hgs_load_scene(hgs_ctx* c, const hgs_gaussians* g, const hgs_hierarch
         c->mean_hi[k] = mhi[k];
     }
     c->depth_full = false;
-    c->seen_pairs = -1;
+    forget_pairs(c);
     c->loaded = true;
     c->mlp_loaded = false;
     c->last_valid = false;
@@ -1142,7 +1164,7 @@ hgs_status hgs_set_cameras(hgs_ctx* c, int32_t n, const hgs_camera* cams) {
     c->cams.assign(cams, cams + n);
     c->total_tiles = (uint32_t)tiles;
     c->tile_abs = tile_base;
-    if (!same_layout) c->seen_pairs = -1;
+    if (!same_layout) forget_pairs(c);
     if ((s = plan_passes(c, same_layout ? c->want_passes : 1, !same_layout))) return s;
     c->views_dirty = true;
     c->last_valid = false;
@@ -1159,7 +1181,7 @@ hgs_status hgs_set_lod(hgs_ctx* c, int32_t mode, float tau) {
     if (!(tau > 0.f) || !finite(tau)) return fail(c, HGS_E_INVALID, "tau must be a positive number");
     if (mode == HGS_LOD_LEARNED && !c->mlp_loaded) return fail(c, HGS_E_STATE, "learned LOD needs hgs_load_lod_mlp first");
     invalidate_graph(c);
-    if (mode != c->lod_mode || tau != c->tau) c->seen_pairs = -1;
+    if (mode != c->lod_mode || tau != c->tau) forget_pairs(c);
     c->lod_mode = mode;
     c->tau = tau;
     if (c->views_host) HIP_TRY(c, hipEventSynchronize(c->views_copied));
@@ -1200,7 +1222,7 @@ hgs_status relayout_tiles(hgs_ctx* c) {
     }
     c->total_tiles = (uint32_t)tiles;
     c->tile_abs = base;
-    c->seen_pairs = -1;
+    forget_pairs(c);
     c->last_valid = false;
     return plan_passes(c, c->want_passes, true);
 }
@@ -1334,6 +1356,7 @@ hgs_status hgs_render(hgs_ctx* c, void* stream, const hgs_output* outs) {
     }
     c->regrows = 0;
     for (int attempt = 0; attempt < 16; ++attempt) {
+        learn_pairs(c);
         if (const bool lists = per_tile_lists(c); lists != c->tile_lists) {
             invalidate_graph(c);
             c->tile_lists = lists;
@@ -1396,7 +1419,6 @@ hgs_status hgs_check(hgs_ctx* c) {
     if (!c) return HGS_E_INVALID;
     HIP_TRY(c, hipSetDevice(c->device));
     HIP_TRY(c, hipMemcpy(c->ctr_host, c->counters.p, sizeof(Counters) * n_passes(c), hipMemcpyDeviceToHost));
-    note_pairs(c);
     const Counters k = merge_passes(c, nullptr);
     if (k.overflow) {
         c->last_valid = false;

@@ -315,6 +315,8 @@ struct EmitArgs {
     bool exact_tiles;
     uint4* scan_tmp;
     Counters* ctr;
+    unsigned long long* seen;        // pinned host memory: receives epoch << 32 | the pass's pairs (report_pairs)
+    uint32_t epoch;
     int tile_w, tile_h;              // tile shape in pixels
     SortBins clear;                  // bins of the pair sort
 };
@@ -326,8 +328,8 @@ void launch_emit(const EmitArgs& a, hipStream_t s);
 
 // Per-tile lists instead of emission in depth order and the pair sort: the
 // sorted entries of every tile go to vals[1], the tiles' ranges to ranges.
-// Of EmitArgs: ntiles, bins, proj, cut_cap, exact_tiles, ctr and the tile
-// shape.
+// Of EmitArgs: ntiles, bins, proj, cut_cap, exact_tiles, ctr, seen, epoch and
+// the tile shape.
 struct TileListArgs {
     uint32_t* tile_count;            // the projection's counts; then the tiles' cursors
     uint32_t total_tiles;

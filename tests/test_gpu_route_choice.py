@@ -1,0 +1,79 @@
+"""Which renders the choice of binning goes by: the renders of the last few
+calls, counted whether or not they were checked, and nothing else that uses the
+device's counters."""
+import math
+
+import pytest
+
+from paper_2603_15186_amd.synth import make_random_box, workloads as W, yaw_camera
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def hgs():
+    from paper_2603_15186_amd import hgs
+    return hgs
+
+
+def _views():
+    """A view of few pairs (looking away from most of the scene) and one of many."""
+    near = yaw_camera(640, 480, 640.0, (2.0, -1.0, 1.5), math.pi / 2)
+    away = yaw_camera(640, 480, 640.0, (2.0, 3.7, 1.5), math.pi / 2)
+    return away, near
+
+
+@pytest.fixture()
+def r(hgs):
+    r = hgs.Renderer(0)
+    r.load_scene(make_random_box(70000, seed=1))       # too many for the lists while nothing is counted
+    r.set_option(hgs.HGS_OPT_TILE_SHAPE, (8 << 16) | 8)
+    yield r
+    r.close()
+
+
+def _step(r, cam, outs=None):
+    r.set_cameras([cam])
+    outs = r.render(outs)
+    torch.cuda.synchronize()
+    return r.route()["lists"], r.stats()["pairs"], [t.clone() for o in outs for t in o]
+
+
+@pytest.mark.parametrize("graph", [0, 1])
+def test_streams_without_checks_learn_their_pairs(hgs, r, graph):
+    light, heavy = _views()
+    want = _step(r, heavy)[2]
+    r.set_option(hgs.HGS_OPT_TILE_SHAPE, (16 << 16) | 16)   # forget the counts
+    r.set_option(hgs.HGS_OPT_TILE_SHAPE, (8 << 16) | 8)
+    r.set_option(hgs.HGS_OPT_USE_GRAPH, graph)
+    r.set_option(hgs.HGS_OPT_SYNC_CHECK, 0)
+    outs = r.alloc_outputs()
+    assert not _step(r, light, outs)[0]
+    assert _step(r, light, outs)[0]
+    for k in range(3):
+        lists, _, img = _step(r, heavy, outs)
+        assert all(torch.equal(a, b) for a, b in zip(want, img))
+        assert lists == (k == 0)
+    assert r.check() == hgs.HGS_OK
+
+
+def test_candidates_are_not_counted_as_a_render(hgs):
+    """Collecting candidates uses the same device counters; the next render
+    still goes by the last render."""
+    scene, cams = W.plan2m(scale=0.1, n_poses=1)
+    r = hgs.Renderer(0)
+    r.load_scene(scene)
+    r.set_option(hgs.HGS_OPT_TILE_SHAPE, (8 << 16) | 8)
+    r.set_option(hgs.HGS_OPT_EXACT_TILES, 0)
+    r.set_lod(hgs.HGS_LOD_THRESHOLD, 1.0)
+    r.set_cameras([yaw_camera(640, 480, 450.0, cams[0].position, math.atan2(cams[0].R[2][1], cams[0].R[2][0]))])
+    r.render()
+    assert r.stats()["pairs"] > 1 << 18
+    r.render()
+    assert not r.route()["lists"]
+    r.lod_candidates(64.0)
+    assert r.check() == hgs.HGS_OK
+    r.render()
+    assert not r.route()["lists"]
+    r.close()
