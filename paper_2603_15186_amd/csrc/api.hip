@@ -32,6 +32,10 @@ struct Work {
     DevMem pkey[2], pval[2], scan_tmp, hist;
 };
 
+struct DepthRange {                   // bit patterns of depths
+    uint32_t lo = 0, hi = 0xffffffffu;
+};
+
 }  // namespace
 
 struct hgs_ctx {
@@ -103,6 +107,7 @@ struct hgs_ctx {
     hipGraph_t graph = nullptr;
     hipGraphExec_t gexec = nullptr;
     bool graph_valid = false;
+    std::vector<DepthRange> graph_depths;   // of each pass, in the captured render (empty: none)
     int64_t graph_launches = 0;
     // stage timing: 6 events per render (start, cut, project, binning, composite start, end)
     bool stage_timing = false;
@@ -163,6 +168,7 @@ void invalidate_graph(hgs_ctx* c) {
     c->gexec = nullptr;
     c->graph = nullptr;
     c->graph_valid = false;
+    c->graph_depths.clear();
 }
 
 hgs_status ensure(hgs_ctx* c, DevMem& m, size_t bytes) {
@@ -465,8 +471,55 @@ bool wide_shape(const hgs_ctx* c) {
     return tiles / n_passes(c) >= kWideTiles && c->seen_pairs <= slack * 128 * tiles;
 }
 
-// One pipeline pass over the views of pass g (counters slot g).
-void enqueue_pass(hgs_ctx* c, hipStream_t s, int g) {
+// Bit patterns of the depths that views [v0, v1) can bin.  Binned depths lie
+// in (znear, distance to the farthest corner of the means' bounding box]:
+// they are sorted by their offset from the smallest near plane, in as many
+// bits as the range takes (all 32 bits where it is not known; a depth outside
+// it, which a camera matrix that is not a rotation can give, is reported as
+// kOvDepth and the batch is redone with all 32 bits).
+DepthRange depth_range(const hgs_ctx* c, int v0, int v1) {
+    if (c->depth_full) return {};
+    float zn = 0.f;
+    double dmax = 0.0;
+    for (int v = v0; v < v1; ++v) {
+        const ViewDev& d = c->views_host[v];
+        zn = v == v0 ? (float)d.znear : std::min(zn, (float)d.znear);
+        double far2 = 0.0;
+        for (int k = 0; k < 3; ++k) {
+            const double e = std::max(std::fabs(c->mean_lo[k] - d.o[k]), std::fabs(c->mean_hi[k] - d.o[k]));
+            far2 += e * e;
+        }
+        dmax = std::max(dmax, std::sqrt(far2));
+    }
+    const float top = (float)(dmax * (1.0 + 1e-6) + 1e-6);
+    uint32_t bb, tb;
+    std::memcpy(&bb, &zn, 4);
+    std::memcpy(&tb, &top, 4);
+    return zn > 0.f && tb > bb ? DepthRange{bb, tb} : DepthRange{};
+}
+
+// A captured render is replayed with other poses: its passes' depth ranges
+// cover those of every pose set since it was recorded, which is again when
+// one leaves them (a later pose then seldom does).
+void cover_depths(hgs_ctx* c) {
+    const int np = n_passes(c);
+    std::vector<DepthRange> want((size_t)np);
+    bool covered = (int)c->graph_depths.size() == np;
+    for (int g = 0; g < np; ++g) {
+        want[g] = depth_range(c, c->pass_v0[g], c->pass_v0[g + 1]);
+        if ((int)c->graph_depths.size() != np) continue;
+        const DepthRange& h = c->graph_depths[g];
+        covered = covered && h.lo <= want[g].lo && h.hi >= want[g].hi;
+        want[g] = {std::min(h.lo, want[g].lo), std::max(h.hi, want[g].hi)};
+    }
+    if (covered) return;
+    invalidate_graph(c);
+    c->graph_depths = want;
+}
+
+// One pipeline pass over the views of pass g (counters slot g); recording:
+// into a graph (cover_depths).
+void enqueue_pass(hgs_ctx* c, hipStream_t s, int g, bool recording) {
     Work& W = c->w[lane_of(c, g)];
     Counters* ctr = P<Counters>(c->counters) + g;
     const int v0 = c->pass_v0[g], v1 = c->pass_v0[g + 1];
@@ -530,36 +583,10 @@ void enqueue_pass(hgs_ctx* c, hipStream_t s, int g) {
     pa.lds_views = ca.group_children;
     pa.proj = P<Proj>(W.proj);
     pa.depth_key = P<uint32_t>(W.dkey[0]);
-    // Binned depths lie in (znear, distance to the farthest corner of the
-    // means' bounding box] of their view, so the sort needs only the bits
-    // that span that range of FP32 bit patterns (a depth outside raises
-    // kOvDepth and the batch is redone with all 32 bits).
-    int depth_bits = 32;
-    pa.depth_base = 0;
-    pa.depth_top = 0xffffffffu;
-    if (!c->depth_full) {
-        float zn = 0.f;
-        double dmax = 0.0;
-        for (int v = v0; v < v1; ++v) {
-            const ViewDev& d = c->views_host[v];
-            zn = v == v0 ? (float)d.znear : std::min(zn, (float)d.znear);
-            double far2 = 0.0;
-            for (int k = 0; k < 3; ++k) {
-                const double e = std::max(std::fabs(c->mean_lo[k] - d.o[k]), std::fabs(c->mean_hi[k] - d.o[k]));
-                far2 += e * e;
-            }
-            dmax = std::max(dmax, std::sqrt(far2));
-        }
-        const float top = (float)(dmax * (1.0 + 1e-6) + 1e-6);
-        uint32_t bb, tb;
-        std::memcpy(&bb, &zn, 4);
-        std::memcpy(&tb, &top, 4);
-        if (zn > 0.f && tb > bb) {
-            pa.depth_base = bb;
-            pa.depth_top = tb;
-            depth_bits = bits_for(tb - bb + 1u);
-        }
-    }
+    const DepthRange depths = recording ? c->graph_depths[g] : depth_range(c, v0, v1);
+    pa.depth_base = depths.lo;
+    pa.depth_top = depths.hi;
+    const int depth_bits = depths.hi == 0xffffffffu ? 32 : bits_for(depths.hi - depths.lo + 1u);
     pa.depth_val = P<uint32_t>(W.dval[0]);
     pa.ntiles = P<uint32_t>(W.ntiles);
     pa.bins = P<BinRec>(W.bins);
@@ -672,14 +699,14 @@ void enqueue_pass(hgs_ctx* c, hipStream_t s, int g) {
 // Passes in order; with two lanes the odd passes run on the second stream
 // (forked from and joined back into s by events), each lane in order on its
 // own work set.
-void enqueue_render(hgs_ctx* c, hipStream_t s) {
+void enqueue_render(hgs_ctx* c, hipStream_t s, bool recording) {
     const int np = n_passes(c);
     const bool two = c->lanes > 1 && np > 1 && c->lane_stream;
     if (two) {
         (void)hipEventRecord(c->fork_ev, s);
         (void)hipStreamWaitEvent(c->lane_stream, c->fork_ev, 0);
     }
-    for (int g = 0; g < np; ++g) enqueue_pass(c, two && (g & 1) ? c->lane_stream : s, g);
+    for (int g = 0; g < np; ++g) enqueue_pass(c, two && (g & 1) ? c->lane_stream : s, g, recording);
     if (two) {
         (void)hipEventRecord(c->join_ev, c->lane_stream);
         (void)hipStreamWaitEvent(s, c->join_ev, 0);
@@ -812,7 +839,7 @@ hgs_status time_plan(hgs_ctx* c, hipStream_t s, const hgs_output* outs, int reps
     if (st) return st;
     c->sync_check = false;
     HIP_TRY(c, hipEventRecord(e0, s));
-    for (int r = 0; r < reps; ++r) enqueue_render(c, s);
+    for (int r = 0; r < reps; ++r) enqueue_render(c, s, false);
     HIP_TRY(c, hipEventRecord(e1, s));
     HIP_TRY(c, hipEventSynchronize(e1));
     c->sync_check = true;
@@ -1366,11 +1393,11 @@ hgs_status hgs_render(hgs_ctx* c, void* stream, const hgs_output* outs) {
             c->wide_shape = wide;
         }
         if (c->use_graph && !c->stage_timing) {
+            cover_depths(c);
             if (!c->graph_valid) {
-                invalidate_graph(c);
                 if (!c->cap_stream) HIP_TRY(c, hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
                 HIP_TRY(c, hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal));
-                enqueue_render(c, c->cap_stream);
+                enqueue_render(c, c->cap_stream, true);
                 hipGraph_t g = nullptr;
                 const hipError_t ce = hipStreamEndCapture(c->cap_stream, &g);
                 if (ce != hipSuccess) return fail(c, HGS_E_HIP, "graph capture failed: %s", hipGetErrorString(ce));
@@ -1381,7 +1408,7 @@ hgs_status hgs_render(hgs_ctx* c, void* stream, const hgs_output* outs) {
             HIP_TRY(c, hipGraphLaunch(c->gexec, s));
             ++c->graph_launches;
         } else {
-            enqueue_render(c, s);
+            enqueue_render(c, s, false);
         }
         HIP_TRY(c, hipGetLastError());
         c->last_valid = true;
