@@ -36,6 +36,8 @@ struct DepthRange {                   // bit patterns of depths
     uint32_t lo = 0, hi = 0xffffffffu;
 };
 
+constexpr int kSeen = 8;              // render calls whose counts the choice of binning goes by
+
 }  // namespace
 
 struct hgs_ctx {
@@ -87,14 +89,16 @@ struct hgs_ctx {
     Counters* ctr_host = nullptr;     // pinned
     bool last_valid = false;
     int64_t regrows = 0;
-    int64_t seen_pairs = -1;          // pairs of the last render that is known to have counted them (-1: none
+    int64_t seen_pairs = -1;          // root mean square of the pairs seen at the last kSeen render calls (-1: none
                                       // since the scene, LOD or tile layout changed)
+    std::array<int64_t, kSeen> seen_last{};   // what they saw, each the last count of a render until then
+    int64_t n_seen = 0;
     unsigned long long* seen_host = nullptr;   // pinned: each pass's count, which the binning stores here with epoch
     unsigned long long* seen_dev = nullptr;    // above it (the same memory, as the device addresses it)
     uint32_t epoch = 1;               // of the scene, LOD, tile layout and passes: older counts are passed over
     bool shape_set = false;           // the compositor's launch shape was chosen by an option or a plan
-    bool wide_shape = false;          // the last render (and the captured graph) used two pixels per thread by itself
-    bool tile_lists = false;          // passes of the last render (and of the captured graph) used per-tile lists
+    bool wide_shape = false;          // the last render used two pixels per thread by itself
+    bool tile_lists = false;          // passes of the last render used per-tile lists
     int binning = 0;                  // HGS_OPT_BINNING
     int last_px = 0;                  // pixels per thread of the last render (0: none yet)
     uint32_t forced_cap = 0;          // test hook: start from this capacity
@@ -104,9 +108,10 @@ struct hgs_ctx {
     // captured render (HGS_OPT_USE_GRAPH): recorded on cap_stream, replayed
     // on the caller's stream while nothing it depends on has changed
     hipStream_t cap_stream = nullptr;
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t gexec = nullptr;
-    bool graph_valid = false;
+    // (a graph for each choice of binning and shape: a change of mind records
+    // nothing again, and takes no graph from under a launch)
+    hipGraph_t graph[4] = {};
+    hipGraphExec_t gexec[4] = {};
     std::vector<DepthRange> graph_depths;   // of each pass, in the captured render (empty: none)
     int64_t graph_launches = 0;
     // stage timing: 6 events per render (start, cut, project, binning, composite start, end)
@@ -163,11 +168,12 @@ void release(DevMem& m) {
 }
 
 void invalidate_graph(hgs_ctx* c) {
-    if (c->gexec) (void)hipGraphExecDestroy(c->gexec);
-    if (c->graph) (void)hipGraphDestroy(c->graph);
-    c->gexec = nullptr;
-    c->graph = nullptr;
-    c->graph_valid = false;
+    for (int i = 0; i < 4; ++i) {
+        if (c->gexec[i]) (void)hipGraphExecDestroy(c->gexec[i]);
+        if (c->graph[i]) (void)hipGraphDestroy(c->graph[i]);
+        c->gexec[i] = nullptr;
+        c->graph[i] = nullptr;
+    }
     c->graph_depths.clear();
 }
 
@@ -432,14 +438,15 @@ int bin_sorted(hgs_ctx* c, Work& W, const ProjectArgs& pa, EmitArgs ea, Composit
 
 // Whether the passes bin through per-tile lists (launch_emit_tiles) or
 // through the depth and pair sorts.  Both give the same lists; the choice
-// follows the pairs that the last render counted (a flat scene's entries when
-// none has counted any yet), since the host does not know a render's own.
+// follows the pairs that the last few renders counted (a flat scene's entries
+// when none has counted any yet), since the host does not know a render's own:
+// the root of their mean square, because light and heavy views may come in
+// turn, and what lists lose on a heavy one grows faster than its pairs.
 // Blocking renders of one view, by the sorts and by the lists: 120,000 pairs
 // in 1,200 tiles 224 and 169 us, 203,000 in 3,600 tiles 255 and 192, 472,000
 // in 1,200 273 and 272, 761,000 in 1,200 337 and 411, 921,000 of large
-// splats in 5,700 453 and 891.  A render that changes its mind needs half or
-// twice the pairs, so that views near the line do not keep re-recording a
-// graph.
+// splats in 5,700 453 and 891.  A change of mind needs half or twice the
+// pairs, so that views near the line keep to one way.
 constexpr int64_t kTileListPairs = 1 << 18;
 bool per_tile_lists(const hgs_ctx* c) {
     uint32_t tiles = 0;
@@ -461,9 +468,8 @@ bool per_tile_lists(const hgs_ctx* c) {
 // 1280 x 720 views, 190 to 210 pairs a tile: 14,400 tiles 119 and 120, 28,800
 // 223 and 194, 57,600 430 and 344; 1920 x 1080, 270 a tile, 48,960: 382 and 299;
 // 640 x 480, 640 to 700 a tile: 48,000 675 and 734, 115,200 1,545 and 1,458;
-// 320 x 240, 860 a tile, 76,800: 1,344 and 1,481.  (The pairs are those of the
-// last counted render; a change of mind needs a third more or less, for the
-// sake of recorded graphs.)
+// 320 x 240, 860 a tile, 76,800: 1,344 and 1,481.  (The pairs are those that
+// the lists go by; a change of mind needs a third more or less.)
 constexpr int64_t kWideTiles = 24576;
 bool wide_shape(const hgs_ctx* c) {
     if (c->shape_set || c->ropts.keep_state || c->ropts.count_nalg || c->seen_pairs < 0) return false;
@@ -741,13 +747,18 @@ void learn_pairs(hgs_ctx* c) {
         if (v >> 32 != c->epoch) return;
         pairs += (int64_t)(v & 0xffffffffull);
     }
-    c->seen_pairs = pairs;
+    c->seen_last[c->n_seen++ % kSeen] = pairs;
+    const int64_t n = std::min<int64_t>(c->n_seen, kSeen);
+    double sq = 0.0;
+    for (int64_t i = 0; i < n; ++i) sq += (double)c->seen_last[i] * (double)c->seen_last[i];
+    c->seen_pairs = (int64_t)std::sqrt(sq / (double)n);
 }
 
 // What the counts were counted on has changed (and with it every captured
 // render, which stores the epoch it was recorded in).
 void forget_pairs(hgs_ctx* c) {
     ++c->epoch;
+    c->n_seen = 0;
     c->seen_pairs = -1;
 }
 
@@ -1384,28 +1395,23 @@ hgs_status hgs_render(hgs_ctx* c, void* stream, const hgs_output* outs) {
     c->regrows = 0;
     for (int attempt = 0; attempt < 16; ++attempt) {
         learn_pairs(c);
-        if (const bool lists = per_tile_lists(c); lists != c->tile_lists) {
-            invalidate_graph(c);
-            c->tile_lists = lists;
-        }
-        if (const bool wide = wide_shape(c); wide != c->wide_shape) {
-            invalidate_graph(c);
-            c->wide_shape = wide;
-        }
+        c->tile_lists = per_tile_lists(c);
+        c->wide_shape = wide_shape(c);
         if (c->use_graph && !c->stage_timing) {
             cover_depths(c);
-            if (!c->graph_valid) {
+            const int gi = (c->tile_lists ? 1 : 0) + (c->wide_shape ? 2 : 0);
+            if (!c->gexec[gi]) {
                 if (!c->cap_stream) HIP_TRY(c, hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
                 HIP_TRY(c, hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal));
                 enqueue_render(c, c->cap_stream, true);
                 hipGraph_t g = nullptr;
                 const hipError_t ce = hipStreamEndCapture(c->cap_stream, &g);
                 if (ce != hipSuccess) return fail(c, HGS_E_HIP, "graph capture failed: %s", hipGetErrorString(ce));
-                c->graph = g;
-                HIP_TRY(c, hipGraphInstantiate(&c->gexec, c->graph, nullptr, nullptr, 0));
-                c->graph_valid = true;
+                if (c->graph[gi]) (void)hipGraphDestroy(c->graph[gi]);
+                c->graph[gi] = g;
+                HIP_TRY(c, hipGraphInstantiate(&c->gexec[gi], g, nullptr, nullptr, 0));
             }
-            HIP_TRY(c, hipGraphLaunch(c->gexec, s));
+            HIP_TRY(c, hipGraphLaunch(c->gexec[gi], s));
             ++c->graph_launches;
         } else {
             enqueue_render(c, s, false);

@@ -41,6 +41,27 @@ def _step(r, cam, outs=None):
 
 
 @pytest.mark.parametrize("graph", [0, 1])
+def test_alternating_views_keep_to_the_sorts(hgs, r, graph):
+    """Light and heavy views in turn: the heavy ones are never listed because
+    the light one before them was counted."""
+    r.set_option(hgs.HGS_OPT_USE_GRAPH, graph)
+    light, heavy = _views()
+    _, few, _ = _step(r, light)
+    assert few <= 1 << 18
+    assert _step(r, light)[0]
+    _, many, want = _step(r, heavy)
+    assert many > 1 << 19
+    for _ in range(4):
+        _step(r, light)
+        lists, _, img = _step(r, heavy)
+        assert not lists
+        assert all(torch.equal(a, b) for a, b in zip(want, img))
+    for _ in range(20):                                 # the heavy ones are over
+        lists = _step(r, light)[0]
+    assert lists
+
+
+@pytest.mark.parametrize("graph", [0, 1])
 def test_streams_without_checks_learn_their_pairs(hgs, r, graph):
     light, heavy = _views()
     want = _step(r, heavy)[2]
