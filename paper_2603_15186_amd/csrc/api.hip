@@ -112,6 +112,7 @@ struct hgs_ctx {
     // nothing again, and takes no graph from under a launch)
     hipGraph_t graph[4] = {};
     hipGraphExec_t gexec[4] = {};
+    int graph_pair_buf[4] = {};       // last_pair_buf of each
     std::vector<DepthRange> graph_depths;   // of each pass, in the captured render (empty: none)
     int64_t graph_launches = 0;
     // stage timing: 6 events per render (start, cut, project, binning, composite start, end)
@@ -1409,9 +1410,11 @@ hgs_status hgs_render(hgs_ctx* c, void* stream, const hgs_output* outs) {
                 if (ce != hipSuccess) return fail(c, HGS_E_HIP, "graph capture failed: %s", hipGetErrorString(ce));
                 if (c->graph[gi]) (void)hipGraphDestroy(c->graph[gi]);
                 c->graph[gi] = g;
+                c->graph_pair_buf[gi] = c->last_pair_buf;
                 HIP_TRY(c, hipGraphInstantiate(&c->gexec[gi], g, nullptr, nullptr, 0));
             }
             HIP_TRY(c, hipGraphLaunch(c->gexec[gi], s));
+            c->last_pair_buf = c->graph_pair_buf[gi];
             ++c->graph_launches;
         } else {
             enqueue_render(c, s, false);

@@ -98,3 +98,33 @@ def test_candidates_are_not_counted_as_a_render(hgs):
     r.render()
     assert not r.route()["lists"]
     r.close()
+
+
+def test_backward_after_each_replay(hgs):
+    """Gradients of renders replayed from either choice's graph, whichever was
+    recorded last: the pairs are read where that render left them."""
+    light, heavy = _views()
+    plain, graph = hgs.Renderer(0), hgs.Renderer(0)
+    for r in (plain, graph):
+        r.load_scene(make_random_box(100000, seed=1))
+        r.set_cameras([light])
+        r.set_option(hgs.HGS_OPT_BINNING, 1 if r is plain else 0)
+    graph.set_option(hgs.HGS_OPT_USE_GRAPH, 1)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    routes = []
+    for cam in [light, light, heavy, heavy, heavy, heavy, light] + [light] * 9 + [heavy]:
+        got = []
+        for r in (plain, graph):
+            r.set_cameras([cam])
+            outs = r.render()
+            grads = [tuple(torch.randn(t.shape, generator=gen.manual_seed(7), device="cuda") for t in outs[0])]
+            got.append(r.backward(grads))
+        torch.cuda.synchronize()
+        routes.append(graph.route()["lists"])
+        for k in got[0]:
+            a, b = got[0][k].double(), got[1][k].double()
+            # equal but for the order of the atomic sums
+            assert ((a - b).abs() <= 1e-4 * a.abs() + 1e-5 * a.abs().max()).all(), (len(routes), k)
+    assert routes[0] is False and routes[1] is True and routes[6] is False and routes[-1] is True
+    plain.close()
+    graph.close()
