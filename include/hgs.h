@@ -286,13 +286,14 @@ typedef struct {
  * 16x8, 16x16, 32x8 or 32x16 with 1, 2 or 4 pixels per compositing thread;
  * compositor batch depth 64/128/256, at most the tile's thread count;
  * persistent or one-workgroup-per-tile compositing for 16x16 tiles; radix
- * digit width 6..11) on the current scene, views, LOD and lanes (kept as
+ * digit width 6..11 where renders bin by the sorts) on the current scene, views, LOD and lanes (kept as
  * set; with kept pixel states, 16x16 tiles only), rendering every view reps
  * >= 1 times per candidate into internal buffers on `stream`, and keep the
  * fastest as the context's options (*out describes it; may be NULL).
- * Coordinate search: compositor choices first, then the digit width.  cache_path (NULL: none) names a text file of earlier plans keyed
- * by scene size, view sizes and LOD; a matching line is applied without
- * timing, a new plan is appended (the key includes the lanes setting).
+ * Coordinate search: compositor choices first, then the digit width.
+ * cache_path (NULL: none) names a text file of earlier plans keyed by scene
+ * size, view sizes and LOD; a matching line is applied without timing, a new
+ * plan is appended (the key includes the lanes setting).
  * Synchronous; leaves stage timing off. */
 hgs_status hgs_autotune(hgs_ctx* ctx, void* stream, const char* cache_path, int32_t reps, hgs_plan* out);
 

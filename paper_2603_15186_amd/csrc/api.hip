@@ -843,12 +843,14 @@ bool read_plan(const char* path, const std::string& key, hgs_plan* p) {
     return found;
 }
 
-// Mean render time of the current options over reps renders (after one
-// checked render that settles the buffer capacities).
+// Mean render time of the current options over reps renders, after two
+// checked ones: the first settles the buffer capacities and counts the pairs,
+// the second takes the binning and shape that renders of so many pairs take.
 hgs_status time_plan(hgs_ctx* c, hipStream_t s, const hgs_output* outs, int reps, hipEvent_t e0, hipEvent_t e1,
                      double* ms) {
-    hgs_status st = hgs_render(c, s, outs);
-    if (st) return st;
+    forget_pairs(c);
+    for (int k = 0; k < 2; ++k)
+        if (hgs_status st = hgs_render(c, s, outs)) return st;
     c->sync_check = false;
     HIP_TRY(c, hipEventRecord(e0, s));
     for (int r = 0; r < reps; ++r) enqueue_render(c, s, false);
@@ -1698,6 +1700,7 @@ hgs_status hgs_autotune(hgs_ctx* c, void* stream, const char* cache_path, int32_
             restore();
             return st;
         }
+        if (c->tile_lists) break;        // nothing is sorted by digits
         if (ms < best.ms) { best.sort_digit_bits = d; best.ms = ms; }
     }
     if ((st = apply(best.tile_w, best.tile_h, best.pixels_per_thread, best.batch_depth, best.persistent,
