@@ -651,12 +651,11 @@ void enqueue_pass(hgs_ctx* c, hipStream_t s, int g, bool recording) {
     ea.exact_tiles = c->ropts.exact_tiles;
     ea.scan_tmp = ca.scan_tmp;
     ea.ctr = ctr;
-    ea.seen = c->seen_dev + g;
-    ea.epoch = c->epoch;
     ea.tile_w = c->ropts.tile_w;
     ea.tile_h = c->ropts.tile_h;
 
     CompositeArgs xa{};
+    xa.report = {c->seen_dev + g, c->epoch};
     xa.pair_cap = c->pair_cap;
     xa.cut_cap = c->cut_cap;
     xa.ranges = P<uint2>(c->ranges) + t0;
@@ -687,6 +686,7 @@ void enqueue_pass(hgs_ctx* c, hipStream_t s, int g, bool recording) {
         ta.pair_cap = c->pair_cap;
         ta.ranges = xa.ranges;
         ta.ctr = ctr;
+        ta.report = xa.report;
         launch_emit_tiles(ea, ta, s);
     } else {
         pr = bin_sorted(c, W, pa, ea, xa, ctr, sa, view_pass, s);

@@ -109,7 +109,8 @@ __global__ void k_ranges_zero(uint2* ranges, uint32_t n) {
 // A key view << shift | local names the tile tile_base(view) + local of the
 // pass; equal keys form one run.
 __global__ void k_ranges(const uint32_t* __restrict__ keys, const Counters* ctr, uint32_t cap, uint2* ranges,
-                         uint32_t n_tiles, const ViewDev* views, int n_views, int shift) {
+                         uint32_t n_tiles, const ViewDev* views, int n_views, int shift, PairsReport report) {
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) report_pairs(report, ctr->pairs, ctr->need_pairs);
     __shared__ uint32_t s_base[kMaxViews];
     for (int v = threadIdx.x; v < n_views; v += blockDim.x) s_base[v] = views[v].tile_base;
     __syncthreads();
@@ -441,7 +442,7 @@ bool tile_shape_ok(int tw, int th, int px) {
 void launch_ranges(const CompositeArgs& a, hipStream_t s) {
     k_ranges_zero<<<1024, 256, 0, s>>>(a.ranges, a.total_tiles);
     k_ranges<<<4096, 256, 0, s>>>(a.keys, a.ctr, a.pair_cap, a.ranges, a.total_tiles, a.views, a.n_views,
-                                  a.key_shift);
+                                  a.key_shift, a.report);
 }
 
 void launch_composite(const CompositeArgs& a, hipStream_t s) {

@@ -315,8 +315,6 @@ struct EmitArgs {
     bool exact_tiles;
     uint4* scan_tmp;
     Counters* ctr;
-    unsigned long long* seen;        // pinned host memory: receives epoch << 32 | the pass's pairs (report_pairs)
-    uint32_t epoch;
     int tile_w, tile_h;              // tile shape in pixels
     SortBins clear;                  // bins of the pair sort
 };
@@ -326,10 +324,17 @@ constexpr size_t tile_sum_words(size_t cap) {
 }
 void launch_emit(const EmitArgs& a, hipStream_t s);
 
+// Where a pass's pair count goes for the next renders' choice of binning:
+// pinned host memory, which receives epoch << 32 | pairs (report_pairs).
+struct PairsReport {
+    unsigned long long* host;
+    uint32_t epoch;
+};
+
 // Per-tile lists instead of emission in depth order and the pair sort: the
 // sorted entries of every tile go to vals[1], the tiles' ranges to ranges.
-// Of EmitArgs: ntiles, bins, proj, cut_cap, exact_tiles, ctr, seen, epoch and
-// the tile shape.
+// Of EmitArgs: ntiles, bins, proj, cut_cap, exact_tiles, ctr and the tile
+// shape.
 struct TileListArgs {
     uint32_t* tile_count;            // the projection's counts; then the tiles' cursors
     uint32_t total_tiles;
@@ -339,10 +344,12 @@ struct TileListArgs {
     uint32_t pair_cap;
     uint2* ranges;
     Counters* ctr;
+    PairsReport report;
 };
 void launch_emit_tiles(const EmitArgs& e, const TileListArgs& a, hipStream_t s);
 
 struct CompositeArgs {
+    PairsReport report;              // (launch_ranges)
     const uint32_t* keys;            // pair sort keys (view << key_shift | tile within the view), grouped
     const uint32_t* vals;            // entry indices
     uint32_t pair_cap;

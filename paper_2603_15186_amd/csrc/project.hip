@@ -198,8 +198,8 @@ __device__ __forceinline__ bool band_span(const RowSpan& r, double u, double v, 
     const double yl = fmin(fmax(-r.ymax_at_x, y0), y1);
     const double tr = r.s * yr, tl = r.s * yl;
     const double sr = fmax(fma(-tr, tr, kBinQ), 1e-30), sl = fmax(fma(-tl, tl, kBinQ), 1e-30);
-    *xb = fma(fma(sr, rsqrt64(sr), -(r.r * yr)), r.ip, u) + 1e-7;
-    *xa = fma(-fma(sl, rsqrt64(sl), r.r * yl), r.ip, u) - 1e-7;
+    *xb = fma(fma(-r.r, yr, sr * rsqrt64(sr)), r.ip, u) + 1e-7;
+    *xa = fma(-fma(r.r, yl, sl * rsqrt64(sl)), r.ip, u) - 1e-7;
     return true;
 }
 
@@ -595,12 +595,6 @@ __device__ __forceinline__ void sum_seen(const uint4* scan_tmp, Counters* ctr) {
 }
 static_assert(kSeenSlots == kWave, "one place per lane");
 
-// The pass's pairs to the host, for the next renders' choice of binning (one
-// thread): a store that nobody waits for, where a copy and its event would
-// cost every render 2 to 8 us.
-__device__ __forceinline__ void report_pairs(const EmitArgs& a, uint32_t pairs) {
-    __hip_atomic_store(a.seen, (unsigned long long)a.epoch << 32 | pairs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-}
 
 // ---------------------------------------------------------------- emission
 
@@ -755,7 +749,6 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(6))) void k
                 if (need > k->need_pairs) k->need_pairs = need;
             }
             k->pairs = total < cap ? (uint32_t)total : cap;
-            report_pairs(a, (uint32_t)(total < 0xffffffffull ? total : 0xffffffffull));
         }
     }
     const uint32_t per = entries_per_block(m, 1024);
@@ -874,7 +867,7 @@ __global__ __launch_bounds__(kNT) void k_emit_tiles(EmitArgs a, TileListArgs l) 
     static_assert(kTileListMax <= 1u << 13 && kNT <= 256, "packed pairs");
     const uint32_t m = min(a.ctr->cut, a.cut_cap);
     const uint32_t per = entries_per_block(m, 256);
-    if (blockIdx.x == 0 && threadIdx.x == 0) report_pairs(a, max(a.ctr->pairs, a.ctr->need_pairs));
+    if (blockIdx.x == 0 && threadIdx.x == 0) report_pairs(l.report, a.ctr->pairs, a.ctr->need_pairs);
     if (blockIdx.x * per >= m) return;
     for (uint32_t t = threadIdx.x; t < l.total_tiles; t += kNT) s_count[t] = 0;
     const uint32_t slot = entry_slot(per);
