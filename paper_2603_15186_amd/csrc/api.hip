@@ -507,17 +507,27 @@ DepthRange depth_range(const hgs_ctx* c, int v0, int v1) {
 
 // A captured render is replayed with other poses: its passes' depth ranges
 // cover those of every pose set since it was recorded, which is again when
-// one leaves them (a later pose then seldom does).
+// one leaves them, and where that takes no more bits, every pose within the
+// box of the means (its diagonal).
 void cover_depths(hgs_ctx* c) {
     const int np = n_passes(c);
+    const bool recorded = (int)c->graph_depths.size() == np;
+    double diag2 = 0.0;
+    for (int k = 0; k < 3; ++k) diag2 += (c->mean_hi[k] - c->mean_lo[k]) * (c->mean_hi[k] - c->mean_lo[k]);
+    const float diag = (float)(std::sqrt(diag2) * (1.0 + 1e-6) + 1e-6);
+    uint32_t far;
+    std::memcpy(&far, &diag, 4);
     std::vector<DepthRange> want((size_t)np);
-    bool covered = (int)c->graph_depths.size() == np;
+    bool covered = recorded;
     for (int g = 0; g < np; ++g) {
-        want[g] = depth_range(c, c->pass_v0[g], c->pass_v0[g + 1]);
-        if ((int)c->graph_depths.size() != np) continue;
-        const DepthRange& h = c->graph_depths[g];
-        covered = covered && h.lo <= want[g].lo && h.hi >= want[g].hi;
-        want[g] = {std::min(h.lo, want[g].lo), std::max(h.hi, want[g].hi)};
+        DepthRange& w = want[g];
+        w = depth_range(c, c->pass_v0[g], c->pass_v0[g + 1]);
+        if (recorded) {
+            const DepthRange& h = c->graph_depths[g];
+            covered = covered && h.lo <= w.lo && h.hi >= w.hi;
+            w = {std::min(h.lo, w.lo), std::max(h.hi, w.hi)};
+        }
+        if (far > w.hi && bits_for(far - w.lo + 1u) == bits_for(w.hi - w.lo + 1u)) w.hi = far;
     }
     if (covered) return;
     invalidate_graph(c);
