@@ -48,10 +48,10 @@ __global__ void k_downsample2x(const float* __restrict__ src, int W, int H, floa
 // per region left the card idle on whole images (16 learned 1280 x 720
 // renders with their errors: 8.62 ms, 6.94 of it here, with one workgroup
 // per region and a 64-bit division per element; 1.61 ms in chunks).  Within
-// a workgroup the lanes of a row sit next to each other, a power of two of them up to a wave, so that
-// narrow windows still fill the workgroup and no index is divided.  Rows are
-// read 16 bytes per lane where both images' rows allow it (RegionDev::vec).
-// FP64 sums in a fixed order.
+// a workgroup the lanes of a row sit next to each other, a power of two of
+// them up to a wave, so that narrow windows still fill the workgroup and no
+// index is divided.  Rows are read 16 bytes per lane where both images' rows
+// allow it (RegionDev::vec).  FP64 sums in a fixed order.
 __device__ __forceinline__ double sq_diff(float a, float b) {
     const double d = (double)a - (double)b;
     return d * d;

@@ -4,16 +4,16 @@
 // Per cut entry (node, view): Sigma = R S S^T R^T (Supplementary Material of
 // NavGSim), camera-space mean t = W (mu - o), first-order perspective
 // Jacobian J at the mean (x/z and y/z clamped to the image's range widened
-// by 15 % of its size per side), Sigma' = J W Sigma W^T J^T + 0.3 I, 2D mean (fx tx/tz + cx,
-// fy ty/tz + cy), colour clamp(sum_k f_k Y_k(d) + 0.5, 0, 1).
+// by 15 % of its size per side), Sigma' = J W Sigma W^T J^T + 0.3 I, 2D mean
+// (fx tx/tz + cx, fy ty/tz + cy), colour clamp(sum_k f_k Y_k(d) + 0.5, 0, 1).
 //
 // The geometry runs in FP64 (which keeps the conic of edge-on sheets
 // accurate).  The pass is bound by its instructions, then by the 76 bytes an
 // entry writes: with IEEE divisions and square roots and divisions by the
 // tile sides 1,000 instructions an entry, 1,480 us for 38 M of them (writes
 // 470 at the rate of a copy); with rcp64, rsqrt64 and shifts 1,340, and
-// 370 -> 313 us for the 8 M entries of a 50-view batch.  Sigma' is formed as T T^T with
-// T = J W R S (2x3), which is symmetric positive semidefinite by
+// 370 -> 313 us for the 8 M entries of a 50-view batch.  Sigma' is formed as
+// T T^T with T = J W R S (2x3), which is symmetric positive semidefinite by
 // construction.  The depth key is the single-precision value of the FP64
 // camera depth, whose three-term sum is evaluated in a fixed order with
 // contraction disabled, so the depth order is an exact, reproducible result.
@@ -351,8 +351,8 @@ __device__ __forceinline__ double sphere_size(const ViewDev& V, float4 b) {
 // from a window of kProjectLdsViews views in LDS: all of them, or with more
 // the ones from the view group of the workgroup's first entry on (the groups
 // of a level follow one another; entries outside, where two levels meet, read
-// theirs from memory).  38 M entries of
-// 96 views without the window: 1,690 us, with it 1,500.
+// theirs from memory).  38 M entries of 96 views without the window: 1,690 us,
+// with it 1,500.
 //
 // PerTile: the entries go into per-tile lists (launch_emit_tiles): every
 // tile's entries are counted here -- per 256 entries in LDS, then one atomic

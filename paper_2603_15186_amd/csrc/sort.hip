@@ -3,20 +3,20 @@
 // A sort over `bits` key bits runs ceil(bits / D) passes with digits of
 // ceil(bits / passes) bits, D the widest digit allowed (6..11: up to 2048
 // buckets), so a 17-bit tile key takes two or three passes and a 32-bit depth
-// key three to six.  The input is cut into groups (group_size); a workgroup takes groups b, b + G, b + 2G, ... so that the groups in flight
-// at any moment form one contiguous window of the input and each digit's
-// output advances as one front (writes of neighbouring groups land next to
-// each other and fill whole cache lines).  Each pass is two launches with
-// no inter-workgroup waiting:
+// key three to six.  The input is cut into groups (group_size); a workgroup
+// takes groups b, b + G, b + 2G, ... so that the groups in flight at any moment
+// form one contiguous window of the input and each digit's output advances as
+// one front (writes of neighbouring groups land next to each other and fill
+// whole cache lines).  Each pass is two launches with no inter-workgroup
+// waiting:
 //   upsweep   : the digit histogram of every group (LDS atomics into
 //               per-wave histograms), also added to the sums of its 16 and
 //               of its 256 neighbours;
 //   downsweep : a group adds up what lies before it (whole 256s, then 16s,
-//               then groups: some 25 reads per digit), then is
-//               ranked stably sub-tile by sub-tile -- lanes
-//               with equal digits are found by ballots over the digit bits,
-//               per-wave counters live in LDS -- and its keys and values are
-//               scattered.
+//               then groups: some 25 reads per digit), then is ranked stably
+//               sub-tile by sub-tile -- lanes with equal digits are found by
+//               ballots over the digit bits, per-wave counters live in LDS --
+//               and its keys and values are scattered.
 // Element counts live in device memory so the launches can be captured in a
 // graph.
 #include "device_util.h"
@@ -307,10 +307,10 @@ __device__ __forceinline__ void downsweep_groups(SH& S, const uint32_t* __restri
 // (Four waves per SIMD, as many as the LDS of 8-bit digits allows: the
 // registers are capped at that.)
 template <int DB, int ITEMS, bool TOP>
-__global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(DB <= 8 ? 4 : 2))) void k_downsweep(const uint32_t* __restrict__ kin, const uint32_t* __restrict__ vin,
-                                                   uint32_t* __restrict__ kout, uint32_t* __restrict__ vout,
-                                                   const uint32_t* count, uint32_t cap, int shift, uint32_t MASK,
-                                                   HistDev H, TopBits top) {
+__global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(DB <= 8 ? 4 : 2)))
+void k_downsweep(const uint32_t* __restrict__ kin, const uint32_t* __restrict__ vin, uint32_t* __restrict__ kout,
+                 uint32_t* __restrict__ vout, const uint32_t* count, uint32_t cap, int shift, uint32_t MASK, HistDev H,
+                 TopBits top) {
     constexpr int NB = 1 << DB;
     constexpr int PER = NB / kNT > 0 ? NB / kNT : 1;      // digits per thread
     static_assert(kSortGroup % (kNT * ITEMS) == 0, "whole sub-tiles per group");
