@@ -121,18 +121,20 @@ __device__ __forceinline__ void slice_cells(const SliceArgs& s, const SliceRec& 
 // and slice_cells does.
 //
 // The bounds' errors are held below kEdge too, else slice_cells decides.  To
-// first order, with e = kUlp and cond = a c / det, which the products of the
-// inverse covariance lose to cancellation:
+// first order, in units of kUlp and with cond = a c / det, which the products
+// of the inverse covariance lose to cancellation:
 //   r2, and the q of a point on the ellipse as slice_cells forms it:
-//     er = e (4 cond r2 + lam dz^2 + amp + 8)  (exp and log of that size);
-//   positions, in cells: ec = e (coordinates + the ellipse's height);
-//   the top and bottom: half of er / r2 and of cond's e of the height, and ec;
+//     er = 4 cond r2 + lam dz^2 + amp + 8  (exp and log of that size);
+//   positions, in cells: ec = coordinates + the ellipse's height;
+//   the top and bottom: half of er / r2 and of cond times the height, and ec;
 //   a row's ends, x = (sqrt(dr) - r y) / p with dr = r2 - (s y)^2:
-//     (er + s reach ec cell) / (p sqrt(dr)) + (|r| ec cell + e (reach + |r| ey)) / p + ec.
+//     (er + s reach ec cell) / (p sqrt(dr)) + (|r| ec cell + reach + |r| ey) / p + ec,
+// where rows have dr > 1e-6 r2, and that is known: 16 er lie below it.
 // Against sums in 60 digits, ends of ellipses of 100 to 3e7 cells and cond up
 // to 1e5 were off by at most a fourteenth of this: 1e-13 cells at 100 cells and
 // cond near 1, 3e-10 at cond 1e5, 2e-8 at 1e4 cells, 4e-6, past kEdge, at 1e6
-// near the top.  (The checks cost 1.6 of 84 us for 2 M Gaussians and 15 planes.)
+// near the top.  (Once per pair for its worst row: 0.3 of 81 us for 2 M
+// Gaussians and 15 planes; with each row's own 1.9.)
 constexpr double kEdge = 1e-6;             // cells
 constexpr double kUlp = 0x1p-51;           // four times the relative error of a rounding
 __device__ __forceinline__ bool slice_rows(const SliceArgs& s, const SliceRec& G, int k, double icell) {
@@ -143,14 +145,11 @@ __device__ __forceinline__ bool slice_rows(const SliceArgs& s, const SliceRec& G
     if (!(r2 > 1e-8 && G.ip > 0.0)) return false;
     const double at = fabs(s.x0) + fabs(s.y0) + fabs(mx) + fabs(my);
     if (!(at * 1e-8 < s.cell)) return false;
-    const double reach = r2 * rsqrt64(r2), ey = reach * G.is, ym = reach * G.yr;
-    const double cond = G.c * G.is * G.is;
-    const double er = kUlp * (4.0 * cond * r2 + (fabs(drop) + G.amp + 8.0)), ec = kUlp * (at + ey) * icell;
-    if (!(er * ey * icell < r2 * (kEdge - ec))) return false;
-    // the ends' error: per_rs / sqrt(dr) + fixed
-    const double per_rs = G.ip * (er * icell + G.s * reach * ec);
-    const double fixed = G.ip * (fabs(G.r) * ec + kUlp * (reach + fabs(G.r) * ey) * icell) + ec;
-    const double dr_min = fmax(1e-6 * r2, 16.0 * er);
+    const double ir = rsqrt64(r2), reach = r2 * ir, ey = reach * G.is, ym = reach * G.yr;
+    const double er = fma(4.0 * G.c * G.is * G.is, r2, fabs(drop) + (G.amp + 8.0)), ec = (at + ey) * icell;
+    const double ends = fma(G.ip, fma(1e3 * G.s + fabs(G.r), ec, (er * (1e3 * ir) + reach + fabs(G.r) * ey) * icell), ec);
+    const double tops = fma(er * ir, ir * ey * icell, ec);
+    if (!(er < r2 * (1e-6 / 16.0 / kUlp) && ends < kEdge / kUlp && tops < kEdge / kUlp)) return false;
     const double u = (mx - s.x0) * icell, v = (my - s.y0) * icell;      // centre, in cells
     const double fj0 = floor(v - ey * icell - kEdge), fj1 = floor(v + ey * icell + kEdge);
     if (fj0 != floor(v - ey * icell + kEdge) || fj1 != floor(v + ey * icell - kEdge)) return false;
@@ -163,14 +162,12 @@ __device__ __forceinline__ bool slice_rows(const SliceArgs& s, const SliceRec& G
             const double yr = fmin(fmax(ym, y0), y1), yl = fmin(fmax(-ym, y0), y1);
             const double tr = G.s * yr, tl = G.s * yl;
             const double dr = fma(-tr, tr, r2), dl = fma(-tl, tl, r2);
-            const double rs = rsqrt64(fmax(dr, 1e-30)), ls = rsqrt64(fmax(dl, 1e-30));
-            const double xr = u + (dr * rs - G.r * yr) * G.ip * icell;
-            const double xl = u - (dl * ls + G.r * yl) * G.ip * icell;
+            const double xr = u + (dr * rsqrt64(fmax(dr, 1e-30)) - G.r * yr) * G.ip * icell;
+            const double xl = u - (dl * rsqrt64(fmax(dl, 1e-30)) + G.r * yl) * G.ip * icell;
             const double fi0 = floor(xl - kEdge), fi1 = floor(xr + kEdge);
             if (pass == 0) {
                 // (near the ellipse's top and bottom its width is not known well)
-                if (!(dr > dr_min && dl > dr_min && fma(per_rs, fmax(rs, ls), fixed) < kEdge) ||
-                    fi0 != floor(xl + kEdge) || fi1 != floor(xr - kEdge))
+                if (!(dr > 1e-6 * r2 && dl > 1e-6 * r2) || fi0 != floor(xl + kEdge) || fi1 != floor(xr - kEdge))
                     return false;
             } else if (fi1 >= 0.0 && fi0 <= (double)(s.nx - 1)) {
                 const int i0 = (int)fmax(fi0, 0.0), i1 = (int)fmin(fi1, (double)(s.nx - 1));
