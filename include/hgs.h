@@ -58,8 +58,9 @@ typedef int32_t hgs_status;
                                      while HGS_OPT_KEEP_STATE is on) */
 #define HGS_OPT_BATCH_DEPTH 4     /* Gaussians staged in LDS per batch: 64, 128 or 256 */
 #define HGS_OPT_USE_GRAPH 5       /* 1: capture the render in a hipGraph on first use and
-                                     replay it while cameras, LOD, options, scene and
-                                     buffers are unchanged (not with stage timing) */
+                                     replay it while the views' number and sizes, LOD,
+                                     options, scene and buffers are unchanged (poses may
+                                     change; not with stage timing) */
 #define HGS_OPT_PERSISTENT 6      /* 1: composite with a persistent tile queue */
 #define HGS_OPT_EXACT_TILES 7     /* 1 (default): bin only tiles the ellipse reaches */
 #define HGS_OPT_INITIAL_CAPACITY 8 /* >0: restart work buffers at this many entries
