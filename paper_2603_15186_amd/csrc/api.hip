@@ -507,16 +507,11 @@ DepthRange depth_range(const hgs_ctx* c, int v0, int v1) {
 
 // A captured render is replayed with other poses: its passes' depth ranges
 // cover those of every pose set since it was recorded, which is again when
-// one leaves them, and where that takes no more bits, every pose within the
-// box of the means (its diagonal).
+// one leaves them.  A range reaches as far as its number of bits does, so that
+// this takes a pose that needs another bit (or a nearer near plane).
 void cover_depths(hgs_ctx* c) {
     const int np = n_passes(c);
     const bool recorded = (int)c->graph_depths.size() == np;
-    double diag2 = 0.0;
-    for (int k = 0; k < 3; ++k) diag2 += (c->mean_hi[k] - c->mean_lo[k]) * (c->mean_hi[k] - c->mean_lo[k]);
-    const float diag = (float)(std::sqrt(diag2) * (1.0 + 1e-6) + 1e-6);
-    uint32_t far;
-    std::memcpy(&far, &diag, 4);
     std::vector<DepthRange> want((size_t)np);
     bool covered = recorded;
     for (int g = 0; g < np; ++g) {
@@ -527,7 +522,9 @@ void cover_depths(hgs_ctx* c) {
             covered = covered && h.lo <= w.lo && h.hi >= w.hi;
             w = {std::min(h.lo, w.lo), std::max(h.hi, w.hi)};
         }
-        if (far > w.hi && bits_for(far - w.lo + 1u) == bits_for(w.hi - w.lo + 1u)) w.hi = far;
+        if (w.hi != 0xffffffffu)
+            w.hi = std::max(w.hi, (uint32_t)std::min<uint64_t>(w.lo + (1ull << bits_for(w.hi - w.lo + 1u)) - 1,
+                                                               0x7f7fffffu));
     }
     if (covered) return;
     invalidate_graph(c);
